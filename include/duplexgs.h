@@ -161,7 +161,7 @@ typedef struct {
     int64_t n_box;         /* (pixel, Gaussian) pairs evaluated inside the Gaussian's box before termination */
     int64_t n_cell_hits;   /* (pixel, list entry) pairs that contributed (Duplex: cells; alpha: Gaussians) */
     int32_t device_error;  /* dgs_status of the last device-side error, 0 if none */
-    int32_t sort_passes;   /* radix passes of the last sort */
+    int32_t sort_passes;   /* 8-bit digits of the last list order: the tile id's, and the depth's 4 in the global order */
     int64_t n_cell_pixels; /* (pixel, cell) pairs the cell walks reach (listed cells of the pixel's tile before
                               termination; DGS_FLAG_STATS renders in the Duplex and LC-WSR modes, else 0) */
 } dgs_stats;
@@ -195,9 +195,10 @@ dgs_status dgs_set_overlap(dgs_ctx ctx, int32_t enable);
  *   DGS_LIST_ORDER_GLOBAL: the primitives (cells, or Gaussians in
  *     DGS_MODE_ALPHA) are radix-sorted by depth first and their keys emitted
  *     in that order, then stably sorted on the tile bits;
- *   DGS_LIST_ORDER_PER_TILE: the keys are emitted in primitive-id order,
- *     stably sorted on the tile bits, and each tile's run is then sorted by
- *     (depth, id) on its own (fast when the lists are short);
+ *   DGS_LIST_ORDER_PER_TILE: the entries are counted into their tiles' runs
+ *     and each run is then sorted by (depth, id) on its own (fast when the
+ *     lists are short; a grid of tiles too large for the counters -- beyond
+ *     about 131,000 tiles -- takes the global way);
  *   DGS_LIST_ORDER_AUTO (default): per tile for per-cell lists (Duplex,
  *     LC-WSR) when the context's last such frame had at most 8 keys per
  *     cell, at most 1024 keys per screen tile on

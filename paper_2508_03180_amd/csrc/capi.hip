@@ -659,12 +659,15 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     if ((st = ensure(c, P, M, want_keys, tiles)) != DGS_OK) return st;
     const uint32_t cap = (uint32_t)c->cap_keys;
     hipStream_t q = c->stream;
-    const bool overlap = cells && !c->timing && c->two_streams && ensure_aux(c);
     // the lists' depth order: a depth sort of the primitives (ties by id)
     // before the key emission, or, when the tile lists are short, a sort of
     // each tile's run after the tile sort (the same order); with the second
     // stream, the work queue is then built there beside the per-tile sort
-    const bool per_tile = per_tile_order(c, tiles, cells);
+    const int chunks = per_tile_order(c, tiles, cells)
+                           ? bin_chunks(P, k.TX, k.TY, 2 * c->cap_keys, c->sort_status_cap)
+                           : 0;
+    const bool per_tile = chunks > 0;
+    const bool overlap = cells && !c->timing && c->two_streams && ensure_aux(c);
     // buffers the backward replays: a saved frame's own, else the context's
     float* cell_v = save ? save->cell_v : c->cell_v;
     GRec* recs = save ? save->recs : c->recs;
@@ -677,9 +680,11 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
         // per-frame zeroing: digit histograms, scan/sort tickets and the
         // compositor queue (misc[1..12]), tile ranges, statistics counters
         ClearList cl;
-        cl.add(c->hist, 8 * 256);
         cl.add(c->misc + 1, 12);
-        cl.add(ranges, 2 * (size_t)tiles);
+        if (!per_tile) {
+            cl.add(c->hist, 8 * 256);
+            cl.add(ranges, 2 * (size_t)tiles);
+        }
         if (o.stats || save) cl.add((uint32_t*)c->counters, 10);
         cl.bump = c->misc + 13;
         FrameK f{k, o, out->color, out->weight_sum, out->final_T, out->last, nullptr, nullptr, nullptr, nullptr};
@@ -721,36 +726,44 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     }
     sm.mark(2);
     const uint64_t* prect = cells ? c->p_rect : c->grect;
-    const uint32_t* order = nullptr;  // null: keys emitted in primitive-id order
-    if (!per_tile) {
+    const int tbits = tile_bits(tiles);
+    uint32_t* svals = c->vals0;
+    bool in1 = false;
+    if (per_tile) {
+        sm.mark(3);
+        sm.mark(4);
+        // the counters take the second key buffer, which is free until the per-tile sort
+        launch_bin_tiles(q, BinArgs{prect, c->p_depth, P, k.TX, k.TY, chunks, reinterpret_cast<uint32_t*>(c->keys1), cap,
+                                    c->keys0, ranges, c->misc + 0, c->sort_status, c->misc + 13, c->misc + 1, c->dev_err,
+                                    cells ? c->load_dev : nullptr});
+        sm.mark(5);
+        sm.mark(6);
+        // the same launch also builds the work queue
+        launch_tile_depth_sort(q, ranges, tiles, c->keys0, svals, c->keys1, save ? save->vals : nullptr,
+                               cells ? kSplitLenCells : kSplitLenGauss, torder, queue,
+                               cells ? c->load_dev + 1 : nullptr, (uint32_t)P);
+    } else {
         launch_prim_keys(q, P, c->p_ntiles, c->p_depth, c->pk0, c->pv0, c->hist);
         const SortScratch ps{c->hist, c->psort_status, c->misc + 2};
         const bool pin1 = launch_radix_sort32(q, c->pk0, c->pv0, c->pk1, c->pv1, (uint32_t)P, ps, c->misc + 13, 1,
                                               c->dev_err);
-        order = pin1 ? c->pv1 : c->pv0;
+        const uint32_t* order = pin1 ? c->pv1 : c->pv0;
+        sm.mark(3);
+        launch_exclusive_scan(q, c->p_ntiles, c->p_offsets, P, c->misc + 0, c->scan_status, c->misc + 13, c->misc + 1,
+                              c->dev_err, order);
+        launch_emit_keys(q, P, order, c->p_ntiles, c->p_offsets, prect, c->p_depth, k.TX, cap, c->keys0, c->vals0,
+                         c->hist + 4 * 256, sort_passes(tbits), c->dev_err);
+        sm.mark(4);
+        // stable sort on the tile bits
+        const SortScratch ss{c->hist + 4 * 256, c->sort_status, c->misc + 6};
+        in1 = launch_radix_sort(q, c->keys0, c->vals0, c->keys1, c->vals1, c->misc + 0, cap, tbits, ss, c->misc + 13,
+                                c->dev_err, true, 32, 5);
+        svals = in1 ? c->vals1 : c->vals0;
+        sm.mark(5);
+        launch_tile_ranges(q, in1 ? c->keys1 : c->keys0, c->misc + 0, cap, ranges, svals, save ? save->vals : nullptr,
+                           cells ? c->load_dev : nullptr, (uint32_t)tiles);
+        sm.mark(6);
     }
-    sm.mark(3);
-    launch_exclusive_scan(q, c->p_ntiles, c->p_offsets, P, c->misc + 0, c->scan_status, c->misc + 13, c->misc + 1,
-                          c->dev_err, order);
-    const int tbits = tile_bits(tiles);
-    launch_emit_keys(q, P, order, c->p_ntiles, c->p_offsets, prect, c->p_depth, k.TX, cap, c->keys0, c->vals0,
-                     c->hist + 4 * 256, sort_passes(tbits), c->dev_err);
-    sm.mark(4);
-    // stable sort on the tile bits
-    const SortScratch ss{c->hist + 4 * 256, c->sort_status, c->misc + 6};
-    const bool in1 = launch_radix_sort(q, c->keys0, c->vals0, c->keys1, c->vals1, c->misc + 0, cap, tbits, ss,
-                                       c->misc + 13, c->dev_err, true, 32, 5);
-    uint64_t* skeys = in1 ? c->keys1 : c->keys0;
-    uint32_t* svals = in1 ? c->vals1 : c->vals0;
-    sm.mark(5);
-    launch_tile_ranges(q, skeys, c->misc + 0, cap, ranges, svals, save && !per_tile ? save->vals : nullptr,
-                       cells ? c->load_dev : nullptr, (uint32_t)tiles);
-    sm.mark(6);
-    // per tile: the same launch also builds the work queue
-    if (per_tile)
-        launch_tile_depth_sort(q, ranges, tiles, skeys, svals, in1 ? c->keys0 : c->keys1,
-                               save ? save->vals : nullptr, cells ? kSplitLenCells : kSplitLenGauss, torder, queue,
-                               cells ? c->load_dev + 1 : nullptr, (uint32_t)P);
     sm.mark(7);
     CompositeArgs a;
     a.ranges = ranges;
@@ -791,6 +804,7 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     c->last_gauss = M;
     c->last_tiles = tiles;
     c->last_in_1 = in1;
+    c->last_binned = per_tile;
     return launched(c);
 }
 
@@ -982,7 +996,10 @@ dgs_status dgs_read_lists(dgs_ctx c, uint64_t* keys, uint32_t* values, uint32_t*
     if ((int64_t)total > c->cap_keys) total = (uint32_t)c->cap_keys;
     const uint64_t* sk = c->last_in_1 ? c->keys1 : c->keys0;
     const uint32_t* sv = c->last_in_1 ? c->vals1 : c->vals0;
-    if (keys && total) hipMemcpyAsync(keys, sk, total * sizeof(uint64_t), hipMemcpyDeviceToDevice, c->stream);
+    if (keys && total && c->last_binned)
+        launch_list_keys(c->stream, c->cur_ranges, (int)c->last_tiles, sv, c->p_depth, keys);
+    else if (keys && total)
+        hipMemcpyAsync(keys, sk, total * sizeof(uint64_t), hipMemcpyDeviceToDevice, c->stream);
     if (values && total) hipMemcpyAsync(values, sv, total * sizeof(uint32_t), hipMemcpyDeviceToDevice, c->stream);
     if (ranges && c->cur_ranges)
         hipMemcpyAsync(ranges, c->cur_ranges, 2 * c->last_tiles * sizeof(uint32_t), hipMemcpyDeviceToDevice,

@@ -613,7 +613,7 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t* __restrict_
                                                      uint32_t prims) {
     __shared__ uint32_t s_cnt[kOrderClasses];
     __shared__ uint32_t s_part[1024];
-    build_work_queue(ranges, ntiles, split_len, order, queue, s_cnt, s_part, (int)threadIdx.x, long_stat, prims);
+    build_work_queue<1024>(ranges, ntiles, split_len, order, queue, s_cnt, s_part, (int)threadIdx.x, long_stat, prims);
 }
 
 static unsigned persistent_grid(int tiles) {

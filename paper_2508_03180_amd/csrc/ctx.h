@@ -105,6 +105,7 @@ struct dgs_ctx_s {
     int last_mode = -1, last_passes = 0;
     int64_t last_prims = 0, last_gauss = 0, last_tiles = 0;
     bool last_in_1 = false;
+    bool last_binned = false;  // the lists were made by counting: no keys are kept
 
     uint32_t* cur_ranges = nullptr;  // tile ranges of the last render (the context's or a saved frame's)
 

@@ -81,19 +81,46 @@ void launch_emit_keys(hipStream_t st, int P, const uint32_t* order, const uint32
                       const uint32_t* offsets, const uint64_t* prect, const uint32_t* depth, int TX, uint32_t cap,
                       uint64_t* keys, uint32_t* vals, uint32_t* hist, int tile_passes, int* err);
 
+// Tile lists by counting, for the per-tile order: one entry (depth bits <<
+// 32 | id) per (primitive, touched tile) in its tile's run, in no particular
+// order inside the run; the tiles' ranges (clamped to the capacity) and the
+// entry total.
+struct BinArgs {
+    const uint64_t* prect;  // pixel rectangles (kEmptyRect: culled)
+    const uint32_t* depth;
+    int P, TX, TY;
+    int chunks;        // from bin_chunks
+    uint32_t* counts;  // the counters given to bin_chunks
+    uint32_t cap;
+    uint64_t* ent;     // [cap]
+    uint32_t* ranges;  // written whole
+    uint32_t* total;
+    uint64_t* status;  // look-back words, tag j = 0
+    const uint32_t* epoch;
+    uint32_t* ticket;  // zero beforehand
+    int* err;
+    uint64_t* load;    // as for launch_tile_ranges
+};
+// Chunks of primitives the counting works in, for P primitives on a grid of
+// TX x TY tiles with `words` 32-bit counters and `status_words` look-back
+// words at hand; 0 when the grid is too large for the counting.
+int bin_chunks(int64_t P, int TX, int TY, int64_t words, size_t status_words);
+void launch_bin_tiles(hipStream_t st, const BinArgs& a);
+
+// Per-tile depth order: each tile's run of ent (depth bits << 32 | id) in
+// ascending order; the ids go to vals, and also to vcopy when set.  ent and
+// spare (a buffer of its size) are scratch.  The same launch builds the
+// compositor's work queue (as launch_tile_order; long_stat, prims too).
+void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, uint64_t* ent, uint32_t* vals,
+                            uint64_t* spare, uint32_t* vcopy, uint32_t split_len, uint32_t* order, uint32_t* queue,
+                            uint64_t* long_stat = nullptr, uint32_t prims = 0);
+// Keys tile << 32 | depth bits of ordered lists (vals by ranges).
+void launch_list_keys(hipStream_t st, const uint32_t* ranges, int tiles, const uint32_t* vals, const uint32_t* depth,
+                      uint64_t* keys);
+
 // [start, end) per tile of the sorted keys; ranges (2 words per tile) must
 // be zero beforehand (tiles without keys keep [0, 0)).  With vout set, the
 // sorted values vin are also copied there (a saved frame's own lists).
-// Per-tile depth order: each tile's run of the tile-sorted keys (emitted in
-// primitive-id order) sorted by (depth bits, id) in place; values also into
-// vcopy when set; spare: a free u64 buffer of the key capacity (used by runs
-// longer than what one workgroup sorts in registers).  The same launch
-// builds the compositor's work queue (as launch_tile_order).
-// long_stat, prims: as for launch_tile_order.
-void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, uint64_t* keys, uint32_t* vals,
-                            uint64_t* spare, uint32_t* vcopy, uint32_t split_len, uint32_t* order, uint32_t* queue,
-                            uint64_t* long_stat = nullptr, uint32_t prims = 0);
-
 // load (nullable, pinned host memory): receives tiles << 32 | key count.
 void launch_tile_ranges(hipStream_t st, const uint64_t* keys, const uint32_t* n_ptr, uint32_t cap,
                         uint32_t* ranges, const uint32_t* vin = nullptr, uint32_t* vout = nullptr,
