@@ -23,6 +23,7 @@
 #include "cells.h"
 #include "common.h"
 #include "launch.h"
+#include "order.h"
 
 namespace dgs {
 
@@ -130,18 +131,17 @@ __device__ inline BRec read_brec(uint32_t lb, int i) {
     return e;
 }
 
-// Backward of a whole 16x16 tile (NS = 4: lane l holds pixel (l & 15,
-// 4 j + (l >> 4)) of strip j) or of one 16x8 half (NS = 2, strips s0 and
-// s0 + 1), in the forward compositor's layout and with its exact gate
-// arithmetic.  Each
+// Backward of a whole tile (NS = 4) or of one half (2), in the forward
+// compositor's layout and with its exact gate arithmetic.  Each
 // pixel walks back from its own last contributing entry; per member, the
 // lane first sums its pixels' contributions, then the wavefront reduces
 // them once for the tile.
 template <int NS, bool RAGGED>
-__device__ inline void duplex_tile_bwd(const BwdArgs& a, int tile, int s0, int lane, GRec* lds) {
+__device__ inline void duplex_tile_bwd(const BwdArgs& a, int tile, int part, int lane, GRec* lds) {
     const CamK& k = a.k;
-    const int tx0 = (tile % k.TX) * kTile, ty0 = (tile / k.TX) * kTile;
-    const int px = tx0 + (lane & 15), py0 = ty0 + 4 * s0 + (lane >> 4);
+    constexpr int W = Block<NS>::kCols, RW = Block<NS>::kRows;
+    const Block<NS> bl((tile % k.TX) * kTile, (tile / k.TX) * kTile, part);
+    const int px = bl.x + Block<NS>::column(lane), py0 = bl.y + Block<NS>::row(lane);
     const uint32_t start = a.ranges[2 * tile], len = a.ranges[2 * tile + 1] - start;
     const int K = a.K;
     const uint32_t kmask = member_mask(K);
@@ -194,13 +194,13 @@ __device__ inline void duplex_tile_bwd(const BwdArgs& a, int tile, int s0, int l
             const int x0 = __float_as_int(r2.y), y0 = __float_as_int(r2.z);
             const uint32_t wxy = __float_as_uint(r2.w);
             const int x1 = x0 + (int)(wxy & 0xffffu), y1 = y0 + (int)(wxy >> 16);
-            if (x0 <= tx0 + 15 && x1 >= tx0) {
-                const int lo = max(x0, tx0) - tx0, hi = min(x1, tx0 + 15) - tx0;
+            if (x0 <= bl.x + W - 1 && x1 >= bl.x) {
+                const int lo = max(x0, bl.x) - bl.x, hi = min(x1, bl.x + W - 1) - bl.x;
                 rcols = ((2u << (hi - lo)) - 1u) << lo;
 #pragma unroll
                 for (int j = 0; j < NS; j++) {
-                    const int sy0 = ty0 + 4 * (s0 + j);
-                    if (y0 <= sy0 + 3 && y1 >= sy0) sm |= 1u << j;
+                    const int sy0 = bl.y + RW * j;
+                    if (y0 <= sy0 + RW - 1 && y1 >= sy0) sm |= 1u << j;
                 }
             }
         }
@@ -237,8 +237,7 @@ __device__ inline void duplex_tile_bwd(const BwdArgs& a, int tile, int s0, int l
 #pragma unroll
                 for (int j = 0; j < NS; j++) {
                     if (am[j] != ~0ull) {
-                        uint32_t ac = (uint32_t)(am[j] | (am[j] >> 32));
-                        ac = (ac | (ac >> 16)) & 0xffffu;  // columns (lane & 15) with a pixel reaching the cell
+                        const uint32_t ac = active_columns<NS>(am[j]);  // columns with a pixel reaching the cell
                         // Bm[j]: the records touching strip j
                         mj[j] = (uint32_t)((__ballot((rcols & ac) != 0u) & Bm[j]) >> base) & cm;
                     }
@@ -369,25 +368,30 @@ __global__ __launch_bounds__(256) void k_composite_bwd(BwdArgs a) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     GRec* lds = s_rec[wave];
     const uint32_t nitems = a.queue[1];
-    for (;;) {
-        uint32_t t = 0;
-        if (lane == 0) t = atomicAdd(a.queue, 1u);
-        // lane 0's ticket in a scalar register: the item, its tile and its
-        // half are then wavefront-uniform, and so is all loop control below
-        t = __builtin_amdgcn_readfirstlane(t);
-        if (t >= nitems) break;
+    ItemSource src;
+    // as in the forward: the item's number in a scalar register
+    for (uint32_t t = __builtin_amdgcn_readfirstlane(first_item<kBwdWaves, 4>(wave, nitems, src)); t < nitems;
+         t = next_item(a.queue, src, lane)) {
         const uint32_t item = a.order[t];
         const int tile = (int)(item >> 3), mode = (int)(item & 7u);
-        // half-tile items (the tiles with the longest lists, which set the
-        // kernel's span) issue ahead of whole-tile items on their SIMD
-        if (mode != 0)
+        // a tile that the forward walks in quarters is walked here as it would
+        // be without them, by the items of its even quarters or of the first: a
+        // Gaussian's gradient then has no more terms, whose order is free
+        bool whole = mode == 0;
+        if (mode >= 4) {
+            whole = a.ranges[2 * tile + 1] - a.ranges[2 * tile] < kSplitLenCells;
+            if (whole ? mode != 4 : (mode & 1) != 0) continue;
+        }
+        // split tiles' items, which set the kernel's span, issue ahead of
+        // whole tiles' on their SIMD
+        if (!whole)
             __builtin_amdgcn_s_setprio(3);
         else
             __builtin_amdgcn_s_setprio(0);
-        if (mode == 0)
+        if (whole)
             duplex_tile_bwd<4, RAGGED>(a, tile, 0, lane, lds);
         else
-            duplex_tile_bwd<2, RAGGED>(a, tile, 2 * (mode - 2), lane, lds);
+            duplex_tile_bwd<2, RAGGED>(a, tile, mode >= 4 ? (mode - 4) >> 1 : mode - 2, lane, lds);
     }
 }
 

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "ctx.h"
+#include "order.h"
 
 using namespace dgs;
 
@@ -275,7 +276,7 @@ dgs_status acquire_frame(dgs_ctx c, int64_t N, int64_t M, int64_t keys, int64_t 
         c->frames.push_back(f);
     }
     hipError_t e = hipSuccess;
-    if (!f->info && (e = hipMalloc((void**)&f->info, 16 * sizeof(uint32_t))) != hipSuccess) goto oom;
+    if (!f->info && (e = hipMalloc((void**)&f->info, kQueueWords * sizeof(uint32_t))) != hipSuccess) goto oom;
     if (M > f->cap_recs) {
         if ((e = grow(f->recs, M, c->stream)) != hipSuccess) goto oom;
         f->cap_recs = M;
@@ -416,6 +417,7 @@ dgs_status dgs_create(int device, void* hip_stream, dgs_ctx* out) {
         hipMalloc((void**)&c->dev_err, sizeof(int)) != hipSuccess ||
         hipMalloc((void**)&c->counters, 5 * sizeof(unsigned long long)) != hipSuccess ||
         hipMalloc((void**)&c->frame, sizeof(FrameK)) != hipSuccess ||
+        hipMalloc((void**)&c->queue, kQueueWords * sizeof(uint32_t)) != hipSuccess ||
         hipHostMalloc((void**)&c->load_host, 2 * sizeof(uint64_t), hipHostMallocMapped) != hipSuccess) {
         dgs_destroy(c);
         return DGS_ERR_OOM;
@@ -454,7 +456,7 @@ dgs_status dgs_destroy(dgs_ctx c) {
                     c->keys0, c->keys1, c->vals0, c->vals1, c->ranges, c->tile_order, c->scan_status, c->sort_status, c->g2d, c->gv, c->dec,
                     c->loss_coef, c->loss_part,
                     c->pk0, c->pk1, c->pv0, c->pv1, c->psort_status,
-                    c->hist, c->misc, c->dev_err, c->counters, c->frame};
+                    c->hist, c->misc, c->dev_err, c->counters, c->frame, c->queue};
     for (void* p : ptrs)
         if (p) hipFree(p);
     if (c->load_host) hipHostFree(c->load_host);
@@ -673,12 +675,12 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     GRec* recs = save ? save->recs : c->recs;
     uint32_t* ranges = save ? save->ranges : c->ranges;
     uint32_t* torder = save ? save->order : c->tile_order;
-    uint32_t* queue = save ? save->info : c->misc + 11;
+    uint32_t* queue = save ? save->info : c->queue;
 
     StageMarks sm(c);
     {
-        // per-frame zeroing: digit histograms, scan/sort tickets and the
-        // compositor queue (misc[1..12]), tile ranges, statistics counters
+        // per-frame zeroing: scan/sort tickets (misc[1..12]), statistics
+        // counters and, for the global order, digit histograms and tile ranges
         ClearList cl;
         cl.add(c->misc + 1, 12);
         if (!per_tile) {
@@ -740,7 +742,7 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
         sm.mark(6);
         // the same launch also builds the work queue
         launch_tile_depth_sort(q, ranges, tiles, c->keys0, svals, c->keys1, save ? save->vals : nullptr,
-                               cells ? kSplitLenCells : kSplitLenGauss, torder, queue,
+                               cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, torder, queue,
                                cells ? c->load_dev + 1 : nullptr, (uint32_t)P);
     } else {
         launch_prim_keys(q, P, c->p_ntiles, c->p_depth, c->pk0, c->pv0, c->hist);
@@ -784,7 +786,7 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     a.queue = queue;
     a.save = save != nullptr;
     if (!per_tile)
-        launch_tile_order(q, ranges, tiles, cells ? kSplitLenCells : kSplitLenGauss, torder, queue,
+        launch_tile_order(q, ranges, tiles, cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, torder, queue,
                           cells ? c->load_dev + 1 : nullptr, (uint32_t)P);
     if (overlap) hipStreamWaitEvent(q, c->ev_join, 0);  // the projected members
     sm.mark(8);
@@ -858,12 +860,15 @@ dgs_status dgs_render_backward(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
         float* D = f->pix + 3 * HW;
         float* T = f->pix + 4 * HW;
         int32_t* last = reinterpret_cast<int32_t*>(f->pix + 5 * HW);
-        launch_fill_u32(q, (uint32_t*)c->g2d, 0u, kG2dRow * (size_t)M);
-        launch_fill_u32(q, (uint32_t*)c->gv, 0u, (size_t)N);
-        // the forward's work queue (same ranges, same split) is in the
-        // frame with its item count: rewind its head only
-        launch_fill_u32(q, f->info, 0u, 1);
-        launch_set_frame(q, FrameK{f->k, f->o, color, D, T, last, nullptr, nullptr, nullptr, nullptr}, c->frame);
+        // one launch: zeroed gradient sums, the frame record, and the counters
+        // of the forward's work queue (same ranges, same split; it is in the
+        // frame with its item count) rewound
+        ClearList cl;
+        cl.add((uint32_t*)c->g2d, kG2dRow * (size_t)M);
+        cl.add((uint32_t*)c->gv, (size_t)N);
+        cl.add(f->info + kQueueStride, kQueueWords - kQueueStride);
+        const FrameK fk{f->k, f->o, color, D, T, last, nullptr, nullptr, nullptr, nullptr};
+        launch_clear(q, cl, &fk, c->frame);
         BwdArgs a;
         a.ranges = f->ranges;
         a.vals = f->vals;

@@ -14,6 +14,39 @@
 
 namespace dgs {
 
+// The pixels a wavefront walks: NS strips of 64, one pixel of each per lane --
+// a whole 16x16 tile (NS = 4) or one 16x8 half of it (NS = 2) in strips of
+// 16x4, strip j four rows below strip j - 1, or one 8x8 quarter (NS = 1).
+template <int NS>
+struct Block {
+    static constexpr int kCols = NS == 1 ? 8 : 16, kRows = 64 / kCols;
+    int x, y;  // its first pixel
+    __device__ __forceinline__ Block(int tx, int ty, int part)
+        : x(tx + (NS == 1 ? 8 * (part & 1) : 0)), y(ty + (NS == 1 ? 8 * (part >> 1) : NS == 2 ? 8 * part : 0)) {}
+    static __device__ __forceinline__ int column(int lane) { return lane & (kCols - 1); }
+    static __device__ __forceinline__ int row(int lane) { return lane / kCols; }
+};
+
+// The row a pixel's vertical offset is measured from.  A strip's offset is
+// that of the row 4 j above it plus 4 j, so that a member's rows need one
+// conversion; whether a pixel passes a member's gate depends on that rounding
+// in the last bit.  A quarter's pixel takes the same offset as in the walk its
+// tile would have without quarters -- in halves from split_len entries on,
+// else whole -- so that how a tile is cut changes no result.
+__device__ __forceinline__ int row_shift(int row, uint32_t len, uint32_t split_len) {
+    return len >= split_len ? row & 4 : row & 12;
+}
+
+// Block columns (bit x: column x) holding an active pixel in a strip, from
+// the ballot of the strip's active lanes.
+template <int NS>
+__device__ inline uint32_t active_columns(uint64_t m) {
+    uint32_t c = (uint32_t)(m | (m >> 32));
+    c |= c >> 16;
+    if constexpr (NS == 1) c |= c >> 8;
+    return c & ((1u << Block<NS>::kCols) - 1u);
+}
+
 // Inclusive prefix sum over the 64 lanes of a wavefront.
 __device__ inline int wave_incl_sum(int x, int lane) {
 #pragma unroll

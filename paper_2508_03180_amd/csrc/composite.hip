@@ -14,10 +14,10 @@
 // Alpha (eqs. alpha_blending, transmittance): the same walk over
 // depth-sorted Gaussians with C += T alpha c, T *= 1 - alpha, plus T bg.
 //
-// Mapping: a wavefront runs without workgroup barriers and owns either a
-// whole 16x16 tile or, for tiles with long lists, one 16x8 half of it
-// (strips 2h and 2h + 1, strip j = rows 4j..4j+3; lane l holds pixel
-// (l & 15, 4j + (l >> 4)) of every strip it owns).  Work items are taken
+// Mapping: a wavefront runs without workgroup barriers and owns a whole 16x16
+// tile or, for tiles with long lists, a 16x8 half or an 8x8 quarter of it (a
+// Block of 4, 2 or 1 strips of 64 pixels; lane l holds one pixel of every
+// strip it owns).  Work items are taken
 // from a queue that lists them heaviest first.  The tile list is consumed in
 // chunks of up to 64 Gaussian records (whole cells): each lane loads one
 // record, the wave ballots which strips every record's box touches, and the
@@ -26,9 +26,9 @@
 // one is composited.  Cells and members that touch none of the tile's
 // strips are skipped with scalar bit tests on the ballots.
 #include "cells.h"
-#include "order.h"
 #include "common.h"
 #include "launch.h"
+#include "order.h"
 
 namespace dgs {
 
@@ -79,41 +79,32 @@ __device__ inline void load_gauss_chunk(const CompositeArgs& a, uint32_t pos, ui
     q.r2 = p[2];
 }
 
-// Ballots of the owned strips each lane's record touches: B[j] for strip
-// s0 + j (rows 4(s0 + j)..4(s0 + j) + 3 of the tile), j < NS; s0 = 0 for a
-// whole tile (NS = 4), 2h for half h (NS = 2).  s0 is wavefront-uniform, so
-// the ballots stay in scalar registers.
-// Also returns, per lane, its record's strip bits (sm) and the tile columns
-// its box covers (cols, bit x for column tx0 + x; 0 when it misses the tile).
+// Ballots of the owned strips each lane's record touches: B[j] for strip j of
+// the block.  The block's origin is wavefront-uniform, so the ballots stay in
+// scalar registers.
+// Also returns, per lane, its record's strip bits (sm) and the block columns
+// its box covers (cols, bit x for column bx + x; 0 when it misses the block).
 template <int NS>
-__device__ inline void strip_ballots(const Chunk& q, int tx0, int ty0, int s0, uint64_t* B, uint32_t& sm,
-                                     uint32_t& cols) {
+__device__ inline void strip_ballots(const Chunk& q, int bx, int by, uint64_t* B, uint32_t& sm, uint32_t& cols) {
+    constexpr int W = Block<NS>::kCols, R = Block<NS>::kRows;
     sm = 0;
     cols = 0;
     if (q.ok) {
         const int x0 = __float_as_int(q.r2.y), y0 = __float_as_int(q.r2.z);
         const uint32_t wxy = __float_as_uint(q.r2.w);
         const int x1 = x0 + (int)(wxy & 0xffffu), y1 = y0 + (int)(wxy >> 16);
-        if (x0 <= tx0 + 15 && x1 >= tx0) {
-            const int lo = max(x0, tx0) - tx0, hi = min(x1, tx0 + 15) - tx0;
+        if (x0 <= bx + W - 1 && x1 >= bx) {
+            const int lo = max(x0, bx) - bx, hi = min(x1, bx + W - 1) - bx;
             cols = ((2u << (hi - lo)) - 1u) << lo;
 #pragma unroll
             for (int j = 0; j < NS; j++) {
-                const int r0 = ty0 + 4 * (s0 + j);
-                if (y0 <= r0 + 3 && y1 >= r0) sm |= 1u << j;
+                const int r0 = by + R * j;
+                if (y0 <= r0 + R - 1 && y1 >= r0) sm |= 1u << j;
             }
         }
     }
 #pragma unroll
     for (int j = 0; j < NS; j++) B[j] = __ballot((sm >> j) & 1u);
-}
-
-// Columns (bit x: tile column x) holding an active pixel in a strip, from
-// the ballot of the strip's active lanes (lane l: column l & 15).
-__device__ inline uint32_t active_columns(uint64_t m) {
-    m |= m >> 32;
-    m |= m >> 16;
-    return (uint32_t)m & 0xffffu;
 }
 
 __device__ inline void store_chunk(GRec* lds, int lane, const Chunk& q) {
@@ -199,7 +190,7 @@ __device__ inline FrameView frame_view(const FrameK* fr) {
 }
 
 // Work item: tile << 3 | mode; mode 0 = the whole tile (all four strips),
-// mode 2 + h = half h (strips 2h and 2h + 1).
+// mode 2 + h = half h, mode 4 + q = quarter q (a Block of 4, 2 or 1 strips).
 
 // Statistics counters (STATS only): n_val, n_rendered (the termination ratio
 // 1 - n_rendered / n_val), in-box member evaluations and (pixel, entry) pairs
@@ -208,8 +199,7 @@ struct Counters {
     uint32_t val = 0, rend = 0, box = 0, cellhit = 0, cellpx = 0;
 };
 
-// The hybrid renderer over one tile (NS = 4) or one half (NS = 2, strips s0
-// and s0 + 1)
+// The hybrid renderer over one tile (NS = 4), half (2) or quarter (1)
 // (Sec. V-A, eq. hybrid_renderer with w_n = v_n T_n and eq. dulpex_T; Sec. V-B
 // termination; Sec. VI-A box gate): cells front to back; a pixel whose
 // transmittance in front of a cell is below eps stops there; inside a cell
@@ -226,11 +216,14 @@ struct Counters {
 // is at least kMinReplayT together with that transmittance.
 // RAGGED: cells with their own member counts (CSR offsets), else K per cell.
 template <bool STATS, int NS, bool LC, bool SAVE, bool RAGGED>
-__device__ inline void duplex_tile(const CompositeArgs& a, const FrameView& f, int tile, int s0, int lane, GRec* lds,
+__device__ inline void duplex_tile(const CompositeArgs& a, const FrameView& f, int tile, int part, int lane, GRec* lds,
                                  Counters& cn) {
-    const int tx0 = (tile % f.TX) * kTile, ty0 = (tile / f.TX) * kTile;
-    const int px = tx0 + (lane & 15), py0 = ty0 + 4 * s0 + (lane >> 4);
+    const Block<NS> bl((tile % f.TX) * kTile, (tile / f.TX) * kTile, part);
+    const int px = bl.x + Block<NS>::column(lane), py0 = bl.y + Block<NS>::row(lane);
     const uint32_t start = a.ranges[2 * tile], end = a.ranges[2 * tile + 1];
+    // a quarter's rows: offsets from the row shift above (row_shift)
+    const int shift = NS == 1 ? row_shift(py0 & (kTile - 1), end - start, kSplitLenCells) : 0;
+    const float shiftf = (float)shift;
     const int K = a.K;
     const uint32_t kmask = member_mask(K);
     const float eps = f.eps, th = f.th, amax = f.amax;
@@ -280,7 +273,7 @@ __device__ inline void duplex_tile(const CompositeArgs& a, const FrameView& f, i
         store_chunk(lds, lane, q);
         uint64_t B[NS];
         uint32_t rsm, rcols;  // this lane's record: strips and tile columns its box touches
-        strip_ballots<NS>(q, tx0, ty0, s0, B, rsm, rcols);
+        strip_ballots<NS>(q, bl.x, bl.y, B, rsm, rcols);
         const float cv = q.v;
         const uint32_t next = pos + nch;
         if (next < end) load_cell_chunk<RAGGED>(a, next, end, lane, q);
@@ -334,7 +327,7 @@ __device__ inline void duplex_tile(const CompositeArgs& a, const FrameView& f, i
                             continue;
                         }
                         // B[j]: the records touching strip j
-                        const uint32_t ac = active_columns(am[j]);
+                        const uint32_t ac = active_columns<NS>(am[j]);
                         mj[j] = (uint32_t)((__ballot((rcols & ac) != 0u) & B[j]) >> base) & cm;
                         live |= mj[j];
                     }
@@ -363,14 +356,14 @@ __device__ inline void duplex_tile(const CompositeArgs& a, const FrameView& f, i
                 // test then rejects the pixel as the box test would
                 const float t0 = inx ? fmaf(e.ca * dx, dx, e.lo) : -INFINITY;
                 const float t1 = e.cb * dx;
-                const uint32_t ry0 = (uint32_t)(py0 - e.y0);
+                const uint32_t ry0 = (uint32_t)(py0 - shift - e.y0);
                 const float dy0 = (float)(int)ry0 + e.oy;
                 // every strip is evaluated (strips the member misses fail the
                 // row test in every lane): no scalar test per strip
 #pragma unroll
                 for (int j = 0; j < NS; j++) {
-                    const uint32_t ry = ry0 + 4u * j;
-                    const float dy = j ? dy0 + 4.0f * j : dy0;  // the row 4j below, without a conversion
+                    const uint32_t ry = NS == 1 ? ry0 + (uint32_t)shift : ry0 + 4u * j;
+                    const float dy = NS == 1 ? dy0 + shiftf : j ? dy0 + 4.0f * j : dy0;  // the row 4j below, without a conversion
                     const float pw = fmaf(dy, fmaf(e.cc, dy, t1), t0);
                     const bool iny = ry <= e.wy;
                     const bool hit = iny & (pw >= thj[j]);  // false once the pixel has terminated
@@ -443,11 +436,14 @@ __device__ inline void duplex_tile(const CompositeArgs& a, const FrameView& f, i
 }
 
 template <bool STATS, int NS>
-__device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, int tile, int s0, int lane, GRec* lds,
+__device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, int tile, int part, int lane, GRec* lds,
                                  Counters& cn) {
-    const int tx0 = (tile % f.TX) * kTile, ty0 = (tile / f.TX) * kTile;
-    const int px = tx0 + (lane & 15), py0 = ty0 + 4 * s0 + (lane >> 4);
+    const Block<NS> bl((tile % f.TX) * kTile, (tile / f.TX) * kTile, part);
+    const int px = bl.x + Block<NS>::column(lane), py0 = bl.y + Block<NS>::row(lane);
     const uint32_t start = a.ranges[2 * tile], end = a.ranges[2 * tile + 1];
+    // a quarter's rows: offsets from the row shift above (row_shift)
+    const int shift = NS == 1 ? row_shift(py0 & (kTile - 1), end - start, kSplitLenGauss) : 0;
+    const float shiftf = (float)shift;
     const float eps = f.eps, th = f.th, amax = f.amax;
 
     float T[NS], C0[NS], C1[NS], C2[NS];
@@ -470,7 +466,7 @@ __device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, in
         store_chunk(lds, lane, q);
         uint64_t B[NS], any = 0;
         uint32_t rsm, rcols;
-        strip_ballots<NS>(q, tx0, ty0, s0, B, rsm, rcols);
+        strip_ballots<NS>(q, bl.x, bl.y, B, rsm, rcols);
 #pragma unroll
         for (int j = 0; j < NS; j++) any |= B[j];
         const uint32_t next = pos + n;
@@ -492,7 +488,7 @@ __device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, in
                     // touching strip j
                     const uint64_t am = __ballot(!(T[j] < eps)) & inbm[j];
                     amall |= am;
-                    const uint32_t ac = active_columns(am);
+                    const uint32_t ac = active_columns<NS>(am);
                     live |= __ballot((rcols & ac) != 0u) & B[j];
                 }
                 if (!amall) {
@@ -509,15 +505,15 @@ __device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, in
             const float dx = (float)(int)rx + e.ox;
             const float t0 = inx ? fmaf(e.ca * dx, dx, e.lo) : -INFINITY;  // as in the Duplex walk
             const float t1 = e.cb * dx;
-            const uint32_t ry0 = (uint32_t)(py0 - e.y0);
+            const uint32_t ry0 = (uint32_t)(py0 - shift - e.y0);
             const float dy0 = (float)(int)ry0 + e.oy;
 #pragma unroll
             for (int j = 0; j < NS; j++) {
                 // termination before each Gaussian (T only changes on a hit
                 // and never rises, so no state is carried across Gaussians)
                 const bool act = inb[j] && !(T[j] < eps);
-                const uint32_t ry = ry0 + 4u * j;
-                const float dy = j ? dy0 + 4.0f * j : dy0;
+                const uint32_t ry = NS == 1 ? ry0 + (uint32_t)shift : ry0 + 4u * j;
+                const float dy = NS == 1 ? dy0 + shiftf : j ? dy0 + 4.0f * j : dy0;
                 const float pw = fmaf(dy, fmaf(e.cc, dy, t1), t0);
                 const bool iny = ry <= e.wy;
                 const bool hit = iny & (pw >= th);
@@ -558,8 +554,9 @@ __device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, in
 }
 
 // Persistent wavefronts: each takes the next work item of a queue that lists
-// them heaviest first, so long tiles start early and short ones fill in
-// behind them on every XCD.  Every wavefront leaves once the queue is empty.
+// them heaviest first (order.h), so long tiles start early and short ones
+// fill in behind them on every XCD.  Every wavefront leaves once the queue is
+// empty.
 // MODE: kModeDuplex, kModeAlpha or kModeLcwsr.
 template <int MODE, bool STATS, bool SAVE, bool RAGGED>
 __global__ __launch_bounds__(256) void k_composite(CompositeArgs a) {
@@ -568,33 +565,35 @@ __global__ __launch_bounds__(256) void k_composite(CompositeArgs a) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     GRec* lds = s_rec[wave];
     const uint32_t nitems = a.queue[1];
+    ItemSource src;
     Counters cn;
-    for (;;) {
-        uint32_t t = 0;
-        if (lane == 0) t = atomicAdd(a.queue, 1u);
-        // lane 0's ticket in a scalar register: the item, its tile and its
-        // half are then wavefront-uniform, and so is all loop control below
-        t = __builtin_amdgcn_readfirstlane(t);
-        if (t >= nitems) break;
+    // the item's number is in a scalar register: the item, its tile and its
+    // half are then wavefront-uniform, and so is all loop control below
+    for (uint32_t t = __builtin_amdgcn_readfirstlane(first_item<kWaves, 2>(wave, nitems, src)); t < nitems;
+         t = next_item(a.queue, src, lane)) {
         const uint32_t item = a.order[t];
         const int tile = (int)(item >> 3), mode = (int)(item & 7u);
-        // half-tile items (the tiles with the longest lists, which set the
-        // kernel's span) issue ahead of whole-tile items on their SIMD
-        if (mode != 0)
+        // the costliest items, which set the kernel's span, issue ahead of the
+        // others on their SIMD
+        if (src.heavy)
             __builtin_amdgcn_s_setprio(3);
         else
             __builtin_amdgcn_s_setprio(0);
         if (MODE == kModeAlpha) {
             if (mode == 0)
                 alpha_tile<STATS, 4>(a, f, tile, 0, lane, lds, cn);
+            else if (mode >= 4)
+                alpha_tile<STATS, 1>(a, f, tile, mode - 4, lane, lds, cn);
             else
-                alpha_tile<STATS, 2>(a, f, tile, 2 * (mode - 2), lane, lds, cn);
+                alpha_tile<STATS, 2>(a, f, tile, mode - 2, lane, lds, cn);
         } else {
             constexpr bool LC = MODE == kModeLcwsr;
             if (mode == 0)
                 duplex_tile<STATS, 4, LC, SAVE, RAGGED>(a, f, tile, 0, lane, lds, cn);
+            else if (mode >= 4)
+                duplex_tile<STATS, 1, LC, SAVE, RAGGED>(a, f, tile, mode - 4, lane, lds, cn);
             else
-                duplex_tile<STATS, 2, LC, SAVE, RAGGED>(a, f, tile, 2 * (mode - 2), lane, lds, cn);
+                duplex_tile<STATS, 2, LC, SAVE, RAGGED>(a, f, tile, mode - 2, lane, lds, cn);
         }
     }
     if (STATS) {
@@ -608,12 +607,12 @@ __global__ __launch_bounds__(256) void k_composite(CompositeArgs a) {
 
 // Builds the work queue (build_work_queue, order.h) in one workgroup.
 __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t* __restrict__ ranges, int ntiles,
-                                                     uint32_t split_len, uint32_t* __restrict__ order,
-                                                     uint32_t* __restrict__ queue, uint64_t* long_stat,
-                                                     uint32_t prims) {
+                                                     uint32_t split_len, const uint32_t* __restrict__ total,
+                                                     uint32_t* __restrict__ order, uint32_t* __restrict__ queue,
+                                                     uint64_t* long_stat, uint32_t prims) {
     __shared__ uint32_t s_cnt[kOrderClasses];
     __shared__ uint32_t s_part[1024];
-    build_work_queue<1024>(ranges, ntiles, split_len, order, queue, s_cnt, s_part, (int)threadIdx.x, long_stat, prims);
+    build_work_queue<1024>(ranges, ntiles, split_rule(split_len, *total), order, queue, s_cnt, s_part, (int)threadIdx.x, long_stat, prims);
 }
 
 static unsigned persistent_grid(int tiles) {
@@ -622,11 +621,11 @@ static unsigned persistent_grid(int tiles) {
     return (unsigned)((waves + kWaves - 1) / kWaves);
 }
 
-void launch_tile_order(hipStream_t st, const uint32_t* ranges, int tiles, uint32_t split_len, uint32_t* order,
-                       uint32_t* queue, uint64_t* long_stat, uint32_t prims) {
+void launch_tile_order(hipStream_t st, const uint32_t* ranges, int tiles, uint32_t split_len, const uint32_t* total,
+                       uint32_t* order, uint32_t* queue, uint64_t* long_stat, uint32_t prims) {
     if (tiles <= 0) return;
-    hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, st, ranges, tiles, split_len, order, queue, long_stat,
-                       prims);
+    hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, st, ranges, tiles, split_len, total, order, queue,
+                       long_stat, prims);
 }
 
 template <int MODE, bool SAVE, bool RAGGED>

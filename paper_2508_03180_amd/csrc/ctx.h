@@ -42,8 +42,9 @@ struct dgs_frame_s {
     int64_t cap_tiles = 0;
     float* pix = nullptr;       // [6][H*W]: colour (3 planes), D, replay T, replay start (int32)
     int64_t cap_pix = 0;
-    uint32_t* info = nullptr;   // [16]: [0] work-queue head, [1] item count, [2] key total,
-                                // [4..13] n_val, n_rendered, n_box, n_cell_hits, n_cell_pixels (u64)
+    uint32_t* info = nullptr;   // [kQueueWords] work queue (order.h: [1] item count, counters from
+                                // [kQueueStride] on), and in its first line [2] key total, [4..13]
+                                // n_val, n_rendered, n_box, n_cell_hits, n_cell_pixels (u64)
 };
 
 struct dgs_ctx_s {
@@ -96,8 +97,9 @@ struct dgs_ctx_s {
     uint32_t* hist = nullptr;     // [8][256]: [0..3] primitive depth bytes, [4..6] key tile bytes
     uint32_t* misc = nullptr;     // [0] key total, [1] scan ticket, [2..5] depth sort tickets,
                                   // [6..8] tile sort tickets, [9] spare, [10] sort count,
-                                  // [11..12] compositor work-queue head and item count,
+                                  // [11..12] spare,
                                   // [13] look-back frame counter
+    uint32_t* queue = nullptr;    // [kQueueWords] the compositor's work queue (a saved frame has its own)
     int* dev_err = nullptr;
     unsigned long long* counters = nullptr;  // n_val, n_rendered, n_box, n_cell_hits, n_cell_pixels
 

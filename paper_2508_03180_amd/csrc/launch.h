@@ -4,9 +4,6 @@
 
 namespace dgs {
 
-// Writes the frame's camera and options to device memory (graph-safe kernel).
-void launch_set_frame(hipStream_t st, const FrameK& f, FrameK* dst);
-
 // Neural decode of the cells' Gaussians into planar attribute arrays
 // (means [3][M], scales [3][M], raw quaternions [4][M], opacity [M], colour
 // [3][M]); cells with cell_ntiles[n] == 0 are skipped (cell_ntiles may be
@@ -48,7 +45,7 @@ void launch_exclusive_scan(hipStream_t st, const uint32_t* in, uint32_t* out, in
 
 void launch_fill_u32(hipStream_t st, uint32_t* p, uint32_t v, size_t n);
 
-// Zeroes up to 8 small u32 buffers in one launch (graph-safe: no memset
+// Zeroes up to 8 u32 buffers in one launch (graph-safe: no memset
 // nodes) and increments *bump (the look-back frame counter) when set.
 struct ClearList {
     uint32_t* p[8];
@@ -112,7 +109,8 @@ void launch_bin_tiles(hipStream_t st, const BinArgs& a);
 // spare (a buffer of its size) are scratch.  The same launch builds the
 // compositor's work queue (as launch_tile_order; long_stat, prims too).
 void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, uint64_t* ent, uint32_t* vals,
-                            uint64_t* spare, uint32_t* vcopy, uint32_t split_len, uint32_t* order, uint32_t* queue,
+                            uint64_t* spare, uint32_t* vcopy, uint32_t split_len, const uint32_t* total,
+                            uint32_t* order, uint32_t* queue,
                             uint64_t* long_stat = nullptr, uint32_t prims = 0);
 // Keys tile << 32 | depth bits of ordered lists (vals by ranges).
 void launch_list_keys(hipStream_t st, const uint32_t* ranges, int tiles, const uint32_t* vals, const uint32_t* depth,
@@ -165,16 +163,17 @@ struct CompositeArgs {
     int32_t* last;
     unsigned long long* counters;  // [4]: n_val, n_rendered, n_box, n_cell_hits (stats mode), nullable
     uint32_t* order;               // [4 * tiles] scratch: heaviest-first work items
-    uint32_t* queue;               // [2] scratch: work-queue head, item count
+    uint32_t* queue;               // [kQueueWords] scratch: item count and counters (order.h)
     bool save;                     // Duplex: also write the frame record's sv_* state (host-side choice)
 };
 // Work queue of the compositor (costliest-first tile / half-tile items);
 // must precede launch_composite_*.  Tiles with at least split_len entries
-// become two half-tile items.
+// become two half-tile items, the longest of them four quarters; *total: the
+// frame's list entries (order.h).
 // long_stat (nullable, pinned host memory): receives prims << 32 | the
 // number of keys in runs of more than 4096 entries.
-void launch_tile_order(hipStream_t st, const uint32_t* ranges, int tiles, uint32_t split_len, uint32_t* order,
-                       uint32_t* queue, uint64_t* long_stat = nullptr, uint32_t prims = 0);
+void launch_tile_order(hipStream_t st, const uint32_t* ranges, int tiles, uint32_t split_len, const uint32_t* total,
+                       uint32_t* order, uint32_t* queue, uint64_t* long_stat = nullptr, uint32_t prims = 0);
 // Split lengths, measured: lists of cells (each entry K members) and lists
 // of Gaussians.
 constexpr uint32_t kSplitLenCells = 32;

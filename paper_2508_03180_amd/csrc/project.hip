@@ -311,12 +311,4 @@ void launch_gauss_project(hipStream_t st, int M, int K, const float* means, cons
                        sh, sh_deg, fr, cell_ntiles, recs, grect, gdepth, gntiles);
 }
 
-__global__ void k_set_frame(FrameK f, FrameK* dst) {
-    if (threadIdx.x == 0) *dst = f;
-}
-
-void launch_set_frame(hipStream_t st, const FrameK& f, FrameK* dst) {
-    hipLaunchKernelGGL(k_set_frame, dim3(1), dim3(64), 0, st, f, dst);
-}
-
 }  // namespace dgs

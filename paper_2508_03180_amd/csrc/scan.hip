@@ -173,8 +173,16 @@ void launch_exclusive_scan(hipStream_t st, const uint32_t* in, uint32_t* out, in
 
 __global__ void k_clear(ClearList l, FrameK f, FrameK* fdst) {
     const size_t gid = blockIdx.x * (size_t)blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
-    for (int b = 0; b < l.count; b++)
-        for (size_t i = gid; i < l.n[b]; i += stride) l.p[b][i] = 0u;
+    for (int b = 0; b < l.count; b++) {
+        size_t i0 = 0;
+        if (((uintptr_t)l.p[b] & 15) == 0) {  // 16 bytes per store
+            uint4* p4 = reinterpret_cast<uint4*>(l.p[b]);
+            const size_t n4 = l.n[b] / 4;
+            for (size_t i = gid; i < n4; i += stride) p4[i] = make_uint4(0u, 0u, 0u, 0u);
+            i0 = 4 * n4;
+        }
+        for (size_t i = i0 + gid; i < l.n[b]; i += stride) l.p[b][i] = 0u;
+    }
     if (l.bump && gid == 0) *l.bump += 1u;
     if (fdst) {
         static_assert(sizeof(FrameK) % 4 == 0, "frame record in words");
@@ -188,8 +196,8 @@ void launch_clear(hipStream_t st, const ClearList& l, const FrameK* f, FrameK* f
     size_t most = 0;
     for (int b = 0; b < l.count; b++) most = l.n[b] > most ? l.n[b] : most;
     if (most == 0) most = 1;
-    unsigned grid = (unsigned)((most + 255) / 256);
-    if (grid > 256) grid = 256;
+    const size_t blocks = (most + 1023) / 1024;
+    const unsigned grid = (unsigned)(blocks > 2048 ? 2048 : blocks);
     FrameK fv;
     if (f) fv = *f;
     else memset(&fv, 0, sizeof(fv));

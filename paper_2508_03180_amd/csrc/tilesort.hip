@@ -261,15 +261,15 @@ constexpr int kTsSharedBytes = kQueueBytes > kTsChunk * 8 ? kQueueBytes : kTsChu
 // only), the others sort the runs.
 __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_tile_sort(
     const uint32_t* __restrict__ ranges, int tiles, uint64_t* __restrict__ ent, uint32_t* __restrict__ vals,
-    uint64_t* __restrict__ spare, uint32_t* __restrict__ vcopy, uint32_t split_len, uint32_t* __restrict__ order,
+    uint64_t* __restrict__ spare, uint32_t* __restrict__ vcopy, uint32_t split_len, const uint32_t* __restrict__ total, uint32_t* __restrict__ order,
     uint32_t* __restrict__ queue, uint64_t* long_stat, uint32_t prims) {
     __shared__ __align__(16) unsigned char smem[kTsSharedBytes];
     __shared__ int lt_s[kTsWaves], lt_len[kTsWaves];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     if (blockIdx.x == 0) {
         uint32_t* s_cnt = reinterpret_cast<uint32_t*>(smem);
-        build_work_queue<kTsThreads>(ranges, tiles, split_len, order, queue, s_cnt, s_cnt + kOrderClasses, tid, long_stat,
-                                     prims);
+        build_work_queue<kTsThreads>(ranges, tiles, split_rule(split_len, *total), order, queue, s_cnt,
+                                     s_cnt + kOrderClasses, tid, long_stat, prims);
         return;
     }
     const int G = (int)gridDim.x - 1, sb = (int)blockIdx.x - 1;
@@ -309,12 +309,13 @@ __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8)))
 }
 
 void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, uint64_t* ent, uint32_t* vals,
-                            uint64_t* spare, uint32_t* vcopy, uint32_t split_len, uint32_t* order, uint32_t* queue,
+                            uint64_t* spare, uint32_t* vcopy, uint32_t split_len, const uint32_t* total,
+                            uint32_t* order, uint32_t* queue,
                             uint64_t* long_stat, uint32_t prims) {
     if (tiles <= 0) return;
     const unsigned grid = (unsigned)((tiles + kTsWaves - 1) / kTsWaves) + 1;  // + the work queue's
     hipLaunchKernelGGL(k_tile_sort, dim3(grid), dim3(kTsThreads), 0, st, ranges, tiles, ent, vals, spare, vcopy,
-                       split_len, order, queue, long_stat, prims);
+                       split_len, total, order, queue, long_stat, prims);
 }
 
 __global__ __launch_bounds__(256) void k_list_keys(const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,

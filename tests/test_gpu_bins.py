@@ -86,3 +86,35 @@ def test_chunk_remainders(r):
 def test_grid_too_large_for_the_counters(r):
     s, cam = front_scene(500, 16400, 2500, 1.0, 60.0, 4)
     check(r, s, cam)
+
+
+@pytest.mark.parametrize("mode", ["duplex", "alpha"])
+@pytest.mark.parametrize("n", [9, 31, 32, 33, 50, 64])
+def test_quarters_change_no_result(mode, n):
+    """A tile that is walked in quarters (it holds more than the frame's
+    entries per SIMD) gives the pixels it gives in halves or whole (the same
+    tile beside others that hold enough)."""
+    from paper_2508_03180_amd.renderer import DeviceScene, Renderer
+    s, cam = front_scene(n, 16, 16, 0.6, 2.0, n)
+    extra = 170000
+    rng = np.random.default_rng(n)
+    wide = dict(s)
+    z = rng.uniform(2.0, 4.0, extra)
+    px, py = rng.uniform(60, 1000, extra), rng.uniform(-8, 8, extra)
+    pos = np.stack([(px - 8) * z / 100.0, py * z / 100.0, z], 1).astype(np.float32)
+    t = scenes.make_tiny_scene(9, n_cells=extra, K=2)
+    t["cell_pos"], t["means"] = pos, np.repeat(pos, 2, 0)
+    t["cell_scale"] = np.full((extra, 3), 0.005, np.float32)
+    t["scales"] = np.full((2 * extra, 3), 0.01, np.float32)
+    for k in ("cell_pos", "cell_scale", "cell_rot", "cell_v_sh", "means", "scales", "rots", "opacities", "sh"):
+        wide[k] = np.concatenate([s[k], t[k]])
+    wcam = dict(cam, width=1024)
+    r = Renderer(0)
+    try:
+        a = r.render(DeviceScene.from_numpy(s, "cuda:0"), cam, mode=mode)
+        b = r.render(DeviceScene.from_numpy(wide, "cuda:0"), wcam, mode=mode)
+        assert r.stats()["num_keys"] > 1024 * 2 * n  # no quarters for a list of up to 2 n entries
+        for k in ("color", "D", "T", "last"):
+            assert torch.equal(a[k], b[k][..., :16]), k
+    finally:
+        r.close()
