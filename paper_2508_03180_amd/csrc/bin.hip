@@ -40,6 +40,7 @@ constexpr int kBinMaxLocal = 16384;  // tiles of a band: 64 KB of LDS counters
 // A lane walks the tiles of its own primitive up to this many; the tiles of
 // a larger one are dealt over the wavefront's lanes.
 constexpr int kBinOwnTiles = 16;
+constexpr int kBinAhead = 4;  // rounds of a chunk loaded at once: 62 -> 49 us for the count of 600k cells at 4K
 constexpr int kBinScanTiles = 64;                                // tiles per workgroup of the scan
 constexpr int kBinScanSplit = 4;                                 // threads per tile
 constexpr int kBinScanEach = kBinMaxChunks / kBinScanSplit;      // chunks per thread
@@ -95,19 +96,36 @@ __device__ __forceinline__ void band_tiles(bool has, uint64_t r, uint32_t depth,
     }
 }
 
-// A culled primitive's rectangle is kEmptyRect.
+// band_tiles over the primitives [p0, p1) of a chunk by the workgroup; the
+// rectangles and depths of kBinAhead rounds are loaded at once.  A culled
+// primitive's rectangle is kEmptyRect.
+template <bool DEPTH, class F>
+__device__ __forceinline__ void chunk_tiles(const uint64_t* __restrict__ prect, const uint32_t* __restrict__ depth, int p0,
+                                            int p1, int band, int TX, int tid, F f) {
+    for (int q = p0 + tid; q - tid < p1; q += kBinAhead * kBinThreads) {
+        uint64_t r[kBinAhead];
+        uint32_t d[kBinAhead];
+#pragma unroll
+        for (int i = 0; i < kBinAhead; i++) {
+            const int p = q + i * kBinThreads;
+            r[i] = p < p1 ? prect[p] : kEmptyRect;
+            d[i] = DEPTH && p < p1 ? depth[p] : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < kBinAhead; i++)
+            band_tiles(r[i] != kEmptyRect, r[i], d[i], (uint32_t)(q + i * kBinThreads), band, TX, tid & 63, f);
+    }
+}
+
 __global__ __launch_bounds__(kBinThreads) void k_bin_count(const uint64_t* __restrict__ prect, int P, int per, int TX,
                                                            int local, uint32_t* __restrict__ counts) {
     extern __shared__ uint32_t s_cnt[];
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int band = blockIdx.x & (kBinBands - 1), chunk = blockIdx.x / kBinBands;
     for (int i = tid; i < local; i += kBinThreads) s_cnt[i] = 0u;
     __syncthreads();
-    const int p0 = chunk * per, p1 = min(P, p0 + per);
-    for (int p = p0 + tid; p - tid < p1; p += kBinThreads) {
-        const uint64_t r = p < p1 ? prect[p] : kEmptyRect;
-        band_tiles(r != kEmptyRect, r, 0u, 0u, band, TX, lane, [&](int s, uint32_t, uint32_t) { atomicAdd(&s_cnt[s], 1u); });
-    }
+    chunk_tiles<false>(prect, nullptr, chunk * per, min(P, (chunk + 1) * per), band, TX, tid,
+                       [&](int s, uint32_t, uint32_t) { atomicAdd(&s_cnt[s], 1u); });
     __syncthreads();
     uint32_t* out = counts + (size_t)blockIdx.x * local;
     for (int i = tid; i < local; i += kBinThreads) out[i] = s_cnt[i];
@@ -118,20 +136,16 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_scatter(const uint64_t* __r
                                                              int local, const uint32_t* __restrict__ offsets, uint32_t cap,
                                                              uint64_t* __restrict__ ent) {
     extern __shared__ uint32_t s_cnt[];
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int band = blockIdx.x & (kBinBands - 1), chunk = blockIdx.x / kBinBands;
     const uint32_t* in = offsets + (size_t)blockIdx.x * local;
     for (int i = tid; i < local; i += kBinThreads) s_cnt[i] = in[i];
     __syncthreads();
-    const int p0 = chunk * per, p1 = min(P, p0 + per);
-    for (int p = p0 + tid; p - tid < p1; p += kBinThreads) {
-        const uint64_t r = p < p1 ? prect[p] : kEmptyRect;
-        const uint32_t d = p < p1 ? depth[p] : 0u;
-        band_tiles(r != kEmptyRect, r, d, (uint32_t)p, band, TX, lane, [&](int s, uint32_t dd, uint32_t id) {
-            const uint32_t pos = atomicAdd(&s_cnt[s], 1u);
-            if (pos < cap) ent[pos] = ((uint64_t)dd << 32) | id;
-        });
-    }
+    chunk_tiles<true>(prect, depth, chunk * per, min(P, (chunk + 1) * per), band, TX, tid,
+                      [&](int s, uint32_t d, uint32_t id) {
+                          const uint32_t pos = atomicAdd(&s_cnt[s], 1u);
+                          if (pos < cap) ent[pos] = ((uint64_t)d << 32) | id;
+                      });
 }
 
 // Sums saturate at 2^32 - 1, far above the largest key capacity: an overflow

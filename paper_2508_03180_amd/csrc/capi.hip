@@ -586,17 +586,20 @@ dgs_status dgs_read_decoded(dgs_ctx c, float* means, float* scales, float* rots,
 }  // extern "C"
 
 // Per-cell tile lists (Duplex, LC-WSR) are put in depth order per tile
-// (launch_tile_depth_sort) when the context's last cell frame had at most 8
-// keys per cell, at most 1024 keys per tile on
-// average, and at most a twentieth of its keys in runs of more than 4096
-// entries (which the per-tile sort handles by chunked merges in global
-// memory over several rounds); before any cell frame, when the key buffer
-// holds at most 256 keys per tile.  The per-tile sort's cost grows with the keys and their
-// run lengths, the depth sort's with the cells only.  Per-Gaussian lists
-// always take the depth sort of the primitives.
-constexpr uint64_t kPerTileOrderKeysPerCell = 8;
+// (launch_bin_tiles, launch_tile_depth_sort) when the context's last cell
+// frame had at most 1024 keys per tile on average, and at most an eighth of
+// its keys in runs of more than 4096 entries (which the per-tile sort handles
+// by chunked merges in global memory over several rounds); before any cell
+// frame, when the key buffer holds at most 256 keys per tile.  Measured, us
+// per frame per tile / global: street views of the 6M-Gaussian scene at 4K
+// (23 to 40 keys per cell, none in long runs) 996 / 1990 and 1463 / 2420, at
+// 1080p 695 / 962, at 720p (5 to 9% of the keys in long runs) 580 / 683 and
+// 435 / 545; the clustered scene's 1M Gaussians as cells of 10, 5, 2 and 1 (0,
+// 0, 4 and 16%) 321 / 404, 404 / 474, 656 / 681 and 1129 / 931; 20,000 ragged
+// cells at 1283 x 717 (13 keys per cell) 230 / 323.  Per-Gaussian lists always
+// take the depth sort of the primitives (1M Gaussians at 1080p, 8%: 605 / 576).
 constexpr int64_t kPerTileOrderMaxMean = 1024;      // keys per tile
-constexpr uint64_t kPerTileOrderLongShare = 20;     // at most 1 / this of the keys in long runs
+constexpr uint64_t kPerTileOrderLongShare = 8;      // at most 1 / this of the keys in long runs
 constexpr int64_t kPerTileOrderCapacity = 256;      // keys per tile, before any cell frame
 
 static bool per_tile_order(dgs_ctx c, int64_t tiles, bool cells) {
@@ -605,10 +608,8 @@ static bool per_tile_order(dgs_ctx c, int64_t tiles, bool cells) {
     if (!cells) return false;
     const uint64_t load = __atomic_load_n(c->load_host, __ATOMIC_RELAXED);
     const uint64_t lng = __atomic_load_n(c->load_host + 1, __ATOMIC_RELAXED);
-    const uint64_t lt = load >> 32, lk = load & 0xffffffffull, lp = lng >> 32, ll = lng & 0xffffffffull;
-    if (lt)
-        return lk <= kPerTileOrderKeysPerCell * lp && lk <= (uint64_t)kPerTileOrderMaxMean * lt &&
-               kPerTileOrderLongShare * ll <= lk;
+    const uint64_t lt = load >> 32, lk = load & 0xffffffffull, ll = lng & 0xffffffffull;
+    if (lt) return lk <= (uint64_t)kPerTileOrderMaxMean * lt && kPerTileOrderLongShare * ll <= lk;
     return c->cap_keys <= kPerTileOrderCapacity * tiles;
 }
 

@@ -21,6 +21,7 @@ constexpr int kScanPart = kScanThreads * kScanItems;
 constexpr int kHistBlocks = 512;
 constexpr int kPrimKeysPerBlock = 1024;
 constexpr int kEmitPrimsPerBlock = 256;
+constexpr int kOwnTiles = 32;
 
 static int hist_grid(int n, int per_block) {
     const int b = (n + per_block - 1) / per_block;
@@ -256,55 +257,81 @@ __global__ __launch_bounds__(256) void k_emit_keys(int P, const uint32_t* __rest
     for (int i = threadIdx.x; i < 257; i += blockDim.x) s_diff[i] = 0;
     if (threadIdx.x == 0) s_all = 0u;
     __syncthreads();
+    // counts one row of a primitive's tiles: `kept` consecutive tile ids from t0
+    const auto count_row = [&](uint32_t t0, uint32_t kept) {
+        if (kept) {
+            if (kept >= 256u) atomicAdd(&s_all, kept >> 8);
+            const uint32_t rem = kept & 255u, a = t0 & 255u;
+            if (rem) {
+                atomicAdd(&s_diff[a], 1);
+                if (a + rem <= 256u) {
+                    atomicAdd(&s_diff[a + rem], -1);
+                } else {
+                    atomicAdd(&s_diff[256], -1);
+                    atomicAdd(&s_diff[0], 1);
+                    atomicAdd(&s_diff[a + rem - 256u], -1);
+                }
+            }
+        }
+        // higher tile bytes change rarely along a row: one count per run
+        for (int b = 1; b < passes; b++) {
+            const int sh8 = 8 * b;
+            for (uint32_t t = t0, te = t0 + kept; t < te;) {
+                const uint32_t run_end = ((t >> sh8) + 1u) << sh8;
+                const uint32_t stop = run_end < te ? run_end : te;
+                atomicAdd(&sh[b - 1][(t >> sh8) & 255u], stop - t);
+                t = stop;
+            }
+        }
+    };
     // grid-stride over the depth order: a capped grid, so each workgroup adds
-    // its histogram to the global one once
-    for (int i0 = blockIdx.x * blockDim.x + threadIdx.x; i0 < P; i0 += gridDim.x * blockDim.x) {
-        const uint32_t p = order ? order[i0] : (uint32_t)i0;  // null order: id order
-        if (p >= (uint32_t)P) continue;  // a permutation of [0, P) unless a sort wait timed out
-        const uint32_t nt = ntiles[p];
+    // its histogram to the global one once.  A lane writes the keys of its own
+    // primitive up to kOwnTiles; those of a larger one are dealt over the
+    // wavefront (one lane writing the up to 32,400 keys of a screen-filling
+    // cell held a 4K frame for 2.7 ms)
+    const int lane = threadIdx.x & 63;
+    for (int i0 = blockIdx.x * blockDim.x + threadIdx.x; i0 - lane < P; i0 += gridDim.x * blockDim.x) {
+        uint32_t p = (uint32_t)P;
+        if (i0 < P) p = order ? order[i0] : (uint32_t)i0;  // null order: id order
+        // a permutation of [0, P) unless a sort wait timed out
+        uint32_t nt = 0, off = 0, d = 0, t00 = 0, w = 0;
+        if (p < (uint32_t)P) nt = ntiles[p];
         if (nt) {
-            const uint32_t off = offsets[i0];
+            off = offsets[i0];
             if ((uint64_t)off + nt > cap) atomicOr(err, 1 << kErrCapacity);
             const uint64_t r = prect[p];
-            const uint32_t d = depth[p];
-            const int tx0 = rect_x0(r) / kTile, tx1 = rect_x1(r) / kTile;
-            const int ty0 = rect_y0(r) / kTile, ty1 = rect_y1(r) / kTile;
-            uint32_t i = off;
-            for (int ty = ty0; ty <= ty1 && i < cap; ty++) {
+            d = depth[p];
+            const int tx0 = rect_x0(r) / kTile, ty0 = rect_y0(r) / kTile;
+            w = (uint32_t)(rect_x1(r) / kTile - tx0 + 1);
+            t00 = (uint32_t)(ty0 * TX + tx0);
+        }
+        if (nt <= (uint32_t)kOwnTiles)
+            for (uint32_t i = off, t0 = t00, done = 0; done < nt && i < cap; done += w, t0 += (uint32_t)TX) {
                 // one row of tiles: consecutive tile ids t0 .. t0 + kept - 1
-                const uint32_t t0 = (uint32_t)(ty * TX + tx0);
-                const uint32_t len = (uint32_t)(tx1 - tx0 + 1);
-                const uint32_t kept = cap - i < len ? cap - i : len;
+                const uint32_t kept = cap - i < w ? cap - i : w;
                 for (uint32_t j = 0; j < kept; j++) {
                     keys[i + j] = ((uint64_t)(t0 + j) << 32) | d;
                     vals[i + j] = p;
                 }
-                if (kept) {
-                    if (kept >= 256u) atomicAdd(&s_all, kept >> 8);
-                    const uint32_t rem = kept & 255u, a = t0 & 255u;
-                    if (rem) {
-                        atomicAdd(&s_diff[a], 1);
-                        if (a + rem <= 256u) {
-                            atomicAdd(&s_diff[a + rem], -1);
-                        } else {
-                            atomicAdd(&s_diff[256], -1);
-                            atomicAdd(&s_diff[0], 1);
-                            atomicAdd(&s_diff[a + rem - 256u], -1);
-                        }
-                    }
-                }
-                // higher tile bytes change rarely along a row: one count per run
-                for (int b = 1; b < passes; b++) {
-                    const int sh8 = 8 * b;
-                    for (uint32_t t = t0, te = t0 + kept; t < te;) {
-                        const uint32_t run_end = ((t >> sh8) + 1u) << sh8;
-                        const uint32_t stop = run_end < te ? run_end : te;
-                        atomicAdd(&sh[b - 1][(t >> sh8) & 255u], stop - t);
-                        t = stop;
-                    }
-                }
+                count_row(t0, kept);
                 i += kept;
             }
+        for (uint64_t m = __ballot(nt > (uint32_t)kOwnTiles); m; m &= m - 1) {
+            const int l = __builtin_ctzll(m);
+            const uint32_t bn = (uint32_t)__builtin_amdgcn_readlane((int)nt, l), bw = (uint32_t)__builtin_amdgcn_readlane((int)w, l);
+            const uint32_t bo = (uint32_t)__builtin_amdgcn_readlane((int)off, l), bt = (uint32_t)__builtin_amdgcn_readlane((int)t00, l);
+            const uint32_t bd = (uint32_t)__builtin_amdgcn_readlane((int)d, l), bp = (uint32_t)__builtin_amdgcn_readlane((int)p, l);
+            const uint32_t keep = bo < cap ? min(bn, cap - bo) : 0u;  // keys below the capacity
+            // k / bw through a double: exact for k < 2^32 / bw with (k + 0.5) / bw
+            // at least 0.5 / bw off any integer
+            const double inv = 1.0 / (double)bw;
+            for (uint32_t k = lane; k < keep; k += 64) {
+                const uint32_t row = (uint32_t)(((double)k + 0.5) * inv);
+                keys[bo + k] = ((uint64_t)(bt + row * (uint32_t)TX + (k - row * bw)) << 32) | bd;
+                vals[bo + k] = bp;
+            }
+            for (uint32_t row = lane; row * bw < keep; row += 64)
+                count_row(bt + row * (uint32_t)TX, min(bw, keep - row * bw));
         }
     }
     __syncthreads();
