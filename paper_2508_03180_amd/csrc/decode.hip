@@ -6,15 +6,24 @@
 // cell frame, mu = x_n + R(Q_n)(O^pos * S_n), and scales eqs. nerual_scales
 // and scale_res, s = max(0, min(sigmoid(y_s), 1 - |O^pos|)) * S_n.
 //
-// Mapping: one decoder per workgroup (blockIdx.y), one cell per thread, so
-// all lanes read the same weight at the same time and it comes through a
-// scalar load; each thread writes its decoder's attribute of the cell's
-// Gaussians straight to the planar outputs.  The opacity decoder, whose
-// second layer is the smallest, also places the centres.  F = H = 32 (the
-// neural-Gaussian default) has an exact-size kernel whose first layer runs
-// input-major over contiguous weight rows; other sizes use register
-// capacities of 36 x 32 or 68 x 64 with predicated loops (the largest
-// spills to scratch).
+// Mapping: one decoder per workgroup (blockIdx.y), one cell per thread.  The
+// workgroup copies its decoder's weights to LDS (at most 51 KB) and every lane
+// reads them from there as broadcasts, four to a ds_read_b128, which four
+// multiply-adds then use: the second layer's are stored output-major,
+// so that both layers read four consecutive ones.  (Read through the scalar
+// cache, the four decoders' weights missed its 16 KB and every wavefront
+// waited on the L2.)  The second layer's outputs pass through LDS from one
+// cell per lane to one Gaussian per lane: the attributes and offsets of
+// consecutive Gaussians are consecutive, and a lane per cell touched a line of
+// its own with every 4-byte store, K times over.
+// Bound by latency (the copies of weights and features, the exchanges through
+// LDS) and by the LDS reads, twice the multiply-adds' issue time: 67 us for the
+// 83,000 visible cells of the 1920 x 1080 orbit at F = H = 32, K = 10 (121
+// through the scalar cache and a lane per cell throughout), 38 us for 20,000
+// cells at F = 48, H = 64, K = 4 (290, its registers spilled).  Two cells per
+// thread halve the LDS reads but leave too few wavefronts: 96 and 50 us.
+// CH, the hidden units held in registers, is 32 or 64.  The opacity decoder,
+// whose second layer is the smallest, also places the centres.
 //
 // The scales, quaternions and centres decide each Gaussian's pixel box, so
 // they are computed in binary32 in one fixed order: every sum is a chain of
@@ -25,6 +34,17 @@
 #include "launch.h"
 
 namespace dgs {
+
+constexpr int kDecodeWaves = 4, kDecodeThreads = 64 * kDecodeWaves;
+constexpr int kDecodeSlots = 20;          // outputs per cell of the LDS buffer, at most
+constexpr size_t kDecodeLds = 64 * 1024;  // LDS of a workgroup, at most
+
+// Orders a wavefront's own LDS accesses: its lanes exchange values through it.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // exp(x) in binary32: Cody-Waite reduction x = n ln2 + r with ln2 split so
 // that n * ln2_hi is exact, the degree-7 Taylor polynomial of e^r in Horner
@@ -65,235 +85,196 @@ __device__ inline void cell_rot32(float w, float x, float y, float z, float* R) 
     R[6] = 2.0f * (xz - wy);        R[7] = 2.0f * (yz + wx);        R[8] = 1.0f - 2.0f * (xx + yy);
 }
 
-// CI, CH: register capacities of the input vector and the hidden layer (the
-// loops run over them, predicated by the actual sizes, so the arrays stay in
-// registers and every sum keeps its order).
-template <int CI, int CH>
-__global__ __launch_bounds__(256) void k_decode(DecodeArgs a) {
-#pragma clang fp contract(off)
-    const int wave = blockIdx.y;  // the decoder
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    const int N = a.N, K = a.K, F = a.F, H = a.H, I = a.F + 4;
-    const bool live = n < N && (a.cell_ntiles == nullptr || a.cell_ntiles[n] != 0);
-    if (!__any(live)) return;  // uniform per wavefront
-    const CamK& k = a.fr->k;
-    const int64_t M = (int64_t)N * K;
-
-    // input vector (f, delta, d) and the layer-1 activations in registers
-    float x[CI], h[CH];
-    float px = 0.0f, py = 0.0f, pz = 0.0f, ex = 0.0f, ey = 0.0f, ez = 0.0f, dist = 1.0f;
-    if (live) {
-        px = a.cell_pos[n];
-        py = a.cell_pos[N + n];
-        pz = a.cell_pos[2 * N + n];
-        ex = px - k.o[0];
-        ey = py - k.o[1];
-        ez = pz - k.o[2];
-        dist = sqrtf((ex * ex + ey * ey) + ez * ez);
-    }
-#pragma unroll
-    for (int i = 0; i < CI; i++) {
-        float v = 0.0f;
-        if (i < F) v = live ? a.features[(int64_t)i * N + n] : 0.0f;
-        else if (i == F) v = dist;
-        else if (i == F + 1) v = ex / dist;
-        else if (i == F + 2) v = ey / dist;
-        else if (i == F + 3) v = ez / dist;
-        x[i] = v;
-    }
-    const int A = wave == 0 ? 1 : wave == 3 ? 4 : 3;  // outputs per Gaussian of this decoder
-    const float* w = a.weights + a.woff[wave];
-    const float* W1 = w;
-    const float* b1 = W1 + (int64_t)I * H;
-    const float* W2 = b1 + H;
-    const int O = K * A;
-    const float* b2 = W2 + (int64_t)H * O;
-#pragma unroll
-    for (int j = 0; j < CH; j++) {
-        float acc = 0.0f;
-        if (j < H) {
-            acc = b1[j];
-#pragma unroll
-            for (int i = 0; i < CI; i++)
-                if (i < I) acc = fmaf(x[i], W1[(int64_t)i * H + j], acc);
-        }
-        h[j] = acc > 0.0f ? acc : 0.0f;
-    }
-    if (!live) return;
-    const float S[3] = {a.cell_scale[n], a.cell_scale[N + n], a.cell_scale[2 * N + n]};
-    for (int kk = 0; kk < K; kk++) {
-        const int64_t g = (int64_t)n * K + kk;
-        float y[4];
-#pragma unroll
-        for (int c = 0; c < 4; c++) {
-            float acc = 0.0f;
-            if (c < A) {
-                const int o = kk * A + c;
-                acc = b2[o];
-#pragma unroll
-                for (int j = 0; j < CH; j++)
-                    if (j < H) acc = fmaf(h[j], W2[(int64_t)j * O + o], acc);
-            }
-            y[c] = acc;
-        }
-        if (wave == 0) {
-            a.opac[g] = tanhf(y[0]);
-            // centre in the cell frame
-            float R[9];
-            cell_rot32(a.cell_rot[n], a.cell_rot[N + n], a.cell_rot[2 * N + n], a.cell_rot[3 * N + n], R);
-            const float u0 = a.offsets[g] * S[0], u1 = a.offsets[M + g] * S[1], u2 = a.offsets[2 * M + g] * S[2];
-            a.means[g] = px + ((R[0] * u0 + R[1] * u1) + R[2] * u2);
-            a.means[M + g] = py + ((R[3] * u0 + R[4] * u1) + R[5] * u2);
-            a.means[2 * M + g] = pz + ((R[6] * u0 + R[7] * u1) + R[8] * u2);
-        } else if (wave == 1) {
-#pragma unroll
-            for (int c = 0; c < 3; c++) a.color[c * M + g] = 1.0f / (1.0f + __expf(-y[c]));
-        } else if (wave == 2) {
-            const float o0 = a.offsets[g], o1 = a.offsets[M + g], o2 = a.offsets[2 * M + g];
-            const float lim = 1.0f - sqrtf((o0 * o0 + o1 * o1) + o2 * o2);
-#pragma unroll
-            for (int c = 0; c < 3; c++) {
-                float r = sigmoid32_def(y[c]);
-                r = r < lim ? r : lim;
-                r = r > 0.0f ? r : 0.0f;
-                a.scales[c * M + g] = r * S[c];
-            }
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; c++) a.rots[c * M + g] = y[c];
-        }
-    }
-}
-
-// Exact-size variant (F, H known at compile time): layer 1 runs input-major
-// (every weight row is one contiguous scalar load) and layer 2 reads, per
-// hidden unit, the A contiguous outputs of one member.  Each sum keeps the
-// order of the general kernel: bias first, then ascending index.
-struct DecodeOut {
-    float* __restrict__ means;
-    float* __restrict__ scales;
-    float* __restrict__ rots;
-    float* __restrict__ opac;
-    float* __restrict__ color;
+// A decoder's weights in LDS: W1 [I][CH], b1 [CH], W2 [O][CH] output-major, b2
+// [O].  Hidden units beyond H have zero weights in and -0 out: their product
+// -0 leaves any sum as it is.
+struct DecoderLds {
+    float *w1, *b1, *w2, *b2;
 };
 
-template <int F, int H, int A>
-__device__ inline void decode_wave(const DecodeArgs& a, const float* __restrict__ w, const float (&x)[F + 4],
-                                   bool live, int n, float px, float py, float pz, int wave, const DecodeOut& out) {
+__host__ __device__ inline size_t decode_lds_floats(int I, int CH, int O) { return (size_t)I * CH + CH + (size_t)O * CH + O; }
+
+// Members of a cell per round through the LDS buffer of `slots` outputs per
+// cell: the rounds are even, and a lane's row of the buffer has an odd length.
+__device__ __forceinline__ int members_per_round(int K, int A, int slots) {
+    const int most = ((slots / A) - 1) | 1;
+    const int rounds = (K + most - 1) / most;
+    return (K + rounds - 1) / rounds;
+}
+
+// The wavefront's 64 cells from n0 on, one per lane (live: the ones to decode).
+// buf: its buffer, 64 x slots outputs.
+template <int CH, int A>
+__device__ inline void decode_cells(const DecodeArgs& a, const DecoderLds& w, float* buf, int slots, int n0, uint64_t live,
+                                    int lane) {
 #pragma clang fp contract(off)
-    constexpr int I = F + 4;
-    const int K = a.K, N = a.N;
-    const int O = K * A;
-    const float* W1 = w;
-    const float* b1 = W1 + I * H;
-    const float* W2 = b1 + H;
-    const float* b2 = W2 + (int64_t)H * O;
-    float h[H];
-#pragma unroll
-    for (int j = 0; j < H; j++) h[j] = b1[j];
-#pragma unroll
-    for (int i = 0; i < I; i++) {
-        const float xi = x[i];
-#pragma unroll
-        for (int j = 0; j < H; j++) h[j] = fmaf(xi, W1[i * H + j], h[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < H; j++) h[j] = h[j] > 0.0f ? h[j] : 0.0f;
-    // every lane stays in the loop (uniform control flow keeps the weight
-    // loads scalar); only live lanes store
+    const int N = a.N, K = a.K, F = a.F;
+    const CamK& k = a.fr->k;
     const int64_t M = (int64_t)N * K;
-    const int nn = live ? n : 0;
-    const float S[3] = {a.cell_scale[nn], a.cell_scale[N + nn], a.cell_scale[2 * N + nn]};
-    for (int kk = 0; kk < K; kk++) {
-        const int64_t g = (int64_t)n * K + kk;
-        float y[A];
+    const int m = (live >> lane) & 1 ? n0 + lane : 0;  // the lane's cell, or cell 0 in its place
+    const float ex = a.cell_pos[m] - k.o[0], ey = a.cell_pos[(int64_t)N + m] - k.o[1];
+    const float ez = a.cell_pos[2 * (int64_t)N + m] - k.o[2];
+    const float dist = sqrtf((ex * ex + ey * ey) + ez * ez);
+    // layer 1, input by input: h_j = b1_j + x_0 W1_0j + x_1 W1_1j + ...
+    float h[CH];
 #pragma unroll
-        for (int c = 0; c < A; c++) y[c] = b2[kk * A + c];
+    for (int j = 0; j < CH; j++) h[j] = w.b1[j];
+    const auto input = [&](int i, float x) __attribute__((always_inline)) {
+        const float4* row = reinterpret_cast<const float4*>(w.w1 + i * CH);
 #pragma unroll
-        for (int j = 0; j < H; j++) {
-#pragma unroll
-            for (int c = 0; c < A; c++) y[c] = fmaf(h[j], W2[(int64_t)j * O + kk * A + c], y[c]);
+        for (int j = 0; j < CH / 4; j++) {
+            const float4 q = row[j];
+            h[4 * j] = fmaf(x, q.x, h[4 * j]);
+            h[4 * j + 1] = fmaf(x, q.y, h[4 * j + 1]);
+            h[4 * j + 2] = fmaf(x, q.z, h[4 * j + 2]);
+            h[4 * j + 3] = fmaf(x, q.w, h[4 * j + 3]);
         }
-        if (!live) continue;
-        if (wave == 0) {
-            out.opac[g] = tanhf(y[0]);
-            float R[9];
-            cell_rot32(a.cell_rot[n], a.cell_rot[N + n], a.cell_rot[2 * N + n], a.cell_rot[3 * N + n], R);
-            const float u0 = a.offsets[g] * S[0], u1 = a.offsets[M + g] * S[1], u2 = a.offsets[2 * M + g] * S[2];
-            out.means[g] = px + ((R[0] * u0 + R[1] * u1) + R[2] * u2);
-            out.means[M + g] = py + ((R[3] * u0 + R[4] * u1) + R[5] * u2);
-            out.means[2 * M + g] = pz + ((R[6] * u0 + R[7] * u1) + R[8] * u2);
-        } else if (wave == 1) {
+    };
+    // eight features at a time, the next eight in flight meanwhile
+    constexpr int kBlock = 8;
+    float x[kBlock];
 #pragma unroll
-            for (int c = 0; c < A; c++) out.color[c * M + g] = 1.0f / (1.0f + __expf(-y[c]));
-        } else if (wave == 2) {
-            const float o0 = a.offsets[g], o1 = a.offsets[M + g], o2 = a.offsets[2 * M + g];
-            const float lim = 1.0f - sqrtf((o0 * o0 + o1 * o1) + o2 * o2);
+    for (int q = 0; q < kBlock; q++) x[q] = a.features[(int64_t)min(q, F - 1) * N + m];
+    for (int i0 = 0; i0 < F; i0 += kBlock) {
+        float nx[kBlock];
 #pragma unroll
-            for (int c = 0; c < A; c++) {
-                float r = sigmoid32_def(y[c]);
-                r = r < lim ? r : lim;
-                r = r > 0.0f ? r : 0.0f;
-                out.scales[c * M + g] = r * S[c];
+        for (int q = 0; q < kBlock; q++) nx[q] = a.features[(int64_t)min(i0 + kBlock + q, F - 1) * N + m];
+#pragma unroll
+        for (int q = 0; q < kBlock; q++)
+            if (i0 + q < F) input(i0 + q, x[q]);  // uniform
+#pragma unroll
+        for (int q = 0; q < kBlock; q++) x[q] = nx[q];
+    }
+    input(F, dist);
+    input(F + 1, ex / dist);
+    input(F + 2, ey / dist);
+    input(F + 3, ez / dist);
+#pragma unroll
+    for (int j = 0; j < CH; j++) h[j] = h[j] > 0.0f ? h[j] : 0.0f;
+    const int G = members_per_round(K, A, slots), row = G | 1, plane = 64 * row;
+    const bool color = A == 3 && blockIdx.y == 1;
+    for (int k0 = 0; k0 < K; k0 += G) {
+        const int gc = min(G, K - k0);
+        // layer 2 of members k0 .. k0 + gc - 1, a cell per lane:
+        // y_o = b2_o + h_0 W2_0o + h_1 W2_1o + ...
+        for (int kk = 0; kk < gc; kk++) {
+            float y[A];
+#pragma unroll
+            for (int o = 0; o < A; o++) y[o] = w.b2[(k0 + kk) * A + o];
+            const float* w2 = w.w2 + (size_t)(k0 + kk) * A * CH;
+#pragma unroll
+            for (int j = 0; j < CH / 4; j++) {
+                float4 q[A];
+#pragma unroll
+                for (int o = 0; o < A; o++) q[o] = reinterpret_cast<const float4*>(w2 + o * CH)[j];
+#pragma unroll
+                for (int o = 0; o < A; o++) {
+                    y[o] = fmaf(h[4 * j], q[o].x, y[o]);
+                    y[o] = fmaf(h[4 * j + 1], q[o].y, y[o]);
+                    y[o] = fmaf(h[4 * j + 2], q[o].z, y[o]);
+                    y[o] = fmaf(h[4 * j + 3], q[o].w, y[o]);
+                }
             }
-        } else {
 #pragma unroll
-            for (int c = 0; c < A; c++) out.rots[c * M + g] = y[c];
+            for (int o = 0; o < A; o++) buf[o * plane + lane * row + kk] = y[o];
         }
+        wave_order();
+        // a Gaussian per lane (e / gc through a float: e < 2^12, exact as
+        // (e + 0.5) / gc is at least 0.5 / gc off any integer)
+        const float inv = 1.0f / (float)gc;
+        for (int e = lane; e < 64 * gc; e += 64) {
+            const int cell = (int)(((float)e + 0.5f) * inv), kk = e - cell * gc;
+            if (!((live >> cell) & 1)) continue;
+            const int n = n0 + cell;
+            const int64_t g = (int64_t)n * K + k0 + kk;
+            const float* yb = buf + cell * row + kk;
+            if constexpr (A == 1) {
+                a.opac[g] = tanhf(yb[0]);
+                // centre in the cell frame
+                float R[9];
+                cell_rot32(a.cell_rot[n], a.cell_rot[(int64_t)N + n], a.cell_rot[2 * (int64_t)N + n],
+                           a.cell_rot[3 * (int64_t)N + n], R);
+                const float u0 = a.offsets[g] * a.cell_scale[n], u1 = a.offsets[M + g] * a.cell_scale[(int64_t)N + n],
+                            u2 = a.offsets[2 * M + g] * a.cell_scale[2 * (int64_t)N + n];
+                a.means[g] = a.cell_pos[n] + ((R[0] * u0 + R[1] * u1) + R[2] * u2);
+                a.means[M + g] = a.cell_pos[(int64_t)N + n] + ((R[3] * u0 + R[4] * u1) + R[5] * u2);
+                a.means[2 * M + g] = a.cell_pos[2 * (int64_t)N + n] + ((R[6] * u0 + R[7] * u1) + R[8] * u2);
+            } else if constexpr (A == 4) {
+#pragma unroll
+                for (int o = 0; o < 4; o++) a.rots[o * M + g] = yb[o * plane];
+            } else if (color) {
+#pragma unroll
+                for (int o = 0; o < 3; o++) a.color[o * M + g] = 1.0f / (1.0f + __expf(-yb[o * plane]));
+            } else {
+                const float o0 = a.offsets[g], o1 = a.offsets[M + g], o2 = a.offsets[2 * M + g];
+                const float lim = 1.0f - sqrtf((o0 * o0 + o1 * o1) + o2 * o2);
+#pragma unroll
+                for (int o = 0; o < 3; o++) {
+                    float r = sigmoid32_def(yb[o * plane]);
+                    r = r < lim ? r : lim;
+                    r = r > 0.0f ? r : 0.0f;
+                    a.scales[o * M + g] = r * a.cell_scale[(int64_t)o * N + n];
+                }
+            }
+        }
+        wave_order();  // the buffer is reused by the next round
     }
 }
 
-template <int F, int H>
-__global__ __launch_bounds__(256) void k_decode_exact(DecodeArgs a, const float* __restrict__ weights,
-                                                      float* __restrict__ means, float* __restrict__ scales,
-                                                      float* __restrict__ rots, float* __restrict__ opac,
-                                                      float* __restrict__ color) {
-#pragma clang fp contract(off)
-    // one decoder per workgroup (blockIdx.y), one cell per thread: the
-    // wavefronts of a compute unit mostly run the same code
-    const int wave = blockIdx.y;
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    const int N = a.N;
-    const bool live = n < N && (a.cell_ntiles == nullptr || a.cell_ntiles[n] != 0);
-    if (!__any(live)) return;  // uniform per wavefront
-    const CamK& k = a.fr->k;
-    float x[F + 4];
-    float px = 0.0f, py = 0.0f, pz = 0.0f, ex = 0.0f, ey = 0.0f, ez = 0.0f, dist = 1.0f;
-    if (live) {
-        px = a.cell_pos[n];
-        py = a.cell_pos[N + n];
-        pz = a.cell_pos[2 * N + n];
-        ex = px - k.o[0];
-        ey = py - k.o[1];
-        ez = pz - k.o[2];
-        dist = sqrtf((ex * ex + ey * ey) + ez * ez);
+template <int CH>
+__global__ __launch_bounds__(kDecodeThreads) __attribute__((amdgpu_waves_per_eu(CH == 32 ? 4 : 2))) void k_decode(DecodeArgs a, int slots) {
+    extern __shared__ float s_w[];
+    const int dec = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int A = dec == 0 ? 1 : dec == 3 ? 4 : 3;  // outputs per Gaussian of this decoder
+    const int H = a.H, I = a.F + 4, O = a.K * A;
+    // the cells, before the weights: a workgroup with none visible has no work
+    const int n0 = (int)(blockIdx.x * kDecodeWaves + wave) * 64, n = n0 + lane;
+    const uint64_t live = __ballot(n < a.N && (a.cell_ntiles == nullptr || a.cell_ntiles[n] != 0));
+    if (!__syncthreads_or(live != 0)) return;
+    DecoderLds w;
+    w.w1 = s_w;
+    w.w2 = w.w1 + I * CH;  // 16-byte aligned: CH is a multiple of four
+    w.b1 = w.w2 + (size_t)O * CH;
+    w.b2 = w.b1 + CH;
+    float* buf = w.b2 + O + (size_t)wave * 64 * slots;
+    const float* W1 = a.weights + a.woff[dec];
+    const float* b1 = W1 + (int64_t)I * H;
+    const float* W2 = b1 + H;
+    const float* b2 = W2 + (int64_t)H * O;
+    // several loads in flight per thread: one at a time, a copy of 4,000 weights
+    // takes 20 us
+#pragma unroll 8
+    for (int q = tid; q < I * CH; q += kDecodeThreads) {
+        const int i = q / CH, j = q % CH;
+        w.w1[q] = j < H ? W1[(int64_t)i * H + j] : 0.0f;
     }
-#pragma unroll
-    for (int i = 0; i < F; i++) x[i] = live ? a.features[(int64_t)i * N + n] : 0.0f;
-    x[F] = dist;
-    x[F + 1] = ex / dist;
-    x[F + 2] = ey / dist;
-    x[F + 3] = ez / dist;
-    const DecodeOut out{means, scales, rots, opac, color};
-    const float* __restrict__ w = weights + a.woff[wave];
-    if (wave == 0)
-        decode_wave<F, H, 1>(a, w, x, live, n, px, py, pz, wave, out);
-    else if (wave == 3)
-        decode_wave<F, H, 4>(a, w, x, live, n, px, py, pz, wave, out);
-    else
-        decode_wave<F, H, 3>(a, w, x, live, n, px, py, pz, wave, out);
+    for (int j = tid; j < CH; j += kDecodeThreads) w.b1[j] = j < H ? b1[j] : 0.0f;
+    for (int o = lane; o < O; o += 64)
+#pragma unroll 8
+        for (int j = wave; j < CH; j += kDecodeWaves) w.w2[o * CH + j] = j < H ? W2[(int64_t)j * O + o] : -0.0f;
+    for (int o = tid; o < O; o += kDecodeThreads) w.b2[o] = b2[o];
+    __syncthreads();
+    if (!live) return;  // uniform per wavefront
+    if (dec == 0) decode_cells<CH, 1>(a, w, buf, slots, n0, live, lane);
+    else if (dec == 3) decode_cells<CH, 4>(a, w, buf, slots, n0, live, lane);
+    else decode_cells<CH, 3>(a, w, buf, slots, n0, live, lane);
+}
+
+template <int CH>
+static void decode(hipStream_t st, const DecodeArgs& a) {
+    const size_t weights = decode_lds_floats(a.F + 4, CH, 4 * a.K) * sizeof(float);
+    const size_t per_slot = kDecodeThreads * sizeof(float);
+    // outputs per cell in the LDS buffer: at least the four of one quaternion
+    int slots = (int)((kDecodeLds - weights) / per_slot);
+    slots = slots < kDecodeSlots ? slots : kDecodeSlots;
+    hipLaunchKernelGGL(k_decode<CH>, dim3((unsigned)((a.N + kDecodeThreads - 1) / kDecodeThreads), 4), dim3(kDecodeThreads),
+                       weights + slots * per_slot, st, a, slots);
 }
 
 void launch_decode(hipStream_t st, const DecodeArgs& a) {
     if (a.N <= 0) return;
-    const dim3 grid((unsigned)((a.N + 255) / 256), 4);
-    if (a.F == 32 && a.H == 32)
-        hipLaunchKernelGGL((k_decode_exact<32, 32>), grid, dim3(256), 0, st, a, a.weights, a.means, a.scales, a.rots,
-                           a.opac, a.color);
-    else if (a.F <= 32 && a.H <= 32)
-        hipLaunchKernelGGL((k_decode<36, 32>), grid, dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_decode<kMaxFeature + 4, kMaxHidden>), grid, dim3(256), 0, st, a);
+    if (a.H <= 32) decode<32>(st, a);
+    else decode<64>(st, a);
 }
 
 }  // namespace dgs
