@@ -5,7 +5,7 @@ Workload: the clustered 1M-Gaussian scene (100,000 cells x 10 Gaussians, SH
 degree 3, seed 1) rendered at 1920x1080 along a 60-frame orbit, inputs
 resident in HBM.  A step is one whole frame through the C ABI: cell
 preprocess, Gaussian projection, depth sort of the cells, scan + key
-emission, onesweep radix sort of the keys on their tile bits, tile ranges
+emission, radix sort of the keys on their tile bits, tile ranges
 and work queue, and the hybrid compositor.  The same frames are
 also rendered by the per-Gaussian-sort alpha-blending path of the same
 library (the comparison path).

@@ -361,15 +361,14 @@ dgs_status dgs_set_timing(dgs_ctx ctx, int32_t enable);
 dgs_status dgs_get_timing(dgs_ctx ctx, float* ms, int32_t n_stages, int32_t* frames);
 
 /* Stable in-place sort of n (key, value) pairs on the low key_bits bits
- * (1..64) with the library's onesweep radix sort.  keys/values are device
+ * (1..64) with the library's radix sort.  keys/values are device
  * buffers of n entries. */
 dgs_status dgs_sort_pairs(dgs_ctx ctx, uint64_t* keys, uint32_t* values, int64_t n, int32_t key_bits);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * sort as dgs_sort_pairs, with the same results, whose scratch memory (the
- * ping-pong key/value buffers, digit counts, look-back words and counters,
- * ~14.3 MB) is one static device array per GPU, held from library load until
+ * ping-pong key/value buffers and digit counts, ~13.3 MB) is one static device array per GPU, held from library load until
  * the process ends.  It calls no hipMalloc, hipFree or allocating routine;
  * it enqueues on the context's stream (kernels and device-to-device copies,
  * no memset).  n above DGS_SORT_NOALLOC_MAX_KEYS returns DGS_ERR_INVALID_ARG

@@ -613,6 +613,12 @@ static bool per_tile_order(dgs_ctx c, int64_t tiles, bool cells) {
     return c->cap_keys <= kPerTileOrderCapacity * tiles;
 }
 
+// Scratch of a sort of the keys: the upper half of sort_status (the tile
+// lists' look-back words, in the lower half, must only ever hold such words).
+static SortScratch sort_scratch(dgs_ctx c) {
+    return SortScratch{(uint32_t*)(c->sort_status + c->sort_status_cap / 2), c->hist};
+}
+
 // The context's second stream and its fork/join events, created on first
 // use.  Not while the context's stream is being captured into a graph (a
 // stream cannot be created inside a capture): such a frame runs on one
@@ -667,7 +673,7 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     // each tile's run after the tile sort (the same order); with the second
     // stream, the work queue is then built there beside the per-tile sort
     const int chunks = per_tile_order(c, tiles, cells)
-                           ? bin_chunks(P, k.TX, k.TY, 2 * c->cap_keys, c->sort_status_cap)
+                           ? bin_chunks(P, k.TX, k.TY, 2 * c->cap_keys, c->sort_status_cap / 2)
                            : 0;
     const bool per_tile = chunks > 0;
     const bool overlap = cells && !c->timing && c->two_streams && ensure_aux(c);
@@ -680,14 +686,11 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
 
     StageMarks sm(c);
     {
-        // per-frame zeroing: scan/sort tickets (misc[1..12]), statistics
-        // counters and, for the global order, digit histograms and tile ranges
+        // per-frame zeroing: the scan's ticket, statistics counters and, for
+        // the global order, tile ranges
         ClearList cl;
-        cl.add(c->misc + 1, 12);
-        if (!per_tile) {
-            cl.add(c->hist, 8 * 256);
-            cl.add(ranges, 2 * (size_t)tiles);
-        }
+        cl.add(c->misc + 1, 1);
+        if (!per_tile) cl.add(ranges, 2 * (size_t)tiles);
         if (o.stats || save) cl.add((uint32_t*)c->counters, 10);
         cl.bump = c->misc + 13;
         FrameK f{k, o, out->color, out->weight_sum, out->final_T, out->last, nullptr, nullptr, nullptr, nullptr};
@@ -746,21 +749,19 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
                                cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, torder, queue,
                                cells ? c->load_dev + 1 : nullptr, (uint32_t)P);
     } else {
-        launch_prim_keys(q, P, c->p_ntiles, c->p_depth, c->pk0, c->pv0, c->hist);
-        const SortScratch ps{c->hist, c->psort_status, c->misc + 2};
-        const bool pin1 = launch_radix_sort32(q, c->pk0, c->pv0, c->pk1, c->pv1, (uint32_t)P, ps, c->misc + 13, 1,
-                                              c->dev_err);
+        launch_prim_keys(q, P, c->p_ntiles, c->p_depth, c->pk0, c->pv0);
+        const bool pin1 = launch_radix_sort32(q, c->pk0, c->pv0, c->pk1, c->pv1, (uint32_t)P,
+                                              SortScratch{(uint32_t*)c->psort_status, c->hist});
         const uint32_t* order = pin1 ? c->pv1 : c->pv0;
         sm.mark(3);
         launch_exclusive_scan(q, c->p_ntiles, c->p_offsets, P, c->misc + 0, c->scan_status, c->misc + 13, c->misc + 1,
                               c->dev_err, order);
         launch_emit_keys(q, P, order, c->p_ntiles, c->p_offsets, prect, c->p_depth, k.TX, cap, c->keys0, c->vals0,
-                         c->hist + 4 * 256, sort_passes(tbits), c->dev_err);
+                         c->dev_err);
         sm.mark(4);
         // stable sort on the tile bits
-        const SortScratch ss{c->hist + 4 * 256, c->sort_status, c->misc + 6};
-        in1 = launch_radix_sort(q, c->keys0, c->vals0, c->keys1, c->vals1, c->misc + 0, cap, tbits, ss, c->misc + 13,
-                                c->dev_err, true, 32, 5);
+        in1 = launch_radix_sort(q, c->keys0, c->vals0, c->keys1, c->vals1, c->misc + 0, cap, tbits,
+                                sort_scratch(c), 32);
         svals = in1 ? c->vals1 : c->vals0;
         sm.mark(5);
         launch_tile_ranges(q, in1 ? c->keys1 : c->keys0, c->misc + 0, cap, ranges, svals, save ? save->vals : nullptr,
@@ -1068,15 +1069,8 @@ dgs_status dgs_sort_pairs(dgs_ctx c, uint64_t* keys, uint32_t* values, int64_t n
     dgs_status st;
     if ((st = ensure(c, 0, 0, n, 0)) != DGS_OK) return st;
     c->last_mode = -1;  // the sort overwrites the last render's sorted lists (saved frames keep their own)
-    ClearList cl;
-    cl.add(c->hist, 8 * 256);
-    cl.add(c->misc + 2, 8);
-    cl.bump = c->misc + 13;
-    launch_clear(c->stream, cl);
-    launch_fill_u32(c->stream, c->misc + 10, (uint32_t)n, 1);
-    SortScratch ss{c->hist, c->sort_status, c->misc + 2};
-    const bool in1 = launch_radix_sort(c->stream, keys, values, c->keys1, c->vals1, c->misc + 10, (uint32_t)n,
-                                       key_bits, ss, c->misc + 13, c->dev_err);
+    const bool in1 = launch_radix_sort(c->stream, keys, values, c->keys1, c->vals1, nullptr, (uint32_t)n, key_bits,
+                                       sort_scratch(c));
     if (in1) {
         hipMemcpyAsync(keys, c->keys1, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, c->stream);
         hipMemcpyAsync(values, c->vals1, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, c->stream);

@@ -14,8 +14,6 @@
 inline std::string timeout_message(int e) {
     std::string m = "device look-back wait timed out in";
     if (e & (1 << dgs::kErrWaitScan)) m += " the exclusive scan";
-    if ((e & (1 << dgs::kErrWaitScan)) && (e & (1 << dgs::kErrWaitSort))) m += " and";
-    if (e & (1 << dgs::kErrWaitSort)) m += " a radix sort pass";
     return m;
 }
 
@@ -72,7 +70,7 @@ struct dgs_ctx_s {
     uint32_t *p_depth = nullptr, *p_ntiles = nullptr, *p_offsets = nullptr;
     uint64_t* p_rect = nullptr;
     uint32_t *pk0 = nullptr, *pk1 = nullptr, *pv0 = nullptr, *pv1 = nullptr;  // depth sort of the primitives
-    uint64_t* psort_status = nullptr;
+    uint64_t* psort_status = nullptr;  // digit counts of the depth sort
     float* cell_v = nullptr;
     dgs::GRec* recs = nullptr;
     uint64_t* grect = nullptr;
@@ -82,7 +80,7 @@ struct dgs_ctx_s {
     uint32_t* tile_order = nullptr;
     uint64_t* scan_status = nullptr;
     size_t scan_status_cap = 0;
-    uint64_t* sort_status = nullptr;
+    uint64_t* sort_status = nullptr;  // lower half: the tile lists' look-back words; upper: digit counts of the key sort
     size_t sort_status_cap = 0;
     dgs::FrameK* frame = nullptr;  // device copy of the current frame's camera and options
     float* dec = nullptr;  // decoded Gaussians of a neural render: [14][M] (means, scales, rots, opacity, colour)
@@ -94,11 +92,8 @@ struct dgs_ctx_s {
     float* loss_coef = nullptr;   // [3][C][H][W] per-pixel coefficients of the loss gradient
     double* loss_part = nullptr;  // [tiles][2] per-tile sums of the loss
     int64_t cap_loss_coef = 0, cap_loss_part = 0;
-    uint32_t* hist = nullptr;     // [8][256]: [0..3] primitive depth bytes, [4..6] key tile bytes
-    uint32_t* misc = nullptr;     // [0] key total, [1] scan ticket, [2..5] depth sort tickets,
-                                  // [6..8] tile sort tickets, [9] spare, [10] sort count,
-                                  // [11..12] spare,
-                                  // [13] look-back frame counter
+    uint32_t* hist = nullptr;     // [256] digit totals of a sort's pass
+    uint32_t* misc = nullptr;     // [0] key total, [1] scan ticket, [2..12] spare, [13] look-back frame counter
     uint32_t* queue = nullptr;    // [kQueueWords] the compositor's work queue (a saved frame has its own)
     int* dev_err = nullptr;
     unsigned long long* counters = nullptr;  // n_val, n_rendered, n_box, n_cell_hits, n_cell_pixels

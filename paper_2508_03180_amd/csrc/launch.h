@@ -63,20 +63,16 @@ void launch_clear(hipStream_t st, const ClearList& l, const FrameK* f = nullptr,
 
 // Depth sort keys of the primitives: key p = depth bits of p when it touches
 // a tile, else all ones (it then sorts last and emits nothing); value = p.
-// Also accumulates the four byte histograms of the keys into hist
-// ([4][256], zeroed beforehand).
 void launch_prim_keys(hipStream_t st, int P, const uint32_t* ntiles, const uint32_t* depth, uint32_t* keys,
-                      uint32_t* vals, uint32_t* hist);
+                      uint32_t* vals);
 
 // One key per (primitive, touched tile), the primitives taken in depth
 // order (order[i], i < P): key = tile << 32 | depth bits, value = primitive
 // id, written at offsets[i] in row-major tile order.  A stable sort of these
-// keys on the tile bits alone then yields the (tile, depth, id) order.  Also
-// accumulates the digit histograms of the kept keys' tile bytes into hist
-// ([tile_passes][256], zeroed beforehand).
+// keys on the tile bits alone then yields the (tile, depth, id) order.
 void launch_emit_keys(hipStream_t st, int P, const uint32_t* order, const uint32_t* ntiles,
                       const uint32_t* offsets, const uint64_t* prect, const uint32_t* depth, int TX, uint32_t cap,
-                      uint64_t* keys, uint32_t* vals, uint32_t* hist, int tile_passes, int* err);
+                      uint64_t* keys, uint32_t* vals, int* err);
 
 // Tile lists by counting, for the per-tile order: one entry (depth bits <<
 // 32 | id) per (primitive, touched tile) in its tile's run, in no particular
@@ -124,28 +120,21 @@ void launch_tile_ranges(hipStream_t st, const uint64_t* keys, const uint32_t* n_
                         uint32_t* ranges, const uint32_t* vin = nullptr, uint32_t* vout = nullptr,
                         uint64_t* load = nullptr, uint32_t tiles = 0);
 
-// Onesweep LSD radix sort of (u64 key, u32 value) pairs on key bits
+// LSD radix sort of (u64 key, u32 value) pairs on key bits
 // [first_bit, first_bit + bits).  The count is read on the device from
-// *n_ptr (clamped to cap).  Returns true when the sorted data ends in
-// (k1, v1), false for (k0, v0).  hist (8 x 256 words) and tickets (8 words)
-// must be zero beforehand; with hist_ready, hist already holds the digit
-// counts of the keys (the key emission counts them).  Pass p tags its
-// look-back words with epoch_tag(*epoch, tag0 + p).
+// *n_ptr (clamped to cap; null: cap).  Returns true when the sorted data ends
+// in (k1, v1), false for (k0, v0).  The scratch needs no clearing.
 struct SortScratch {
-    uint32_t* hist;     // [passes][256]
-    uint64_t* status;   // sort_status_words(cap) look-back words
-    uint32_t* tickets;  // [passes]
+    uint32_t* counts;  // [sort_status_words(cap)] digit counts of the partitions
+    uint32_t* totals;  // [256] digit totals
 };
 int sort_passes(int bits);
 size_t sort_status_words(int64_t cap);
 bool launch_radix_sort(hipStream_t st, uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1,
-                       const uint32_t* n_ptr, uint32_t cap, int bits, const SortScratch& s,
-                       const uint32_t* epoch, int* err, bool hist_ready = false, int first_bit = 0,
-                       uint32_t tag0 = 1);
-// The same for n (host count) u32 keys on all 32 bits; hist must hold the
-// keys' four byte histograms.  Returns true when the data ends in (k1, v1).
+                       const uint32_t* n_ptr, uint32_t cap, int bits, const SortScratch& s, int first_bit = 0);
+// The same for n (host count) u32 keys on all 32 bits.
 bool launch_radix_sort32(hipStream_t st, uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, uint32_t n,
-                         const SortScratch& s, const uint32_t* epoch, uint32_t tag0, int* err);
+                         const SortScratch& s);
 
 struct CompositeArgs {
     const uint32_t* ranges;

@@ -1,4 +1,4 @@
-// dgs_sort_pairs_noalloc: the library's onesweep sort with its scratch
+// dgs_sort_pairs_noalloc: the library's radix sort with its scratch
 // memory in one static device array, for callers that cannot allocate.
 //
 // Every GPU the library runs on holds its own copy of `scratch` from module
@@ -18,20 +18,17 @@ namespace {
 constexpr int64_t kNoAllocMaxKeys = DGS_SORT_NOALLOC_MAX_KEYS;
 
 // Layout of the scratch array (byte offsets, each part 256-byte aligned):
-//   words  [64] u32: [0] look-back epoch counter, [1..8] pass tickets, [9] key count
-//   hist   [8][256] u32 digit counts
+//   totals [256] u32 digit totals
 //   keys   [kNoAllocMaxKeys] u64 and vals [kNoAllocMaxKeys] u32: the sort's ping-pong partner
-//   status look-back words of every partition, u64
-constexpr size_t kOffWords = 0;
-constexpr size_t kOffHist = 256;
-constexpr size_t kOffKeys = kOffHist + 8 * 256 * 4;
+//   counts digit counts of every partition, u32
+constexpr size_t kOffTotals = 0;
+constexpr size_t kOffKeys = kOffTotals + 256 * 4;
 constexpr size_t kOffVals = kOffKeys + 8 * (size_t)kNoAllocMaxKeys;
-constexpr size_t kOffStatus = kOffVals + 4 * (size_t)kNoAllocMaxKeys;
-// 256 look-back words per partition of at least 1,024 keys
-constexpr size_t kStatusWords = (size_t)((kNoAllocMaxKeys + 1023) / 1024) * 256;
-constexpr size_t kScratchBytes = kOffStatus + 8 * kStatusWords;  // ~14.3 MB
+constexpr size_t kOffCounts = kOffVals + 4 * (size_t)kNoAllocMaxKeys;
+// 256 counts per partition of at least 1,024 keys
+constexpr size_t kCountWords = (size_t)((kNoAllocMaxKeys + 1023) / 1024) * 256;
+constexpr size_t kScratchBytes = kOffCounts + 4 * kCountWords;  // ~13.3 MB
 
-// Zero at module load: epoch 0 (never used by a sort) in every status word.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -81,24 +78,11 @@ dgs_status dgs_sort_pairs_noalloc(dgs_ctx c, uint64_t* keys, uint32_t* values, i
         return DGS_ERR_DEVICE;
     }
     hipSetDevice(c->device);
-    uint32_t* words = reinterpret_cast<uint32_t*>(base + kOffWords);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(base + kOffHist);
     uint64_t* k1 = reinterpret_cast<uint64_t*>(base + kOffKeys);
     uint32_t* v1 = reinterpret_cast<uint32_t*>(base + kOffVals);
-    uint64_t* status = reinterpret_cast<uint64_t*>(base + kOffStatus);
-    // the array keeps the previous call's contents: the digit counts and
-    // the pass tickets start at zero again (a kernel, no memset node), the
-    // epoch counter moves on so that old look-back words are never read as
-    // this call's
-    ClearList cl;
-    cl.add(hist, 8 * 256);
-    cl.add(words + 1, 8);
-    cl.bump = words + 0;
-    launch_clear(c->stream, cl);
-    launch_fill_u32(c->stream, words + 9, (uint32_t)n, 1);
-    const SortScratch ss{hist, status, words + 1};
-    const bool in1 = launch_radix_sort(c->stream, keys, values, k1, v1, words + 9, (uint32_t)n, key_bits, ss,
-                                       words + 0, c->dev_err);
+    // the array keeps the previous call's contents, which no pass reads
+    const SortScratch ss{reinterpret_cast<uint32_t*>(base + kOffCounts), reinterpret_cast<uint32_t*>(base + kOffTotals)};
+    const bool in1 = launch_radix_sort(c->stream, keys, values, k1, v1, nullptr, (uint32_t)n, key_bits, ss);
     if (in1) {
         hipMemcpyAsync(keys, k1, (size_t)n * sizeof(uint64_t), hipMemcpyDeviceToDevice, c->stream);
         hipMemcpyAsync(values, v1, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToDevice, c->stream);

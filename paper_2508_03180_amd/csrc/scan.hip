@@ -14,19 +14,8 @@ namespace dgs {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanPart = kScanThreads * kScanItems;
-// Histogram-producing kernels run capped grids (grid-stride), each
-// workgroup adding its LDS histogram to the global one once: every global
-// bin then takes at most kHistBlocks atomics.  The key emission is bound by
-// its stores, so it keeps one primitive per thread up to the cap.
-constexpr int kHistBlocks = 512;
-constexpr int kPrimKeysPerBlock = 1024;
-constexpr int kEmitPrimsPerBlock = 256;
 constexpr int kOwnTiles = 32;
 
-static int hist_grid(int n, int per_block) {
-    const int b = (n + per_block - 1) / per_block;
-    return b < 1 ? 1 : (b > kHistBlocks ? kHistBlocks : b);
-}
 constexpr int kSpinLimit = 1 << 22;
 
 // status word: epoch << 34 | flag << 32 | value; flag 1 = partition total,
@@ -207,162 +196,82 @@ void launch_clear(hipStream_t st, const ClearList& l, const FrameK* f, FrameK* f
 
 // ---------------------------------------------------------------- keys
 
-// Depth keys of the primitives with their four byte histograms (per
-// workgroup in LDS, added to the global ones once).
+// Depth keys of the primitives.
 __global__ __launch_bounds__(256) void k_prim_keys(int P, const uint32_t* __restrict__ ntiles,
                                                    const uint32_t* __restrict__ depth, uint32_t* __restrict__ keys,
-                                                   uint32_t* __restrict__ vals, uint32_t* __restrict__ hist) {
-    __shared__ uint32_t sh[4][256];
-    for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) (&sh[0][0])[i] = 0u;
-    __syncthreads();
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < P; p += gridDim.x * blockDim.x) {
-        const uint32_t k = ntiles[p] ? depth[p] : 0xffffffffu;
-        keys[p] = k;
-        vals[p] = (uint32_t)p;
-#pragma unroll
-        for (int b = 0; b < 4; b++) atomicAdd(&sh[b][(k >> (8 * b)) & 255u], 1u);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) {
-        const uint32_t c = (&sh[0][0])[i];
-        if (c) atomicAdd(&hist[i], c);
-    }
+                                                   uint32_t* __restrict__ vals) {
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= P) return;
+    const uint32_t d = depth[p];  // beside the count: one round trip
+    keys[p] = ntiles[p] ? d : 0xffffffffu;
+    vals[p] = (uint32_t)p;
 }
 
 void launch_prim_keys(hipStream_t st, int P, const uint32_t* ntiles, const uint32_t* depth, uint32_t* keys,
-                      uint32_t* vals, uint32_t* hist) {
+                      uint32_t* vals) {
     if (P <= 0) return;
-    hipLaunchKernelGGL(k_prim_keys, dim3(hist_grid(P, kPrimKeysPerBlock)), dim3(256), 0, st, P, ntiles, depth, keys, vals, hist);
+    hipLaunchKernelGGL(k_prim_keys, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, P, ntiles, depth, keys, vals);
 }
 
-// Key emission in depth order, fused with the digit histograms of the tile
-// bytes (hist[b][d]: kept keys whose tile byte b is d).  Along one row of a
-// primitive's tile rectangle the tile ids are consecutive: the low tile byte
-// then covers a run of bins, counted with a difference array (a +1 / -1 pair
-// per run, prefix-summed at the end), and each higher tile byte changes at
-// most a few times, counted once per run.  Only keys below the capacity are
-// counted (they are the ones sorted).
+// Key emission in depth order.  A lane writes the keys of its own primitive
+// up to kOwnTiles; those of a larger one are dealt over the wavefront (one
+// lane writing the up to 32,400 keys of a screen-filling cell held a 4K frame
+// for 2.7 ms).
 __global__ __launch_bounds__(256) void k_emit_keys(int P, const uint32_t* __restrict__ order,
                                                    const uint32_t* __restrict__ ntiles,
                                                    const uint32_t* __restrict__ offsets,
                                                    const uint64_t* __restrict__ prect,
                                                    const uint32_t* __restrict__ depth, int TX, uint32_t cap,
                                                    uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                   uint32_t* __restrict__ hist, int passes, int* err) {
-    __shared__ uint32_t sh[3][256];  // tile bytes 1, 2 (byte 0 below)
-    __shared__ int32_t s_diff[257];  // low tile byte: difference array over the bins
-    __shared__ uint32_t s_all;       // low tile byte: runs of 256 or more add to every bin
-    __shared__ uint32_t s_wsum[4];
-    for (int i = threadIdx.x; i < 3 * 256; i += blockDim.x) (&sh[0][0])[i] = 0u;
-    for (int i = threadIdx.x; i < 257; i += blockDim.x) s_diff[i] = 0;
-    if (threadIdx.x == 0) s_all = 0u;
-    __syncthreads();
-    // counts one row of a primitive's tiles: `kept` consecutive tile ids from t0
-    const auto count_row = [&](uint32_t t0, uint32_t kept) {
-        if (kept) {
-            if (kept >= 256u) atomicAdd(&s_all, kept >> 8);
-            const uint32_t rem = kept & 255u, a = t0 & 255u;
-            if (rem) {
-                atomicAdd(&s_diff[a], 1);
-                if (a + rem <= 256u) {
-                    atomicAdd(&s_diff[a + rem], -1);
-                } else {
-                    atomicAdd(&s_diff[256], -1);
-                    atomicAdd(&s_diff[0], 1);
-                    atomicAdd(&s_diff[a + rem - 256u], -1);
-                }
+                                                   int* err) {
+    const int lane = threadIdx.x & 63, i0 = blockIdx.x * blockDim.x + threadIdx.x;
+    uint32_t p = (uint32_t)P;
+    if (i0 < P) p = order ? order[i0] : (uint32_t)i0;  // null order: id order
+    // a permutation of [0, P) unless a scan wait timed out
+    uint32_t nt = 0, off = 0, d = 0, t00 = 0, w = 0;
+    if (p < (uint32_t)P) nt = ntiles[p];
+    if (nt) {
+        off = offsets[i0];
+        if ((uint64_t)off + nt > cap) atomicOr(err, 1 << kErrCapacity);
+        const uint64_t r = prect[p];
+        d = depth[p];
+        const int tx0 = rect_x0(r) / kTile, ty0 = rect_y0(r) / kTile;
+        w = (uint32_t)(rect_x1(r) / kTile - tx0 + 1);
+        t00 = (uint32_t)(ty0 * TX + tx0);
+    }
+    if (nt <= (uint32_t)kOwnTiles)
+        for (uint32_t i = off, t0 = t00, done = 0; done < nt && i < cap; done += w, t0 += (uint32_t)TX) {
+            // one row of tiles: consecutive tile ids t0 .. t0 + kept - 1
+            const uint32_t kept = cap - i < w ? cap - i : w;
+            for (uint32_t j = 0; j < kept; j++) {
+                keys[i + j] = ((uint64_t)(t0 + j) << 32) | d;
+                vals[i + j] = p;
             }
+            i += kept;
         }
-        // higher tile bytes change rarely along a row: one count per run
-        for (int b = 1; b < passes; b++) {
-            const int sh8 = 8 * b;
-            for (uint32_t t = t0, te = t0 + kept; t < te;) {
-                const uint32_t run_end = ((t >> sh8) + 1u) << sh8;
-                const uint32_t stop = run_end < te ? run_end : te;
-                atomicAdd(&sh[b - 1][(t >> sh8) & 255u], stop - t);
-                t = stop;
-            }
-        }
-    };
-    // grid-stride over the depth order: a capped grid, so each workgroup adds
-    // its histogram to the global one once.  A lane writes the keys of its own
-    // primitive up to kOwnTiles; those of a larger one are dealt over the
-    // wavefront (one lane writing the up to 32,400 keys of a screen-filling
-    // cell held a 4K frame for 2.7 ms)
-    const int lane = threadIdx.x & 63;
-    for (int i0 = blockIdx.x * blockDim.x + threadIdx.x; i0 - lane < P; i0 += gridDim.x * blockDim.x) {
-        uint32_t p = (uint32_t)P;
-        if (i0 < P) p = order ? order[i0] : (uint32_t)i0;  // null order: id order
-        // a permutation of [0, P) unless a sort wait timed out
-        uint32_t nt = 0, off = 0, d = 0, t00 = 0, w = 0;
-        if (p < (uint32_t)P) nt = ntiles[p];
-        if (nt) {
-            off = offsets[i0];
-            if ((uint64_t)off + nt > cap) atomicOr(err, 1 << kErrCapacity);
-            const uint64_t r = prect[p];
-            d = depth[p];
-            const int tx0 = rect_x0(r) / kTile, ty0 = rect_y0(r) / kTile;
-            w = (uint32_t)(rect_x1(r) / kTile - tx0 + 1);
-            t00 = (uint32_t)(ty0 * TX + tx0);
-        }
-        if (nt <= (uint32_t)kOwnTiles)
-            for (uint32_t i = off, t0 = t00, done = 0; done < nt && i < cap; done += w, t0 += (uint32_t)TX) {
-                // one row of tiles: consecutive tile ids t0 .. t0 + kept - 1
-                const uint32_t kept = cap - i < w ? cap - i : w;
-                for (uint32_t j = 0; j < kept; j++) {
-                    keys[i + j] = ((uint64_t)(t0 + j) << 32) | d;
-                    vals[i + j] = p;
-                }
-                count_row(t0, kept);
-                i += kept;
-            }
-        for (uint64_t m = __ballot(nt > (uint32_t)kOwnTiles); m; m &= m - 1) {
-            const int l = __builtin_ctzll(m);
-            const uint32_t bn = (uint32_t)__builtin_amdgcn_readlane((int)nt, l), bw = (uint32_t)__builtin_amdgcn_readlane((int)w, l);
-            const uint32_t bo = (uint32_t)__builtin_amdgcn_readlane((int)off, l), bt = (uint32_t)__builtin_amdgcn_readlane((int)t00, l);
-            const uint32_t bd = (uint32_t)__builtin_amdgcn_readlane((int)d, l), bp = (uint32_t)__builtin_amdgcn_readlane((int)p, l);
-            const uint32_t keep = bo < cap ? min(bn, cap - bo) : 0u;  // keys below the capacity
-            // k / bw through a double: exact for k < 2^32 / bw with (k + 0.5) / bw
-            // at least 0.5 / bw off any integer
-            const double inv = 1.0 / (double)bw;
-            for (uint32_t k = lane; k < keep; k += 64) {
-                const uint32_t row = (uint32_t)(((double)k + 0.5) * inv);
-                keys[bo + k] = ((uint64_t)(bt + row * (uint32_t)TX + (k - row * bw)) << 32) | bd;
-                vals[bo + k] = bp;
-            }
-            for (uint32_t row = lane; row * bw < keep; row += 64)
-                count_row(bt + row * (uint32_t)TX, min(bw, keep - row * bw));
+    for (uint64_t m = __ballot(nt > (uint32_t)kOwnTiles); m; m &= m - 1) {
+        const int l = __builtin_ctzll(m);
+        const uint32_t bn = (uint32_t)__builtin_amdgcn_readlane((int)nt, l), bw = (uint32_t)__builtin_amdgcn_readlane((int)w, l);
+        const uint32_t bo = (uint32_t)__builtin_amdgcn_readlane((int)off, l), bt = (uint32_t)__builtin_amdgcn_readlane((int)t00, l);
+        const uint32_t bd = (uint32_t)__builtin_amdgcn_readlane((int)d, l), bp = (uint32_t)__builtin_amdgcn_readlane((int)p, l);
+        const uint32_t keep = bo < cap ? min(bn, cap - bo) : 0u;  // keys below the capacity
+        // k / bw through a double: exact for k < 2^32 / bw with (k + 0.5) / bw
+        // at least 0.5 / bw off any integer
+        const double inv = 1.0 / (double)bw;
+        for (uint32_t k = lane; k < keep; k += 64) {
+            const uint32_t row = (uint32_t)(((double)k + 0.5) * inv);
+            keys[bo + k] = ((uint64_t)(bt + row * (uint32_t)TX + (k - row * bw)) << 32) | bd;
+            vals[bo + k] = bp;
         }
     }
-    __syncthreads();
-    {
-        // low tile byte: inclusive prefix sum of the difference array
-        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-        int32_t x = s_diff[tid];
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int32_t u = __shfl_up(x, o, 64);
-            if (lane >= o) x += u;
-        }
-        if (lane == 63) s_wsum[wave] = (uint32_t)x;
-        __syncthreads();
-        for (int w = 0; w < wave; w++) x += (int32_t)s_wsum[w];
-        const uint32_t c = (uint32_t)x + s_all;
-        if (c) atomicAdd(&hist[tid], c);
-    }
-    for (int b = 1; b < passes; b++)
-        for (int i = threadIdx.x; i < 256; i += blockDim.x) {
-            const uint32_t c = sh[b - 1][i];
-            if (c) atomicAdd(&hist[b * 256 + i], c);
-        }
 }
 
 void launch_emit_keys(hipStream_t st, int P, const uint32_t* order, const uint32_t* ntiles,
                       const uint32_t* offsets, const uint64_t* prect, const uint32_t* depth, int TX, uint32_t cap,
-                      uint64_t* keys, uint32_t* vals, uint32_t* hist, int tile_passes, int* err) {
+                      uint64_t* keys, uint32_t* vals, int* err) {
     if (P <= 0) return;
-    hipLaunchKernelGGL(k_emit_keys, dim3(hist_grid(P, kEmitPrimsPerBlock)), dim3(256), 0, st, P, order, ntiles, offsets, prect, depth, TX,
-                       cap, keys, vals, hist, tile_passes, err);
+    hipLaunchKernelGGL(k_emit_keys, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, P, order, ntiles, offsets,
+                       prect, depth, TX, cap, keys, vals, err);
 }
 
 __global__ __launch_bounds__(256) void k_tile_ranges(const uint64_t* __restrict__ keys,
