@@ -5,13 +5,13 @@
 // Gaussian window (sigma 1.5, weights summing to 1), the image zero outside
 // its borders, c1 = 0.01^2, c2 = 0.03^2.
 //
-// Two passes, each streaming down strips of 64 columns: a wavefront owns
-// one strip (lane l: column c0 + l) and kRowsOut output rows; it walks the
-// kRowsOut + 10 input rows top to bottom, loading each row (with the
-// 5-column halo on either side) a few rows ahead, blurs it along the row
-// from a per-wavefront LDS row buffer, and keeps the last 11 row sums in
-// registers for the blur along the column -- no workgroup barriers, no
-// 2D tile in LDS:
+// Two passes, each streaming down strips of 64 columns: a wavefront (a
+// workgroup of its own) owns one strip (lane l: column c0 + l) and a number of
+// output rows (strip_rows); it walks those rows and the 5 above and below
+// them top to bottom, loading each row (with the 5-column halo on either
+// side) a few rows ahead, blurs it along the row from an LDS row buffer, and
+// keeps the last 11 row sums in registers for the blur along the column -- no
+// workgroup barriers, no 2D tile in LDS:
 //   k_ssim_fwd  window statistics of x and y -> the SSIM map; per-strip sums
 //               of SSIM and |x - y| (binary64) and, when a gradient is
 //               wanted, the three per-pixel coefficients of dL/dx:
@@ -20,10 +20,16 @@
 //               + y blur(dL/d E[xy]) + (1 - lam)/n sign(x - y)
 //               (the window is symmetric, so the adjoint of the zero-filled
 //               blur is the same blur);
-//   k_loss_sum  the strip sums in a fixed order -> L (binary64, stored as
-//               binary32): the result does not depend on scheduling.
-// Everything is HBM-bound: x and y are read twice, three coefficient planes
-// written and read once, the gradient written once.
+//   loss_sum    the strip sums in a fixed order -> L (binary64, stored as
+//               binary32): the result does not depend on scheduling.  One more
+//               workgroup of the backward pass; a launch of its own without one.
+// The rows are unrolled by 11, the period of the register rings (unrolled
+// whole, 42 rows were more code than the instruction cache holds).  The
+// forward is bound by its VALU work (237 instructions a row, of them 110
+// multiply-adds and 33 products; keeping the products in the row buffer
+// instead took 61 us for 54), the backward by memory (five planes read, one
+// written): 3 x 1600 x 1200 54 and 42 us, 71 and 49 before; 3 x 843 x 178,
+// whose 32-row strips left most SIMDs idle, 16 and 13 us, 35 and 26 before.
 #include <math.h>
 
 #include <string>
@@ -35,13 +41,10 @@ using namespace dgs;
 namespace {
 
 constexpr int kTaps = 11, kRad = 5;
-constexpr int kStrip = 64;                    // columns per wavefront (one per lane)
-constexpr int kWaves = 4;                     // strips side by side per workgroup
-constexpr int kThreads = 64 * kWaves;
-constexpr int kRowsOut = 32;                  // output rows per wavefront
-constexpr int kRowsIn = kRowsOut + 2 * kRad;  // input rows it reads
-constexpr int kAhead = 4;                     // input rows loaded ahead
+constexpr int kStrip = 64;                      // columns per wavefront (one per lane)
+constexpr int kAhead = 4;                       // input rows loaded ahead
 constexpr int kRowBuf = kStrip + 2 * kRad + 6;  // one row and its halo (+ padding)
+constexpr int kSimds = 1024;                    // of 256 CUs
 constexpr float kC1 = 0.01f * 0.01f, kC2 = 0.03f * 0.03f;
 
 struct Window {
@@ -52,12 +55,15 @@ struct LossArgs {
     const float* x;
     const float* y;
     int C, H, W;
-    float lam;
+    int rows;        // output rows of a strip: 11 k + 1
+    int nx, ny;      // strips along a row, along a column
     float dls;       // dL/dSSIM at every pixel: -lam / n
     float l1c;       // (1 - lam) / n
     float* coef;     // [3][C][H][W], null: loss only
-    double* part;    // [tiles][2]: sum of SSIM, sum of |x - y|
+    double* part;    // [strips][2]: sum of SSIM, sum of |x - y|
     float* grad;     // [C][H][W]
+    double n, lam;   // pixels, lambda
+    float* loss;
 };
 
 __device__ inline double wave_sum(double v) {
@@ -89,200 +95,215 @@ struct StripCols {
     }
 };
 
-// The part index of this wavefront's strip.
-__device__ __forceinline__ size_t strip_index() {
-    return (((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * kWaves + (threadIdx.x >> 6);
-}
-
-// The forward pass's state along one strip: rows in flight, the last 11
-// row sums and centre values, the running sums.
-struct FwdStrip {
-    const float* X;
-    const float* Y;
-    float* bx;
-    float* by;
-    StripCols cols;
-    int c, r0, gx, lane;
-    size_t plane;
-    float ax[kAhead], hx[kAhead], ay[kAhead], hy[kAhead];
-    float ring[kTaps][5];                // row sums of x, y, x^2, y^2, xy of the last 11 rows
-    float cxv[kRad + 1], cyv[kRad + 1];  // x, y at column c0 + lane of the last 6 rows
-    double ssum, l1sum;
+// The strip of a workgroup: neighbours share input rows and columns, and the
+// backward reads the coefficients that the forward wrote, so each XCD has one
+// contiguous range of them in both.
+struct Strip {
+    int c, c0, r0;
+    __device__ __forceinline__ Strip(const LossArgs& a, int t)
+        : c(t / (a.nx * a.ny)), c0(t % a.nx * kStrip), r0(t / a.nx % a.ny * a.rows) {}
 };
 
-// Input row I of the strip (image row r0 - 5 + I); from I = 10 on, also
-// output row r0 + I - 10 (centre row I - 5).  A template per row, so that
-// every ring index is a constant (the rows are unrolled by the recursion).
-template <int I>
-__device__ __forceinline__ void fwd_row(FwdStrip& st, const LossArgs& a, const Window& w) {
-    constexpr int sl = I % kAhead;
-    wave_sync();  // the previous row's reads are done
-    st.bx[st.lane] = st.ax[sl];
-    st.by[st.lane] = st.ay[sl];
-    if (st.cols.hb) {
-        st.bx[kStrip + st.lane] = st.hx[sl];
-        st.by[kStrip + st.lane] = st.hy[sl];
+// The strip sums, by one wavefront in a fixed order, then L.
+__device__ void loss_sum(const LossArgs& a, int strips, int lane) {
+    double s = 0.0, l = 0.0;
+    const double2* part = reinterpret_cast<const double2*>(a.part);
+#pragma unroll 8
+    for (int t = lane; t < strips; t += 64) {
+        const double2 p = part[t];
+        s += p.x;
+        l += p.y;
     }
-    wave_sync();
-    if constexpr (I + kAhead < kRowsIn) {
-        st.cols.load(st.X, a.H, a.W, st.r0 - kRad + I + kAhead, st.ax[sl], st.hx[sl]);
-        st.cols.load(st.Y, a.H, a.W, st.r0 - kRad + I + kAhead, st.ay[sl], st.hy[sl]);
-    }
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f, s4 = 0.0f;
+    s = wave_sum(s);
+    l = wave_sum(l);
+    if (lane == 0) *a.loss = (float)((1.0 - a.lam) * l / a.n + a.lam * (1.0 - s / a.n));
+}
+
+template <bool GRAD>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_ssim_fwd(LossArgs a, Window w) {
+    __shared__ float bx[kRowBuf], by[kRowBuf];
+    const int lane = threadIdx.x;
+    const int t = xcd_remap(blockIdx.x, gridDim.x);
+    const Strip st(a, t);
+    const size_t plane = (size_t)a.H * a.W, n = (size_t)a.C * plane;
+    const float* X = a.x + st.c * plane;
+    const float* Y = a.y + st.c * plane;
+    const StripCols cols(st.c0, lane);
+    const int gx = st.c0 + lane;
+    // indexed by input row modulo 11; of the loads kAhead rows are live, of the centres 6
+    float ax[kTaps], hx[kTaps], ay[kTaps], hy[kTaps], cx[kTaps], cy[kTaps];
+    float ring[kTaps][5];  // row sums of x, y, x^2, y^2, xy of the last 11 rows
+    double ssum = 0.0, l1sum = 0.0;
 #pragma unroll
-    for (int t = 0; t < kTaps; t++) {
-        const float xv = st.bx[st.lane + t], yv = st.by[st.lane + t], g = w.g[t];
-        s0 = fmaf(g, xv, s0);
-        s1 = fmaf(g, yv, s1);
-        s2 = fmaf(g, xv * xv, s2);
-        s3 = fmaf(g, yv * yv, s3);
-        s4 = fmaf(g, xv * yv, s4);
+    for (int i = 0; i < kAhead; i++) {
+        cols.load(X, a.H, a.W, st.r0 - kRad + i, ax[i], hx[i]);
+        cols.load(Y, a.H, a.W, st.r0 - kRad + i, ay[i], hy[i]);
     }
-    constexpr int rs = I % kTaps;
-    st.ring[rs][0] = s0;
-    st.ring[rs][1] = s1;
-    st.ring[rs][2] = s2;
-    st.ring[rs][3] = s3;
-    st.ring[rs][4] = s4;
-    st.cxv[I % (kRad + 1)] = st.bx[st.lane + kRad];
-    st.cyv[I % (kRad + 1)] = st.by[st.lane + kRad];
-    if constexpr (I >= 2 * kRad) {
-        const int gy = st.r0 + I - 2 * kRad;
-        if (gy < a.H && st.gx < a.W) {
+    const int rin = min(a.rows, a.H - st.r0) + 2 * kRad;  // input rows that count
+    for (int base = 0; base < rin; base += kTaps) {
+#pragma unroll
+        for (int j = 0; j < kTaps; j++) {
+            // input row base + j: image row r0 - 5 + base + j
+            const int jl = (j + kAhead) % kTaps, gl = st.r0 - kRad + base + j + kAhead;
+            wave_sync();  // the previous row's reads are done
+            bx[lane] = ax[j];
+            by[lane] = ay[j];
+            if (cols.hb) {
+                bx[kStrip + lane] = hx[j];
+                by[kStrip + lane] = hy[j];
+            }
+            wave_sync();
+            cols.load(X, a.H, a.W, gl, ax[jl], hx[jl]);
+            cols.load(Y, a.H, a.W, gl, ay[jl], hy[jl]);
+            float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f, s4 = 0.0f;
+#pragma unroll
+            for (int k = 0; k < kTaps; k++) {
+                const float xv = bx[lane + k], yv = by[lane + k], g = w.g[k];
+                s0 = fmaf(g, xv, s0);
+                s1 = fmaf(g, yv, s1);
+                s2 = fmaf(g, xv * xv, s2);
+                s3 = fmaf(g, yv * yv, s3);
+                s4 = fmaf(g, xv * yv, s4);
+            }
+            ring[j][0] = s0;
+            ring[j][1] = s1;
+            ring[j][2] = s2;
+            ring[j][3] = s3;
+            ring[j][4] = s4;
+            cx[j] = bx[lane + kRad];
+            cy[j] = by[lane + kRad];
+            const int i = base + j;
+            if (i < 2 * kRad || i >= rin) continue;
+            // output row r0 + i - 10, whose centre is input row i - 5
+            const int gy = st.r0 + i - 2 * kRad;
+            if (gx >= a.W) continue;
             float m[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int k = 0; k < kTaps; k++) {
                 const float g = w.g[k];
 #pragma unroll
-                for (int t = 0; t < 5; t++) m[t] = fmaf(g, st.ring[(I - 2 * kRad + k) % kTaps][t], m[t]);
+                for (int q = 0; q < 5; q++) m[q] = fmaf(g, ring[(j + 1 + k) % kTaps][q], m[q]);
             }
             const float mx = m[0], my = m[1];
             const float sxx = m[2] - mx * mx, syy = m[3] - my * my, sxy = m[4] - mx * my;
             const float a1 = 2.0f * mx * my + kC1, a2 = 2.0f * sxy + kC2;
             const float b1 = mx * mx + my * my + kC1, b2 = sxx + syy + kC2;
             const float sv = (a1 * a2) / (b1 * b2);
-            constexpr int cs = (I - kRad) % (kRad + 1);
-            st.ssum += (double)sv;
-            st.l1sum += (double)fabsf(st.cxv[cs] - st.cyv[cs]);
-            if (a.coef) {
+            const int jc = (j + kTaps - kRad) % kTaps;
+            ssum += (double)sv;
+            l1sum += (double)fabsf(cx[jc] - cy[jc]);
+            if (GRAD) {
                 // S = a1 a2 / (b1 b2): d/d mu_x through a1 (2 mu_y), a2 (-2 mu_y),
                 // b1 (2 mu_x), b2 (-2 mu_x); d/d E[x^2] through b2; d/d E[xy] through a2
-                const float ds = a.dls * sv;
-                const size_t p = st.c * st.plane + (size_t)gy * a.W + st.gx, n = (size_t)a.C * st.plane;
-                a.coef[p] = ds * (2.0f * my / a1 - 2.0f * my / a2 - 2.0f * mx / b1 + 2.0f * mx / b2);
-                a.coef[n + p] = -ds / b2;
-                a.coef[2 * n + p] = 2.0f * ds / a2;
+                // (with a2 from S cancelled against the division by a2, so that
+                // only b1, b2 >= c1, c2 are divided by)
+                const float i1 = 1.0f / b1, i2 = 1.0f / b2;
+                const float ds = a.dls * sv, q = 2.0f * a.dls * (i1 * i2);
+                const size_t p = st.c * plane + (size_t)gy * a.W + gx;
+                a.coef[p] = q * my * (a2 - a1) + 2.0f * mx * ds * (i2 - i1);
+                a.coef[n + p] = -ds * i2;
+                a.coef[2 * n + p] = q * a1;
             }
         }
     }
-    if constexpr (I + 1 < kRowsIn) fwd_row<I + 1>(st, a, w);
-}
-
-__global__ __launch_bounds__(kThreads) void k_ssim_fwd(LossArgs a, Window w) {
-    __shared__ float rb[kWaves][2][kRowBuf];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int c = blockIdx.z;
-    const int c0 = (blockIdx.x * kWaves + wv) * kStrip, r0 = blockIdx.y * kRowsOut;
-    const size_t plane = (size_t)a.H * a.W;
-    FwdStrip st{a.x + c * plane, a.y + c * plane, rb[wv][0], rb[wv][1], StripCols(c0, lane), c, r0, c0 + lane,
-                lane, plane};
-    st.ssum = 0.0;
-    st.l1sum = 0.0;
-    // input row i is image row r0 - 5 + i; rows i .. i + kAhead - 1 are in flight
-#pragma unroll
-    for (int i = 0; i < kAhead; i++) {
-        st.cols.load(st.X, a.H, a.W, r0 - kRad + i, st.ax[i], st.hx[i]);
-        st.cols.load(st.Y, a.H, a.W, r0 - kRad + i, st.ay[i], st.hy[i]);
-    }
-    fwd_row<0>(st, a, w);
-    const double ssum = wave_sum(st.ssum), l1sum = wave_sum(st.l1sum);
+    ssum = wave_sum(ssum);
+    l1sum = wave_sum(l1sum);
     if (lane == 0) {
-        const size_t t = strip_index();
-        a.part[2 * t] = ssum;
-        a.part[2 * t + 1] = l1sum;
+        a.part[2 * (size_t)t] = ssum;
+        a.part[2 * (size_t)t + 1] = l1sum;
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_ssim_bwd(LossArgs a, Window w) {
-    __shared__ float rb[kWaves][3][kRowBuf];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int c = blockIdx.z;
-    const int c0 = (blockIdx.x * kWaves + wv) * kStrip, r0 = blockIdx.y * kRowsOut;
+// Workgroup 0 sums the loss, the others take the strips.
+__global__ __launch_bounds__(64) void k_ssim_bwd(LossArgs a, Window w) {
+    __shared__ float rb[3][kRowBuf];
+    const int lane = threadIdx.x;
+    if (blockIdx.x == 0) {
+        loss_sum(a, (int)gridDim.x - 1, lane);
+        return;
+    }
+    // shifted by the block of the sum, so that a strip's XCD is the forward's
+    const int strips = (int)gridDim.x - 1, b = (int)blockIdx.x < strips ? (int)blockIdx.x : 0;
+    const Strip st(a, xcd_remap(b, strips));
     const size_t plane = (size_t)a.H * a.W, n = (size_t)a.C * plane;
-    const float* cf[3] = {a.coef + c * plane, a.coef + n + c * plane, a.coef + 2 * n + c * plane};
-    const StripCols cols(c0, lane);
-    float av[kAhead][3], hv[kAhead][3];
+    const float* X = a.x + st.c * plane;
+    const float* Y = a.y + st.c * plane;
+    const float* cf[3] = {a.coef + st.c * plane, a.coef + n + st.c * plane, a.coef + 2 * n + st.c * plane};
+    const StripCols cols(st.c0, lane);
+    const int gx = st.c0 + lane;
+    float av[kTaps][3], hv[kTaps][3];  // indexed by input row modulo 11; kAhead rows live
+    float xr[kTaps], yr[kTaps];        // x, y of the output row, by its last input row
+    float ring[kTaps][3];              // row sums of the three coefficient planes of the last 11 rows
 #pragma unroll
     for (int i = 0; i < kAhead; i++)
 #pragma unroll
-        for (int q = 0; q < 3; q++) cols.load(cf[q], a.H, a.W, r0 - kRad + i, av[i][q], hv[i][q]);
-    float ring[kTaps][3];  // row sums of the three coefficient planes of the last 11 rows
-    const int gx = c0 + lane;
+        for (int q = 0; q < 3; q++) cols.load(cf[q], a.H, a.W, st.r0 - kRad + i, av[i][q], hv[i][q]);
+    const int rin = min(a.rows, a.H - st.r0) + 2 * kRad;
+    for (int base = 0; base < rin; base += kTaps) {
 #pragma unroll
-    for (int i = 0; i < kRowsIn; i++) {
-        const int sl = i % kAhead;
-        wave_sync();
+        for (int j = 0; j < kTaps; j++) {
+            const int i = base + j, jl = (j + kAhead) % kTaps;
+            wave_sync();
 #pragma unroll
-        for (int q = 0; q < 3; q++) {
-            rb[wv][q][lane] = av[sl][q];
-            if (cols.hb) rb[wv][q][kStrip + lane] = hv[sl][q];
+            for (int q = 0; q < 3; q++) {
+                rb[q][lane] = av[j][q];
+                if (cols.hb) rb[q][kStrip + lane] = hv[j][q];
+            }
+            wave_sync();
+#pragma unroll
+            for (int q = 0; q < 3; q++)
+                cols.load(cf[q], a.H, a.W, st.r0 - kRad + i + kAhead, av[jl][q], hv[jl][q]);
+            {
+                const int gl = st.r0 + i + kAhead - 2 * kRad;
+                const bool in = gl >= st.r0 && gl < a.H && gx < a.W;
+                const size_t p = (size_t)(in ? gl : 0) * a.W + (in ? gx : 0);
+                xr[jl] = X[p];
+                yr[jl] = Y[p];
+            }
+            float s[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < kTaps; k++) {
+                const float g = w.g[k];
+#pragma unroll
+                for (int q = 0; q < 3; q++) s[q] = fmaf(g, rb[q][lane + k], s[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < 3; q++) ring[j][q] = s[q];
+            if (i < 2 * kRad || i >= rin || gx >= a.W) continue;
+            float m[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < kTaps; k++) {
+                const float g = w.g[k];
+#pragma unroll
+                for (int q = 0; q < 3; q++) m[q] = fmaf(g, ring[(j + 1 + k) % kTaps][q], m[q]);
+            }
+            const float xv = xr[j], yv = yr[j];
+            const float sg = (float)(xv > yv) - (float)(xv < yv);
+            a.grad[st.c * plane + (size_t)(st.r0 + i - 2 * kRad) * a.W + gx] =
+                fmaf(a.l1c, sg, fmaf(yv, m[2], fmaf(2.0f * xv, m[1], m[0])));
         }
-        wave_sync();
-        if (i + kAhead < kRowsIn) {
-#pragma unroll
-            for (int q = 0; q < 3; q++) cols.load(cf[q], a.H, a.W, r0 - kRad + i + kAhead, av[sl][q], hv[sl][q]);
-        }
-        float s[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int t = 0; t < kTaps; t++) {
-            const float g = w.g[t];
-#pragma unroll
-            for (int q = 0; q < 3; q++) s[q] = fmaf(g, rb[wv][q][lane + t], s[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < 3; q++) ring[i % kTaps][q] = s[q];
-        if (i < 2 * kRad) continue;
-        const int gy = r0 + i - 2 * kRad;
-        if (gy >= a.H || gx >= a.W) continue;
-        float b[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int k = 0; k < kTaps; k++) {
-            const float g = w.g[k];
-#pragma unroll
-            for (int q = 0; q < 3; q++) b[q] = fmaf(g, ring[(i - 2 * kRad + k) % kTaps][q], b[q]);
-        }
-        const size_t p = c * plane + (size_t)gy * a.W + gx;
-        const float xv = a.x[p], yv = a.y[p];
-        const float sg = (float)(xv > yv) - (float)(xv < yv);
-        a.grad[p] = fmaf(a.l1c, sg, fmaf(yv, b[2], fmaf(2.0f * xv, b[1], b[0])));
     }
 }
 
-// One workgroup: the strip sums in a fixed order, then L.
-__global__ __launch_bounds__(kThreads) void k_loss_sum(const double* part, size_t tiles, double n, double lam,
-                                                       float* loss) {
-    __shared__ double red[2][kThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, grp = tid >> 6;
-    double s = 0.0, l = 0.0;
-    for (size_t t = tid; t < tiles; t += kThreads) {
-        s += part[2 * t];
-        l += part[2 * t + 1];
-    }
-    s = wave_sum(s);
-    l = wave_sum(l);
-    if (lane == 0) {
-        red[0][grp] = s;
-        red[1][grp] = l;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        double ss = 0.0, ll = 0.0;
-        for (int i = 0; i < kThreads / 64; i++) {
-            ss += red[0][i];
-            ll += red[1][i];
+__global__ __launch_bounds__(64) void k_loss_sum(LossArgs a, int strips) { loss_sum(a, strips, (int)threadIdx.x); }
+
+// Output rows of a strip, 11 k + 1 (with the 10 rows of its window a whole
+// number of ring periods): the least (strips per SIMD + 2) x (rows + 10).  A
+// row takes a wavefront about as long alone as two more strips on its SIMD
+// add: 3 x 1600 x 1200 with its gradient takes 80, 87, 89 and 119 us in 23,
+// 34, 45 and 67 rows, 4, 3, 2 and 2 strips per SIMD.
+int strip_rows(int64_t columns, int H) {
+    int best = 12;
+    double least = INFINITY;
+    for (int rows = 12; rows <= 67; rows += kTaps) {
+        const int64_t strips = columns * ((H + rows - 1) / rows), per = (strips + kSimds - 1) / kSimds;
+        const double cost = (double)(per + 2) * (rows + 2 * kRad);
+        if (cost < least) {
+            least = cost;
+            best = rows;
         }
-        *loss = (float)((1.0 - lam) * ll / n + lam * (1.0 - ss / n));
     }
+    return best;
 }
 
 // The 11 window weights: exp(-t^2 / (2 sigma^2)) for t = -5..5, divided by
@@ -334,32 +355,39 @@ dgs_status dgs_loss_l1_ssim(dgs_ctx c, const float* image, const float* target, 
     }
     hipSetDevice(c->device);
     const int64_t n = (int64_t)channels * height * width;
-    const dim3 grid((unsigned)((width + kWaves * kStrip - 1) / (kWaves * kStrip)),
-                    (unsigned)((height + kRowsOut - 1) / kRowsOut), (unsigned)channels);
-    const int64_t tiles = (int64_t)grid.x * grid.y * grid.z * kWaves;  // strips
-    hipError_t e = ensure_buf(c->loss_part, c->cap_loss_part, 2 * tiles, c->stream);
+    LossArgs a;
+    a.nx = (width + kStrip - 1) / kStrip;
+    a.rows = strip_rows((int64_t)a.nx * channels, height);
+    a.ny = (height + a.rows - 1) / a.rows;
+    const int64_t strips = (int64_t)a.nx * a.ny * channels;
+    hipError_t e = ensure_buf(c->loss_part, c->cap_loss_part, 2 * strips, c->stream);
     if (e == hipSuccess && grad_image) e = ensure_buf(c->loss_coef, c->cap_loss_coef, 3 * n, c->stream);
     if (e != hipSuccess) {
         c->err = std::string("loss: hipMalloc failed: ") + hipGetErrorString(e);
         return DGS_ERR_OOM;
     }
-    LossArgs a;
     a.x = image;
     a.y = target;
     a.C = channels;
     a.H = height;
     a.W = width;
-    a.lam = lambda;
     a.dls = (float)(-(double)lambda / (double)n);
     a.l1c = (float)((1.0 - (double)lambda) / (double)n);
-    a.coef = grad_image ? c->loss_coef : nullptr;
+    a.coef = c->loss_coef;
     a.part = c->loss_part;
     a.grad = grad_image;
+    a.n = (double)n;
+    a.lam = (double)lambda;
+    a.loss = loss;
     const Window w = make_window();
-    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(kThreads), 0, c->stream, a, w);
-    hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(kThreads), 0, c->stream, (const double*)c->loss_part,
-                       (size_t)tiles, (double)n, (double)lambda, loss);
-    if (grad_image) hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(kThreads), 0, c->stream, a, w);
+    const dim3 grid((unsigned)strips), block(64);
+    if (grad_image) {
+        hipLaunchKernelGGL(k_ssim_fwd<true>, grid, block, 0, c->stream, a, w);
+        hipLaunchKernelGGL(k_ssim_bwd, dim3((unsigned)strips + 1), block, 0, c->stream, a, w);
+    } else {
+        hipLaunchKernelGGL(k_ssim_fwd<false>, grid, block, 0, c->stream, a, w);
+        hipLaunchKernelGGL(k_loss_sum, dim3(1), block, 0, c->stream, a, (int)strips);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) {
         c->err = std::string("loss: kernel launch failed: ") + hipGetErrorString(e);
