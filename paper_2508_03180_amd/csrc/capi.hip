@@ -418,11 +418,11 @@ dgs_status dgs_create(int device, void* hip_stream, dgs_ctx* out) {
         hipMalloc((void**)&c->counters, 5 * sizeof(unsigned long long)) != hipSuccess ||
         hipMalloc((void**)&c->frame, sizeof(FrameK)) != hipSuccess ||
         hipMalloc((void**)&c->queue, kQueueWords * sizeof(uint32_t)) != hipSuccess ||
-        hipHostMalloc((void**)&c->load_host, 2 * sizeof(uint64_t), hipHostMallocMapped) != hipSuccess) {
+        hipHostMalloc((void**)&c->load_host, 3 * sizeof(uint64_t), hipHostMallocMapped) != hipSuccess) {
         dgs_destroy(c);
         return DGS_ERR_OOM;
     }
-    c->load_host[0] = c->load_host[1] = 0;
+    c->load_host[0] = c->load_host[1] = c->load_host[2] = 0;
     if (hipHostGetDevicePointer((void**)&c->load_dev, c->load_host, 0) != hipSuccess) {
         dgs_destroy(c);
         return DGS_ERR_DEVICE;
@@ -950,10 +950,13 @@ dgs_status dgs_frame_stats(dgs_ctx c, dgs_frame f, dgs_stats* out) {
 dgs_status dgs_sync(dgs_ctx c) {
     if (!c) return DGS_ERR_INVALID_ARG;
     hipSetDevice(c->device);
+    uint32_t* report = reinterpret_cast<uint32_t*>(c->load_host + 2);
+    __atomic_store_n(report, kNoReport, __ATOMIC_RELAXED);
+    launch_report(c->stream, c->dev_err, nullptr, reinterpret_cast<uint32_t*>(c->load_dev + 2));
     if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(c, DGS_ERR_DEVICE, "stream synchronize failed");
-    int e = 0;
-    if (hipMemcpy(&e, c->dev_err, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
-        return fail(c, DGS_ERR_DEVICE, "error flag readback failed");
+    const uint32_t bits = __atomic_load_n(report, __ATOMIC_RELAXED);
+    if (bits == kNoReport) return fail(c, DGS_ERR_DEVICE, "error flag readback failed");
+    const int e = (int)bits;
     if (e) {
         // cleared in stream order, before the next frame can set a flag
         launch_fill_u32(c->stream, reinterpret_cast<uint32_t*>(c->dev_err), 0u, 1);

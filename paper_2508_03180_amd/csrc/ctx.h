@@ -61,6 +61,7 @@ struct dgs_ctx_s {
     // list order: [0] tiles << 32 | keys (0: none yet), as the frame's tile
     // ranges are built; [1] its primitives << 32 | its keys in runs of more
     // than 4096 entries, as its work queue is built.
+    // [2] the device error bits that dgs_sync reads.
     uint64_t* load_host = nullptr;
     uint64_t* load_dev = nullptr;
     hipStream_t aux = nullptr;

@@ -44,6 +44,12 @@ void launch_exclusive_scan(hipStream_t st, const uint32_t* in, uint32_t* out, in
                            const uint32_t* idx = nullptr);
 
 void launch_fill_u32(hipStream_t st, uint32_t* p, uint32_t v, size_t n);
+// dst[0] = *err, dst[1] = *keys (nullable) for the host: dst is the device
+// address of pinned memory, read after the stream (or an event behind this)
+// has been waited for.  The host stores kNoReport into dst[0] beforehand: a
+// report that did not run leaves it there.
+constexpr uint32_t kNoReport = 0xffffffffu;
+void launch_report(hipStream_t st, const int* err, const uint32_t* keys, uint32_t* dst);
 
 // Zeroes up to 8 u32 buffers in one launch (graph-safe: no memset
 // nodes) and increments *bump (the look-back frame counter) when set.

@@ -86,6 +86,7 @@ class DeviceExecutor final : public Executor {
         hipEvent_t done = nullptr;
         FrameK* hframe = nullptr;   // pinned host copy source of the frame record
         uint32_t* hinfo = nullptr;  // pinned: [0] device error bits, [1] key count
+        uint32_t* dinfo = nullptr;  // its device address
         struct Graph {
             uint64_t generation;
             hipGraphExec_t exec;
@@ -110,7 +111,8 @@ public:
             if (hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking) != hipSuccess ||
                 hipEventCreateWithFlags(&s.done, hipEventDisableTiming) != hipSuccess ||
                 hipHostMalloc((void**)&s.hframe, sizeof(FrameK), hipHostMallocDefault) != hipSuccess ||
-                hipHostMalloc((void**)&s.hinfo, 2 * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
+                hipHostMalloc((void**)&s.hinfo, 2 * sizeof(uint32_t), hipHostMallocMapped) != hipSuccess ||
+                hipHostGetDevicePointer((void**)&s.dinfo, s.hinfo, 0) != hipSuccess) {
                 err = "stream, event or pinned buffer creation failed";
                 return DGS_ERR_DEVICE;
             }
@@ -204,10 +206,9 @@ public:
                 return st;
             }
         }
-        if (hipMemcpyAsync(s.hinfo, s.ctx->dev_err, sizeof(uint32_t), hipMemcpyDeviceToHost, s.stream) != hipSuccess ||
-            hipMemcpyAsync(s.hinfo + 1, s.ctx->misc, sizeof(uint32_t), hipMemcpyDeviceToHost, s.stream) !=
-                hipSuccess ||
-            hipEventRecord(s.done, s.stream) != hipSuccess) {
+        __atomic_store_n(s.hinfo, kNoReport, __ATOMIC_RELAXED);
+        launch_report(s.stream, s.ctx->dev_err, s.ctx->misc, s.dinfo);
+        if (hipEventRecord(s.done, s.stream) != hipSuccess) {
             err = "completion record failed";
             return DGS_ERR_DEVICE;
         }
@@ -225,8 +226,12 @@ public:
             err = "frame failed on the device";
             return DGS_ERR_DEVICE;
         }
-        const uint32_t bits = s.hinfo[0];
-        *keys = s.hinfo[1];
+        const uint32_t bits = __atomic_load_n(s.hinfo, __ATOMIC_RELAXED);
+        *keys = __atomic_load_n(s.hinfo + 1, __ATOMIC_RELAXED);
+        if (bits == kNoReport) {
+            err = "frame failed on the device";
+            return DGS_ERR_DEVICE;
+        }
         if (bits) {
             hipMemsetAsync(s.ctx->dev_err, 0, sizeof(int), s.stream);
             hipStreamSynchronize(s.stream);
