@@ -156,7 +156,7 @@ __device__ __forceinline__ uint32_t sat_add(uint32_t a, uint32_t b) {
 }
 
 // status word: epoch << 34 | flag << 32 | value; flag 1 = workgroup total,
-// 2 = inclusive prefix (as in the exclusive scan of scan.hip).
+// 2 = inclusive prefix.
 __global__ __launch_bounds__(kBinScanTiles * kBinScanSplit) void k_bin_scan(
     uint32_t* __restrict__ counts, int chunks, int TX, int tiles, int local, uint32_t cap, uint32_t* __restrict__ ranges,
     uint32_t* __restrict__ total, uint64_t* status, const uint32_t* ep, uint32_t* ticket, int* err, uint64_t* load) {

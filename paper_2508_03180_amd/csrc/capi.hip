@@ -587,19 +587,23 @@ dgs_status dgs_read_decoded(dgs_ctx c, float* means, float* scales, float* rots,
 
 // Per-cell tile lists (Duplex, LC-WSR) are put in depth order per tile
 // (launch_bin_tiles, launch_tile_depth_sort) when the context's last cell
-// frame had at most 1024 keys per tile on average, and at most an eighth of
-// its keys in runs of more than 4096 entries (which the per-tile sort handles
-// by chunked merges in global memory over several rounds); before any cell
-// frame, when the key buffer holds at most 256 keys per tile.  Measured, us
-// per frame per tile / global: street views of the 6M-Gaussian scene at 4K
-// (23 to 40 keys per cell, none in long runs) 996 / 1990 and 1463 / 2420, at
-// 1080p 695 / 962, at 720p (5 to 9% of the keys in long runs) 580 / 683 and
-// 435 / 545; the clustered scene's 1M Gaussians as cells of 10, 5, 2 and 1 (0,
-// 0, 4 and 16%) 321 / 404, 404 / 474, 656 / 681 and 1129 / 931; 20,000 ragged
-// cells at 1283 x 717 (13 keys per cell) 230 / 323.  Per-Gaussian lists always
-// take the depth sort of the primitives (1M Gaussians at 1080p, 8%: 605 / 576).
+// frame had at most 1024 keys per tile on average, at most an eighth of its
+// keys in runs of more than 4096 entries (which the per-tile sort handles by
+// chunked merges in global memory over several rounds) and at most 8 M keys
+// (beyond, two radix passes cost a key less than its tile's sorting network,
+// whatever the launches); before any cell frame, when the key buffer holds at
+// most 256 keys per tile.  Measured, us per frame per tile / global: street
+// views of the 6M-Gaussian scene at 4K (6, 14 and 24 M keys, none in long
+// runs) 962 / 1076, 970 / 950 and 1431 / 1364, at 1080p (2 to 7 M) 628 / 747,
+// 479 / 526, 685 / 703 and 705 / 703, at 720p (5 to 9% of the keys in long
+// runs) 563 / 597, 423 / 460 and 590 / 600; the clustered scene's 1M Gaussians
+// as cells of 10, 5, 2 and 1 (0, 0, 4 and 16%) 308 / 411, 390 / 458, 649 / 589
+// and 1092 / 846; 20,000 ragged cells at 1283 x 717 (13 keys per cell) 219 /
+// 304.  Per-Gaussian lists always take the depth sort of the primitives (1M
+// Gaussians at 1080p, 8%: 580 / 466).
 constexpr int64_t kPerTileOrderMaxMean = 1024;      // keys per tile
 constexpr uint64_t kPerTileOrderLongShare = 8;      // at most 1 / this of the keys in long runs
+constexpr uint64_t kPerTileOrderMaxKeys = 8u << 20;
 constexpr int64_t kPerTileOrderCapacity = 256;      // keys per tile, before any cell frame
 
 static bool per_tile_order(dgs_ctx c, int64_t tiles, bool cells) {
@@ -609,7 +613,8 @@ static bool per_tile_order(dgs_ctx c, int64_t tiles, bool cells) {
     const uint64_t load = __atomic_load_n(c->load_host, __ATOMIC_RELAXED);
     const uint64_t lng = __atomic_load_n(c->load_host + 1, __ATOMIC_RELAXED);
     const uint64_t lt = load >> 32, lk = load & 0xffffffffull, ll = lng & 0xffffffffull;
-    if (lt) return lk <= (uint64_t)kPerTileOrderMaxMean * lt && kPerTileOrderLongShare * ll <= lk;
+    if (lt)
+        return lk <= (uint64_t)kPerTileOrderMaxMean * lt && kPerTileOrderLongShare * ll <= lk && lk <= kPerTileOrderMaxKeys;
     return c->cap_keys <= kPerTileOrderCapacity * tiles;
 }
 
@@ -752,12 +757,10 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
         launch_prim_keys(q, P, c->p_ntiles, c->p_depth, c->pk0, c->pv0);
         const bool pin1 = launch_radix_sort32(q, c->pk0, c->pv0, c->pk1, c->pv1, (uint32_t)P,
                                               SortScratch{(uint32_t*)c->psort_status, c->hist});
-        const uint32_t* order = pin1 ? c->pv1 : c->pv0;
+        const DepthOrder order = pin1 ? DepthOrder{c->pk1, c->pv1, c->pk0, c->pv0} : DepthOrder{c->pk0, c->pv0, c->pk1, c->pv1};
         sm.mark(3);
-        launch_exclusive_scan(q, c->p_ntiles, c->p_offsets, P, c->misc + 0, c->scan_status, c->misc + 13, c->misc + 1,
-                              c->dev_err, order);
-        launch_emit_keys(q, P, order, c->p_ntiles, c->p_offsets, prect, c->p_depth, k.TX, cap, c->keys0, c->vals0,
-                         c->dev_err);
+        launch_emit_keys(q, P, order, prect, c->p_offsets, (uint32_t*)c->scan_status, k.TX, cap, c->keys0, c->vals0,
+                         c->misc + 0, c->dev_err);
         sm.mark(4);
         // stable sort on the tile bits
         in1 = launch_radix_sort(q, c->keys0, c->vals0, c->keys1, c->vals1, c->misc + 0, cap, tbits,

@@ -22,7 +22,7 @@ constexpr int kModeLcwsr = 2;
 constexpr int kErrInvalid = 1;  // malformed cell_offsets
 constexpr int kErrCapacity = 3;
 constexpr int kErrTimeout = 6;
-constexpr int kErrWaitScan = 8;  // the exclusive scan's look-back
+constexpr int kErrWaitScan = 8;  // the tile lists' scan's look-back
 
 // Per-frame camera constants, passed by value to kernels.
 struct CamK {

@@ -623,7 +623,7 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t* __restrict_
                                                      uint32_t* __restrict__ order, uint32_t* __restrict__ queue,
                                                      uint64_t* long_stat, uint32_t prims) {
     __shared__ uint32_t s_cnt[kOrderClasses];
-    __shared__ uint32_t s_part[1024];
+    __shared__ uint32_t s_part[16];
     build_work_queue<1024>(ranges, ntiles, split_rule(split_len, *total), order, queue, s_cnt, s_part, (int)threadIdx.x, long_stat, prims);
 }
 

@@ -34,15 +34,6 @@ void launch_gauss_project(hipStream_t st, int M, int K, const float* means, cons
                           const uint32_t* cell_ntiles, GRec* recs, uint64_t* grect, uint32_t* gdepth,
                           uint32_t* gntiles, bool overlapped = false);
 
-// Exclusive scan of n u32 values (in[i], or in[idx[i]] when idx is set);
-// *total receives the sum.  status needs scan_status_words(n) 64-bit words;
-// *ticket must be zero; *epoch is the device frame counter (look-back tag
-// j = 0).
-size_t scan_status_words(int64_t n);
-void launch_exclusive_scan(hipStream_t st, const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total,
-                           uint64_t* status, const uint32_t* epoch, uint32_t* ticket, int* err,
-                           const uint32_t* idx = nullptr);
-
 void launch_fill_u32(hipStream_t st, uint32_t* p, uint32_t v, size_t n);
 // dst[0] = *err, dst[1] = *keys (nullable) for the host: dst is the device
 // address of pinned memory, read after the stream (or an event behind this)
@@ -72,13 +63,22 @@ void launch_clear(hipStream_t st, const ClearList& l, const FrameK* f = nullptr,
 void launch_prim_keys(hipStream_t st, int P, const uint32_t* ntiles, const uint32_t* depth, uint32_t* keys,
                       uint32_t* vals);
 
+// The primitives in depth order: their sorted depth keys (launch_prim_keys)
+// and ids; rx, ry (P words each) receive their rectangles' words.
+struct DepthOrder {
+    const uint32_t* depth;
+    const uint32_t* id;
+    uint32_t* rx;
+    uint32_t* ry;
+};
 // One key per (primitive, touched tile), the primitives taken in depth
-// order (order[i], i < P): key = tile << 32 | depth bits, value = primitive
-// id, written at offsets[i] in row-major tile order.  A stable sort of these
-// keys on the tile bits alone then yields the (tile, depth, id) order.
-void launch_emit_keys(hipStream_t st, int P, const uint32_t* order, const uint32_t* ntiles,
-                      const uint32_t* offsets, const uint64_t* prect, const uint32_t* depth, int TX, uint32_t cap,
-                      uint64_t* keys, uint32_t* vals, int* err);
+// order: key = tile << 32 | depth bits, value = primitive id, in row-major
+// tile order; *total receives their number.  A stable sort of these keys on
+// the tile bits alone then yields the (tile, depth, id) order.  offsets (P
+// words) and sums (scan_status_words(P) 64-bit words) are scratch.
+size_t scan_status_words(int64_t n);
+void launch_emit_keys(hipStream_t st, int P, const DepthOrder& order, const uint64_t* prect, uint32_t* offsets,
+                      uint32_t* sums, int TX, uint32_t cap, uint64_t* keys, uint32_t* vals, uint32_t* total, int* err);
 
 // Tile lists by counting, for the per-tile order: one entry (depth bits <<
 // 32 | id) per (primitive, touched tile) in its tile's run, in no particular

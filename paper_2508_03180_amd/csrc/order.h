@@ -76,7 +76,7 @@ __device__ __forceinline__ void tile_items(uint32_t len, SplitRule r, uint32_t& 
 }
 
 // s_cnt [kOrderClasses]: counts, then the first slot of each class;
-// s_part [NT]: the threads' partial sums (LDS of the calling workgroup).
+// s_part [NT / 64]: the wavefronts' sums (LDS of the calling workgroup).
 template <int NT>
 __device__ __forceinline__ void build_work_queue(const uint32_t* __restrict__ ranges, int ntiles, SplitRule rule,
                                         uint32_t* __restrict__ order, uint32_t* __restrict__ queue,
@@ -115,18 +115,25 @@ __device__ __forceinline__ void build_work_queue(const uint32_t* __restrict__ ra
         loc[j] = run;
         run += s_cnt[kOrderClasses - 1 - (kPer * tid + j)];
     }
-    s_part[tid] = run;
-    __syncthreads();
-    for (int o = 1; o < NT; o <<= 1) {  // inclusive scan of the per-thread totals
-        const uint32_t x = tid >= o ? s_part[tid - o] : 0u;
-        __syncthreads();
-        s_part[tid] += x;
-        __syncthreads();
+    // scan of the per-thread totals: within the wavefronts, then over them
+    uint32_t incl = run;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_up(incl, o, 64);
+        if ((tid & 63) >= o) incl += x;
     }
-    const uint32_t before = s_part[tid] - run;
+    if ((tid & 63) == 63) s_part[tid >> 6] = incl;
+    __syncthreads();
+    uint32_t before = incl - run, items = 0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; w++) {
+        const uint32_t x = s_part[w];
+        if (w < tid >> 6) before += x;
+        items += x;
+    }
 #pragma unroll
     for (int j = 0; j < kPer; j++) s_cnt[kOrderClasses - 1 - (kPer * tid + j)] = before + loc[j];
-    if (tid == NT - 1) queue[1] = s_part[NT - 1];
+    if (tid == 0) queue[1] = items;
     if (tid < kQueues) *reinterpret_cast<uint64_t*>(queue + kQueueStride * (1 + tid)) = 0;
     __syncthreads();
     for (int t0 = tid; t0 < ntiles; t0 += kAhead * NT) {

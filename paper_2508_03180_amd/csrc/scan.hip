@@ -1,5 +1,5 @@
-// Single-pass exclusive prefix sum with decoupled look-back, plus the key
-// emission and tile-range kernels of cell rasterization (Sec. IV-B).  The
+// The key offsets, key emission and tile-range kernels of cell rasterization
+// (Sec. IV-B), and small fills and readbacks.  The
 // primitives are first sorted by depth (ties by id); the offsets of their
 // keys come from a scan over that order, so the emitted sequence is already
 // in (depth, id) order within every tile and a stable sort on the tile bits
@@ -11,127 +11,18 @@
 
 namespace dgs {
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 8;
-constexpr int kScanPart = kScanThreads * kScanItems;
-constexpr int kOwnTiles = 32;
-
-constexpr int kSpinLimit = 1 << 22;
-
-// status word: epoch << 34 | flag << 32 | value; flag 1 = partition total,
-// 2 = inclusive prefix.  Words from an older epoch read as unpublished.
-__device__ inline uint64_t ld_status(const uint64_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline void st_status(uint64_t* p, uint64_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// Primitives per workgroup of k_prim_offsets.
+constexpr int kOffsetBlock = 1024;
 
 // Inclusive scan across the 64 lanes of a wavefront.
 __device__ inline uint32_t wave_incl_scan(uint32_t v) {
-    int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-        uint32_t u = __shfl_up(v, d, 64);
+        const uint32_t u = __shfl_up(v, d, 64);
         if (lane >= d) v += u;
     }
     return v;
-}
-
-__device__ inline uint32_t wave_sum_u32(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// Persistent blocks take partitions from a ticket counter in launch order, so
-// a partition only ever waits for partitions that are already running.
-__global__ __launch_bounds__(kScanThreads) void k_scan_excl(const uint32_t* __restrict__ in,
-                                                             uint32_t* __restrict__ out, int64_t n,
-                                                             uint32_t* __restrict__ total, uint64_t* status,
-                                                             const uint32_t* ep, uint32_t* ticket, int* err,
-                                                             const uint32_t* __restrict__ idx) {
-    __shared__ uint32_t s_part, s_wsum[kScanThreads / 64], s_excl;
-    const uint32_t epoch = epoch_tag(*ep, 0);
-    const int nparts = (int)((n + kScanPart - 1) / kScanPart);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (;;) {
-        if (tid == 0) s_part = atomicAdd(ticket, 1u);
-        __syncthreads();
-        const int part = (int)__builtin_amdgcn_readfirstlane(s_part);  // uniform: scalar loop control
-        if (part >= nparts) break;
-        const int64_t base = (int64_t)part * kScanPart + (int64_t)tid * kScanItems;
-        uint32_t x[kScanItems], sum = 0;
-#pragma unroll
-        for (int i = 0; i < kScanItems; i++) {
-            uint32_t j = (uint32_t)(base + i);
-            if (idx && base + i < n) j = idx[base + i];  // a permutation of [0, n)
-            x[i] = (base + i < n && j < (uint64_t)n) ? in[j] : 0u;
-            sum += x[i];
-        }
-        uint32_t incl = wave_incl_scan(sum);
-        if (lane == 63) s_wsum[wave] = incl;
-        __syncthreads();
-        uint32_t wprefix = 0, btotal = 0;
-        for (int w = 0; w < kScanThreads / 64; w++) {
-            uint32_t s = s_wsum[w];
-            if (w < wave) wprefix += s;
-            btotal += s;
-        }
-        if (wave == 0) {
-            // decoupled look-back by the whole wavefront: lane l reads the
-            // status of partition j - l, so one round trip covers 64
-            // predecessors; it stops at the nearest inclusive prefix
-            const uint64_t tag = (uint64_t)epoch << 34;
-            uint32_t excl = 0;
-            if (part == 0) {
-                if (lane == 0) st_status(&status[0], tag | (2ull << 32) | btotal);
-            } else {
-                if (lane == 0) st_status(&status[part], tag | (1ull << 32) | btotal);
-                int j = part - 1, spins = 0;
-                for (;;) {
-                    const int idx = j - lane;
-                    uint32_t flag = 2, val = 0;  // before partition 0: an inclusive prefix of 0
-                    if (idx >= 0) {
-                        const uint64_t st = ld_status(&status[idx]);
-                        flag = (uint32_t)(st >> 34) == epoch ? (uint32_t)(st >> 32) & 3u : 0u;
-                        val = (uint32_t)st;
-                    }
-                    const uint64_t notready = __ballot(flag == 0), inclusive = __ballot(flag == 2);
-                    const int fn = notready ? __builtin_ctzll(notready) : 64;
-                    const int li = inclusive ? __builtin_ctzll(inclusive) : 64;
-                    if (li < fn) {  // every partition down to the nearest inclusive prefix is published
-                        excl += wave_sum_u32(lane <= li ? val : 0u);
-                        break;
-                    }
-                    if (fn > 0) {  // totals of the published run [0, fn): take them and move on
-                        excl += wave_sum_u32(lane < fn ? val : 0u);
-                        j -= fn;
-                        continue;
-                    }
-                    if (++spins > kSpinLimit) {
-                        if (lane == 0) atomicOr(err, (1 << kErrTimeout) | (1 << kErrWaitScan));
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                }
-                if (lane == 0) st_status(&status[part], tag | (2ull << 32) | (excl + btotal));
-            }
-            if (lane == 0) {
-                s_excl = excl;
-                if (part == nparts - 1) *total = excl + btotal;
-            }
-        }
-        __syncthreads();
-        uint32_t run = s_excl + wprefix + incl - sum;
-#pragma unroll
-        for (int i = 0; i < kScanItems; i++) {
-            if (base + i < n) out[base + i] = run;
-            run += x[i];
-        }
-        if (gridDim.x >= (unsigned)nparts) break;  // the other partitions went to other workgroups
-        __syncthreads();  // s_part / s_wsum are reused by the next partition
-    }
 }
 
 __global__ void k_fill_u32(uint32_t* p, uint32_t v, size_t n) {
@@ -157,20 +48,7 @@ void launch_report(hipStream_t st, const int* err, const uint32_t* keys, uint32_
     hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, st, err, keys, dst);
 }
 
-size_t scan_status_words(int64_t n) { return (size_t)((n + kScanPart - 1) / kScanPart) + 1; }
-
-void launch_exclusive_scan(hipStream_t st, const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total,
-                           uint64_t* status, const uint32_t* epoch, uint32_t* ticket, int* err,
-                           const uint32_t* idx) {
-    if (n <= 0) {
-        launch_fill_u32(st, total, 0u, 1);
-        return;
-    }
-    const size_t nparts = (size_t)((n + kScanPart - 1) / kScanPart);
-    const unsigned grid = (unsigned)(nparts < 1024 ? nparts : 1024);
-    hipLaunchKernelGGL(k_scan_excl, dim3(grid), dim3(kScanThreads), 0, st, in, out, n, total, status,
-                       epoch, ticket, err, idx);
-}
+size_t scan_status_words(int64_t n) { return (size_t)((n + 2 * kOffsetBlock - 1) / (2 * kOffsetBlock)) + 1; }
 
 __global__ void k_clear(ClearList l, FrameK f, FrameK* fdst) {
     const size_t gid = blockIdx.x * (size_t)blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
@@ -224,65 +102,215 @@ void launch_prim_keys(hipStream_t st, int P, const uint32_t* ntiles, const uint3
     hipLaunchKernelGGL(k_prim_keys, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, P, ntiles, depth, keys, vals);
 }
 
-// Key emission in depth order.  A lane writes the keys of its own primitive
-// up to kOwnTiles; those of a larger one are dealt over the wavefront (one
-// lane writing the up to 32,400 keys of a screen-filling cell held a 4K frame
-// for 2.7 ms).
-__global__ __launch_bounds__(256) void k_emit_keys(int P, const uint32_t* __restrict__ order,
-                                                   const uint32_t* __restrict__ ntiles,
-                                                   const uint32_t* __restrict__ offsets,
-                                                   const uint64_t* __restrict__ prect,
-                                                   const uint32_t* __restrict__ depth, int TX, uint32_t cap,
-                                                   uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                   int* err) {
-    const int lane = threadIdx.x & 63, i0 = blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t p = (uint32_t)P;
-    if (i0 < P) p = order ? order[i0] : (uint32_t)i0;  // null order: id order
-    // a permutation of [0, P) unless a scan wait timed out
-    uint32_t nt = 0, off = 0, d = 0, t00 = 0, w = 0;
-    if (p < (uint32_t)P) nt = ntiles[p];
-    if (nt) {
-        off = offsets[i0];
-        if ((uint64_t)off + nt > cap) atomicOr(err, 1 << kErrCapacity);
-        const uint64_t r = prect[p];
-        d = depth[p];
-        const int tx0 = rect_x0(r) / kTile, ty0 = rect_y0(r) / kTile;
-        w = (uint32_t)(rect_x1(r) / kTile - tx0 + 1);
-        t00 = (uint32_t)(ty0 * TX + tx0);
+// Offsets of the primitives' keys in depth order, first within blocks of
+// kOffsetBlock primitives with the blocks' sums, then (k_block_offsets) of the
+// blocks.  One scan of the whole order whose partitions waited for each other
+// took 22 us for 1 M primitives, mostly for the wait; these take 17 (with the rectangles) and 5.
+// The rectangles, which the tile counts come from, are also left in depth
+// order: a gather in that order moves a line for each of its words, so there is
+// this one and the emission reads in sequence.
+__global__ __launch_bounds__(256) void k_prim_offsets(int P, DepthOrder o, const uint64_t* __restrict__ prect,
+                                                      uint32_t* __restrict__ offsets, uint32_t* __restrict__ sums) {
+    constexpr int kItems = kOffsetBlock / 256;
+    __shared__ uint32_t s_wsum[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i0 = blockIdx.x * kOffsetBlock + threadIdx.x * kItems;
+    uint32_t p[kItems], x[kItems], sum = 0;
+    uint64_t r[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        // all ones: touches no tile (launch_prim_keys)
+        const bool in = i0 + i < P && o.depth[i0 + i] != 0xffffffffu;
+        p[i] = in ? o.id[i0 + i] : (uint32_t)P;
     }
-    if (nt <= (uint32_t)kOwnTiles)
-        for (uint32_t i = off, t0 = t00, done = 0; done < nt && i < cap; done += w, t0 += (uint32_t)TX) {
-            // one row of tiles: consecutive tile ids t0 .. t0 + kept - 1
-            const uint32_t kept = cap - i < w ? cap - i : w;
-            for (uint32_t j = 0; j < kept; j++) {
-                keys[i + j] = ((uint64_t)(t0 + j) << 32) | d;
-                vals[i + j] = p;
-            }
-            i += kept;
+#pragma unroll
+    for (int i = 0; i < kItems; i++) r[i] = p[i] < (uint32_t)P ? prect[p[i]] : 0u;
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const int w = rect_x1(r[i]) / kTile - rect_x0(r[i]) / kTile + 1;
+        const int h = rect_y1(r[i]) / kTile - rect_y0(r[i]) / kTile + 1;
+        x[i] = p[i] < (uint32_t)P ? (uint32_t)(w * h) : 0u;
+        sum += x[i];
+        if (i0 + i < P) {
+            o.rx[i0 + i] = (uint32_t)r[i];
+            o.ry[i0 + i] = (uint32_t)(r[i] >> 32);
         }
-    for (uint64_t m = __ballot(nt > (uint32_t)kOwnTiles); m; m &= m - 1) {
-        const int l = __builtin_ctzll(m);
-        const uint32_t bn = (uint32_t)__builtin_amdgcn_readlane((int)nt, l), bw = (uint32_t)__builtin_amdgcn_readlane((int)w, l);
-        const uint32_t bo = (uint32_t)__builtin_amdgcn_readlane((int)off, l), bt = (uint32_t)__builtin_amdgcn_readlane((int)t00, l);
-        const uint32_t bd = (uint32_t)__builtin_amdgcn_readlane((int)d, l), bp = (uint32_t)__builtin_amdgcn_readlane((int)p, l);
-        const uint32_t keep = bo < cap ? min(bn, cap - bo) : 0u;  // keys below the capacity
-        // k / bw through a double: exact for k < 2^32 / bw with (k + 0.5) / bw
-        // at least 0.5 / bw off any integer
-        const double inv = 1.0 / (double)bw;
-        for (uint32_t k = lane; k < keep; k += 64) {
-            const uint32_t row = (uint32_t)(((double)k + 0.5) * inv);
-            keys[bo + k] = ((uint64_t)(bt + row * (uint32_t)TX + (k - row * bw)) << 32) | bd;
-            vals[bo + k] = bp;
+    }
+    const uint32_t incl = wave_incl_scan(sum);
+    if (lane == 63) s_wsum[wave] = incl;
+    __syncthreads();
+    uint64_t run = incl - sum;
+    for (int w = 0; w < wave; w++) run += s_wsum[w];
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        if (i0 + i < P) offsets[i0 + i] = (uint32_t)run;
+        run += x[i];
+    }
+    if (threadIdx.x == 255) sums[blockIdx.x] = (uint32_t)min(run, (uint64_t)0xffffffffu);
+}
+
+// sums -> exclusive prefixes, in place; *total = their sum (both at most
+// 2^32 - 1).  One workgroup.
+__global__ __launch_bounds__(1024) void k_block_offsets(uint32_t* __restrict__ sums, uint32_t blocks, uint32_t cap,
+                                                        uint32_t* __restrict__ total, int* err) {
+    constexpr uint32_t kItems = 4;
+    __shared__ uint64_t s_wsum[16];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint64_t carry = 0;
+    for (uint32_t b0 = 0; b0 < blocks; b0 += 1024 * kItems) {
+        const uint32_t b = b0 + tid * kItems;
+        uint32_t x[kItems];
+        uint64_t sum = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < kItems; i++) x[i] = b + i < blocks ? sums[b + i] : 0u;
+#pragma unroll
+        for (uint32_t i = 0; i < kItems; i++) sum += x[i];
+        uint64_t incl = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint64_t u = __shfl_up(incl, d, 64);
+            if (lane >= (uint32_t)d) incl += u;
         }
+        if (lane == 63) s_wsum[wave] = incl;
+        __syncthreads();
+        uint64_t run = carry + incl - sum;
+        for (uint32_t w = 0; w < 16; w++) {
+            const uint64_t s = s_wsum[w];
+            if (w < wave) run += s;
+            carry += s;
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kItems; i++) {
+            if (b + i < blocks) sums[b + i] = (uint32_t)min(run, (uint64_t)0xffffffffu);
+            run += x[i];
+        }
+        __syncthreads();  // s_wsum is written again
+    }
+    if (tid == 0) {
+        *total = (uint32_t)min(carry, (uint64_t)0xffffffffu);
+        if (carry > cap) atomicOr(err, 1 << kErrCapacity);
     }
 }
 
-void launch_emit_keys(hipStream_t st, int P, const uint32_t* order, const uint32_t* ntiles,
-                      const uint32_t* offsets, const uint64_t* prect, const uint32_t* depth, int TX, uint32_t cap,
-                      uint64_t* keys, uint32_t* vals, int* err) {
-    if (P <= 0) return;
-    hipLaunchKernelGGL(k_emit_keys, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, P, order, ntiles, offsets,
-                       prect, depth, TX, cap, keys, vals, err);
+// Key emission in depth order, a workgroup per kEmitKeys consecutive keys
+// whatever their primitives' sizes: it finds the first key's primitive in the
+// blocks' and the block's offsets, marks the places where the following
+// primitives begin and spreads them by a maximum scan.  The stores are
+// consecutive.  3.2 M keys of 1 M primitives 17 us, 35 with a lane or (beyond
+// 32 tiles) a wavefront per primitive, which took 1043 us for 13.7 M keys of
+// 600,000 cells, some of 32,400 tiles (the frame 1846 us, now 950).
+constexpr int kEmitKeys = 2048;
+__global__ __launch_bounds__(256) void k_emit_keys(int P, DepthOrder order, const uint32_t* __restrict__ offsets,
+                                                   const uint32_t* __restrict__ blocks,
+                                                   const uint32_t* __restrict__ total, int TX, uint32_t cap,
+                                                   uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+    constexpr int kItems = kEmitKeys / 256;
+    __shared__ uint32_t s_off[kEmitKeys];                     // offset of primitive first + i, minus k0
+    __shared__ __align__(16) uint16_t s_own[kEmitKeys];       // the key's primitive, minus first
+    __shared__ uint32_t s_wave[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t n = min(*total, cap), k0 = blockIdx.x * (uint32_t)kEmitKeys;
+    if (k0 >= n) return;
+    const uint32_t cnt = min(n - k0, (uint32_t)kEmitKeys);
+    // the number of the workgroup's 256 flags, in every thread
+    const auto count = [&](bool f) {
+        const uint32_t c = (uint32_t)__popcll(__ballot(f));
+        if (lane == 0) s_wave[wave] = c;
+        __syncthreads();
+        const uint32_t r = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+        __syncthreads();  // s_wave is written again
+        return r;
+    };
+    // the block of the first key's primitive: the last that begins at or before it
+    uint32_t lo = 0, hi = (uint32_t)((P + kOffsetBlock - 1) / kOffsetBlock);
+    while (hi - lo > 1) {  // blocks[lo] <= k0
+        const uint32_t step = (hi - lo + 255) / 256, b = lo + tid * step;
+        const uint32_t c = count(b < hi && blocks[b] <= k0);  // at least thread 0's
+        lo += (c - 1) * step;
+        hi = min(hi, lo + step);
+    }
+    const uint32_t bo = k0 - blocks[lo], q = lo * kOffsetBlock + tid * 4;
+    uint32_t c = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+        c += (uint32_t)__popcll(__ballot(q + i < (uint32_t)P && offsets[min(q + i, (uint32_t)P - 1)] <= bo));
+    if (lane == 0) s_wave[wave] = c;
+    __syncthreads();
+    const uint32_t first = lo * kOffsetBlock + s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3] - 1;
+    // the primitives from there on: every one before n has a key, so the
+    // workgroup's keys are of at most kEmitKeys of them
+#pragma unroll
+    for (int i = 0; i < kItems; i++) s_own[tid + 256 * i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const uint32_t l = tid + 256 * i, g = first + l;
+        if (g < (uint32_t)P) {
+            const uint32_t o = blocks[g / kOffsetBlock] + offsets[g] - k0;  // negative for the first
+            s_off[l] = o;
+            if (l > 0 && o < cnt) s_own[o] = (uint16_t)l;
+        }
+    }
+    __syncthreads();
+    // maximum over the keys up to each one: eight consecutive per thread
+    {
+        const uint4 v = reinterpret_cast<const uint4*>(s_own)[tid];
+        uint32_t m[8] = {v.x & 0xffffu, v.x >> 16, v.y & 0xffffu, v.y >> 16,
+                         v.z & 0xffffu, v.z >> 16, v.w & 0xffffu, v.w >> 16};
+#pragma unroll
+        for (int i = 1; i < 8; i++) m[i] = max(m[i], m[i - 1]);
+        uint32_t x = m[7];
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t u = __shfl_up(x, d, 64);
+            if (lane >= d) x = max(x, u);
+        }
+        if (lane == 63) s_wave[wave] = x;
+        uint32_t before = __shfl_up(x, 1, 64);
+        if (lane == 0) before = 0;
+        __syncthreads();
+        for (int w = 0; w < wave; w++) before = max(before, s_wave[w]);
+        uint32_t h[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) h[i] = max(m[2 * i], before) | max(m[2 * i + 1], before) << 16;
+        reinterpret_cast<uint4*>(s_own)[tid] = make_uint4(h[0], h[1], h[2], h[3]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const uint32_t k = tid + 256 * i;
+        if (k >= cnt) break;
+        const uint32_t l = s_own[k], j = k - s_off[l], g = first + l;
+        const uint64_t r = order.rx[g] | (uint64_t)order.ry[g] << 32;
+        const int tx0 = rect_x0(r) / kTile, ty0 = rect_y0(r) / kTile;
+        const uint32_t w = (uint32_t)(rect_x1(r) / kTile - tx0 + 1);
+        // j / w by a reciprocal, at most one off (j < 2^24)
+        uint32_t row = (uint32_t)(((float)j + 0.5f) * __builtin_amdgcn_rcpf((float)w));
+        int col = (int)(j - row * w);
+        if (col < 0) {
+            col += (int)w;
+            row--;
+        } else if (col >= (int)w) {
+            col -= (int)w;
+            row++;
+        }
+        keys[k0 + k] = ((uint64_t)((ty0 + row) * (uint32_t)TX + (uint32_t)(tx0 + col)) << 32) | order.depth[g];
+        vals[k0 + k] = order.id[g];
+    }
+}
+
+void launch_emit_keys(hipStream_t st, int P, const DepthOrder& order, const uint64_t* prect, uint32_t* offsets,
+                      uint32_t* sums, int TX, uint32_t cap, uint64_t* keys, uint32_t* vals, uint32_t* total, int* err) {
+    if (P <= 0) {
+        launch_fill_u32(st, total, 0u, 1);
+        return;
+    }
+    const unsigned blocks = (unsigned)((P + kOffsetBlock - 1) / kOffsetBlock);
+    hipLaunchKernelGGL(k_prim_offsets, dim3(blocks), dim3(256), 0, st, P, order, prect, offsets, sums);
+    hipLaunchKernelGGL(k_block_offsets, dim3(1), dim3(1024), 0, st, sums, blocks, cap, total, err);
+    if (cap > 0)
+        hipLaunchKernelGGL(k_emit_keys, dim3((unsigned)(((uint64_t)cap + kEmitKeys - 1) / kEmitKeys)), dim3(256), 0, st,
+                           P, order, offsets, sums, total, TX, cap, keys, vals);
 }
 
 __global__ __launch_bounds__(256) void k_tile_ranges(const uint64_t* __restrict__ keys,
