@@ -53,15 +53,17 @@ def tile_sort_passes(tiles):
 
 
 def sort_traffic(prims, keys, tiles, per_tile):
-    """Algorithmic bytes of the sort: the passes over the (tile, depth) keys
-    on their tile bits (u64 key + u32 value read and written: 24 B per key
-    and pass), and either the depth order of the primitives before them --
-    depth keys written (key and value, 8 B per primitive) and four 8-bit
-    passes over them (16 B read and written per primitive and pass) -- or,
-    with the per-tile order, the sort of each tile's run after them (24 B
-    per key)."""
-    tile_bytes = keys * 24 * tile_sort_passes(tiles)
-    return tile_bytes + (keys * 24 if per_tile else prims * (8 + 4 * 16))
+    """Algorithmic bytes of the sort.  Per-tile order: each primitive's
+    rectangle read for the counts and again, with its depth, for the entries
+    (20 B per primitive), the 8-byte entries written and read and the sorted
+    ids written (20 B per key).  Global order: the depth keys of the primitives
+    written (key and value, 8 B) and four 8-bit passes over them (the key read
+    for the counts, key and value read and written: 20 B per primitive and
+    pass), then the passes over the (tile, depth) keys on their tile bits (u64
+    key and u32 value: 32 B per key and pass)."""
+    if per_tile:
+        return prims * 20 + keys * 20
+    return prims * (8 + 4 * 20) + keys * 32 * tile_sort_passes(tiles)
 
 
 def sort_stage_ms(st):

@@ -201,7 +201,7 @@ dgs_status dgs_set_overlap(dgs_ctx ctx, int32_t enable);
  *     about 131,000 tiles -- takes the global way);
  *   DGS_LIST_ORDER_AUTO (default): per tile for per-cell lists (Duplex,
  *     LC-WSR) when the context's last such frame had at most 1024 keys per
- *     screen tile on average, at most an eighth of its keys in tile runs of
+ *     screen tile on average, at most 1/64 of its keys in tile runs of
  *     more than 4096 entries and at most 8,388,608 keys (the device leaves
  *     those counts in pinned host memory as the frame's lists are built; before any such frame: when the key capacity
  *     is at most 256 keys per tile), else global (always for

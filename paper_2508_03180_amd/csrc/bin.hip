@@ -159,7 +159,8 @@ __device__ __forceinline__ uint32_t sat_add(uint32_t a, uint32_t b) {
 // 2 = inclusive prefix.
 __global__ __launch_bounds__(kBinScanTiles * kBinScanSplit) void k_bin_scan(
     uint32_t* __restrict__ counts, int chunks, int TX, int tiles, int local, uint32_t cap, uint32_t* __restrict__ ranges,
-    uint32_t* __restrict__ total, uint64_t* status, const uint32_t* ep, uint32_t* ticket, int* err, uint64_t* load) {
+    uint32_t* __restrict__ total, uint64_t* status, const uint32_t* ep, uint32_t* ticket, uint32_t* __restrict__ long_tiles,
+    uint32_t* nlong, int* err, uint64_t* load) {
     __shared__ uint32_t s_sum[kBinScanSplit][kBinScanTiles];
     __shared__ uint32_t s_wsum[kBinScanTiles / 64], s_part, s_excl;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -253,9 +254,11 @@ __global__ __launch_bounds__(kBinScanTiles * kBinScanSplit) void k_bin_scan(
     const uint32_t up = __shfl_up(incl, 1, 64);
     if (lane > 0) start = sat_add(start, up);
     if (t >= tiles) return;
-    if (grp == 0)  // tiles without entries keep [0, 0)
-        *reinterpret_cast<uint2*>(ranges + 2 * (size_t)t) =
-            n && start < cap ? make_uint2(start, min(sat_add(start, n), cap)) : make_uint2(0u, 0u);
+    if (grp == 0) {  // tiles without entries keep [0, 0)
+        const uint2 r = n && start < cap ? make_uint2(start, min(sat_add(start, n), cap)) : make_uint2(0u, 0u);
+        *reinterpret_cast<uint2*>(ranges + 2 * (size_t)t) = r;
+        if (r.y - r.x > kLongRun) long_tiles[atomicAdd(nlong, 1u)] = (uint32_t)t;
+    }
     uint32_t run = sat_add(start, before);
 #pragma unroll
     for (int i = 0; i < kBinScanEach; i++) {
@@ -273,7 +276,7 @@ void launch_bin_tiles(hipStream_t st, const BinArgs& a) {
     hipLaunchKernelGGL(k_bin_count, grid, dim3(kBinThreads), lds, st, a.prect, a.P, per, a.TX, local, a.counts);
     hipLaunchKernelGGL(k_bin_scan, dim3((unsigned)((tiles + kBinScanTiles - 1) / kBinScanTiles)),
                        dim3(kBinScanTiles * kBinScanSplit), 0, st, a.counts, chunks, a.TX, tiles, local, a.cap, a.ranges,
-                       a.total, a.status, a.epoch, a.ticket, a.err, a.load);
+                       a.total, a.status, a.epoch, a.ticket, a.long_tiles, a.nlong, a.err, a.load);
     hipLaunchKernelGGL(k_bin_scatter, grid, dim3(kBinThreads), lds, st, a.prect, a.depth, a.P, per, a.TX, local,
                        (const uint32_t*)a.counts, a.cap, a.ent);
 }

@@ -587,22 +587,23 @@ dgs_status dgs_read_decoded(dgs_ctx c, float* means, float* scales, float* rots,
 
 // Per-cell tile lists (Duplex, LC-WSR) are put in depth order per tile
 // (launch_bin_tiles, launch_tile_depth_sort) when the context's last cell
-// frame had at most 1024 keys per tile on average, at most an eighth of its
-// keys in runs of more than 4096 entries (which the per-tile sort handles by
-// chunked merges in global memory over several rounds) and at most 8 M keys
-// (beyond, two radix passes cost a key less than its tile's sorting network,
-// whatever the launches); before any cell frame, when the key buffer holds at
-// most 256 keys per tile.  Measured, us per frame per tile / global: street
-// views of the 6M-Gaussian scene at 4K (6, 14 and 24 M keys, none in long
-// runs) 962 / 1076, 970 / 950 and 1431 / 1364, at 1080p (2 to 7 M) 628 / 747,
-// 479 / 526, 685 / 703 and 705 / 703, at 720p (5 to 9% of the keys in long
-// runs) 563 / 597, 423 / 460 and 590 / 600; the clustered scene's 1M Gaussians
-// as cells of 10, 5, 2 and 1 (0, 0, 4 and 16%) 308 / 411, 390 / 458, 649 / 589
-// and 1092 / 846; 20,000 ragged cells at 1283 x 717 (13 keys per cell) 219 /
-// 304.  Per-Gaussian lists always take the depth sort of the primitives (1M
-// Gaussians at 1080p, 8%: 580 / 466).
+// frame had at most 1024 keys per tile on average, at most 1/64 of its keys in
+// runs of more than 4096 entries (the longest run, sorted by one workgroup in
+// several rounds, is then the sort's span) and at most 8 M keys (beyond, two
+// radix passes cost a key less than its tile's sorting network, whatever the
+// launches); before any cell frame, when the key buffer holds at most 256 keys
+// per tile.  Measured, us per frame per tile / global: street views of the
+// 6M-Gaussian scene at 4K (6, 14 and 24 M keys, none in long runs) 965 / 1076,
+// 971 / 952 and 1442 / 1366, at 1080p (2 to 7 M) 632 / 748, 476 / 528, 669 /
+// 705 and 686 / 704, at 720p (5 to 9% of the keys in long runs) 551 / 598, 422
+// / 461 and 570 / 604; the clustered scene's 1M Gaussians as cells of 10, 5, 4
+// and 3 (0 to 2%) 312 / 409, 379 / 456, 413 / 478 and 503 / 535, of 2 (3 to 5%)
+// 607 / 598 to 724 / 558, of 1 (13 to 21%) 1011 / 837 to 1328 / 794; 20,000
+// ragged cells at 1283 x 717 (13 keys per cell) 220 / 304.  Per-Gaussian lists
+// always take the depth sort of the primitives (1M Gaussians at 1080p, 8%: 533
+// / 461).
 constexpr int64_t kPerTileOrderMaxMean = 1024;      // keys per tile
-constexpr uint64_t kPerTileOrderLongShare = 8;      // at most 1 / this of the keys in long runs
+constexpr uint64_t kPerTileOrderLongShare = 64;     // at most 1 / this of the keys in long runs
 constexpr uint64_t kPerTileOrderMaxKeys = 8u << 20;
 constexpr int64_t kPerTileOrderCapacity = 256;      // keys per tile, before any cell frame
 
@@ -691,10 +692,10 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
 
     StageMarks sm(c);
     {
-        // per-frame zeroing: the scan's ticket, statistics counters and, for
-        // the global order, tile ranges
+        // per-frame zeroing: the scan's ticket and the number of long runs,
+        // statistics counters and, for the global order, tile ranges
         ClearList cl;
-        cl.add(c->misc + 1, 1);
+        cl.add(c->misc + 1, 2);
         if (!per_tile) cl.add(ranges, 2 * (size_t)tiles);
         if (o.stats || save) cl.add((uint32_t*)c->counters, 10);
         cl.bump = c->misc + 13;
@@ -745,12 +746,12 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
         sm.mark(4);
         // the counters take the second key buffer, which is free until the per-tile sort
         launch_bin_tiles(q, BinArgs{prect, c->p_depth, P, k.TX, k.TY, chunks, reinterpret_cast<uint32_t*>(c->keys1), cap,
-                                    c->keys0, ranges, c->misc + 0, c->sort_status, c->misc + 13, c->misc + 1, c->dev_err,
-                                    cells ? c->load_dev : nullptr});
+                                    c->keys0, ranges, c->misc + 0, c->sort_status, c->misc + 13, c->misc + 1, c->vals1,
+                                    c->misc + 2, c->dev_err, cells ? c->load_dev : nullptr});
         sm.mark(5);
         sm.mark(6);
         // the same launch also builds the work queue
-        launch_tile_depth_sort(q, ranges, tiles, c->keys0, svals, c->keys1, save ? save->vals : nullptr,
+        launch_tile_depth_sort(q, ranges, tiles, c->vals1, c->misc + 2, c->keys0, svals, c->keys1, save ? save->vals : nullptr,
                                cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, torder, queue,
                                cells ? c->load_dev + 1 : nullptr, (uint32_t)P);
     } else {

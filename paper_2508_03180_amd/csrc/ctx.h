@@ -94,7 +94,7 @@ struct dgs_ctx_s {
     double* loss_part = nullptr;  // [tiles][2] per-tile sums of the loss
     int64_t cap_loss_coef = 0, cap_loss_part = 0;
     uint32_t* hist = nullptr;     // [256] digit totals of a sort's pass
-    uint32_t* misc = nullptr;     // [0] key total, [1] tile lists' scan ticket, [2..12] spare, [13] look-back frame counter
+    uint32_t* misc = nullptr;     // [0] key total, [1] tile lists' scan ticket, [2] long runs, [3..12] spare, [13] look-back frame counter
     uint32_t* queue = nullptr;    // [kQueueWords] the compositor's work queue (a saved frame has its own)
     int* dev_err = nullptr;
     unsigned long long* counters = nullptr;  // n_val, n_rendered, n_box, n_cell_hits, n_cell_pixels

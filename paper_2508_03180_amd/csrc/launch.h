@@ -97,9 +97,12 @@ struct BinArgs {
     uint64_t* status;  // look-back words, tag j = 0
     const uint32_t* epoch;
     uint32_t* ticket;  // zero beforehand
+    uint32_t* long_tiles;  // [cap / kLongRun] the tiles of more than kLongRun entries, in no particular order
+    uint32_t* nlong;       // their number; zero beforehand
     int* err;
     uint64_t* load;    // as for launch_tile_ranges
 };
+constexpr uint32_t kLongRun = 2048;
 // Chunks of primitives the counting works in, for P primitives on a grid of
 // TX x TY tiles with `words` 32-bit counters and `status_words` look-back
 // words at hand; 0 when the grid is too large for the counting.
@@ -108,9 +111,11 @@ void launch_bin_tiles(hipStream_t st, const BinArgs& a);
 
 // Per-tile depth order: each tile's run of ent (depth bits << 32 | id) in
 // ascending order; the ids go to vals, and also to vcopy when set.  ent and
-// spare (a buffer of its size) are scratch.  The same launch builds the
+// spare (a buffer of its size) are scratch; long_tiles, nlong as made by
+// launch_bin_tiles.  The same launch builds the
 // compositor's work queue (as launch_tile_order; long_stat, prims too).
-void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, uint64_t* ent, uint32_t* vals,
+void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, const uint32_t* long_tiles,
+                            const uint32_t* nlong, uint64_t* ent, uint32_t* vals,
                             uint64_t* spare, uint32_t* vcopy, uint32_t split_len, const uint32_t* total,
                             uint32_t* order, uint32_t* queue,
                             uint64_t* long_stat = nullptr, uint32_t prims = 0);

@@ -29,6 +29,12 @@ constexpr int kTsWaves = 4;
 constexpr int kTsThreads = 64 * kTsWaves;
 constexpr int kTsShort = 256;            // longest run one wavefront sorts
 constexpr int kTsChunk = 4 * kTsThreads;  // longest run the workgroup sorts in registers
+// Workgroups that sort the listed longer runs, one run at a time: among the
+// others' four tiles, two such runs in one workgroup were the kernel's span
+// (1920 x 1080, 333,333 cells of 3 with a few runs of 3,600: frame 568 -> 503
+// us).  With runs from 1,024 on listed, and 256 workgroups, views with a
+// thousand of them waited here (large scene 685 -> 860 us, now 669).
+constexpr unsigned kTsLongGroups = 1024;
 
 __device__ __forceinline__ void put_sorted(uint32_t* vr, uint32_t* vcopy, int i, uint64_t v) {
     vr[i] = (uint32_t)v;
@@ -260,7 +266,8 @@ constexpr int kTsSharedBytes = kQueueBytes > kTsChunk * 8 ? kQueueBytes : kTsChu
 // Workgroup 0 builds the compositor's work queue (it needs the tile ranges
 // only), the others sort the runs.
 __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_tile_sort(
-    const uint32_t* __restrict__ ranges, int tiles, uint64_t* __restrict__ ent, uint32_t* __restrict__ vals,
+    const uint32_t* __restrict__ ranges, int tiles, const uint32_t* __restrict__ long_tiles,
+    const uint32_t* __restrict__ nlong, int long_groups, uint64_t* __restrict__ ent, uint32_t* __restrict__ vals,
     uint64_t* __restrict__ spare, uint32_t* __restrict__ vcopy, uint32_t split_len, const uint32_t* __restrict__ total, uint32_t* __restrict__ order,
     uint32_t* __restrict__ queue, uint64_t* long_stat, uint32_t prims) {
     __shared__ __align__(16) unsigned char smem[kTsSharedBytes];
@@ -272,8 +279,19 @@ __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8)))
                                      s_cnt + kOrderClasses, tid, long_stat, prims);
         return;
     }
-    const int G = (int)gridDim.x - 1, sb = (int)blockIdx.x - 1;
     uint64_t* sd = reinterpret_cast<uint64_t*>(smem);
+    if ((int)blockIdx.x <= long_groups) {
+        const uint32_t n = *nlong;
+#pragma unroll 1
+        for (uint32_t i = blockIdx.x - 1; i < n; i += (uint32_t)long_groups) {
+            const uint32_t t = long_tiles[i], s = ranges[2 * t];
+            sort_long_run(sd, (uint32_t)__builtin_amdgcn_readfirstlane(s),
+                          __builtin_amdgcn_readfirstlane((int)(ranges[2 * t + 1] - s)), ent, vals, spare, vcopy, tid);
+            __syncthreads();  // sd is reused by the next run
+        }
+        return;
+    }
+    const int G = (int)gridDim.x - 1 - long_groups, sb = (int)blockIdx.x - 1 - long_groups;
     // wavefront w takes a tile of the w-th band of G tiles, at an offset
     // that moves by a fixed stride from band to band
     const int t = w * G + (int)(((int64_t)sb + (int64_t)w * (G * 5 / 8 + 1)) % G);
@@ -298,23 +316,25 @@ __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8)))
         else wave_sort_run<4>(kr, vr, vc, L, lane);
     }
     __syncthreads();
-    // the long runs, one at a time with the whole workgroup
+    // the runs longer than a wavefront sorts, one at a time with the whole
+    // workgroup (those beyond kLongRun are the listed ones)
 #pragma unroll 1
     for (int i = 0; i < kTsWaves; i++) {
         const int len = __builtin_amdgcn_readfirstlane(lt_len[i]);
-        if (len <= kTsShort) continue;
+        if (len <= kTsShort || len > (int)kLongRun) continue;
         sort_long_run(sd, (uint32_t)__builtin_amdgcn_readfirstlane(lt_s[i]), len, ent, vals, spare, vcopy, tid);
         __syncthreads();  // sd is reused by the next run
     }
 }
 
-void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, uint64_t* ent, uint32_t* vals,
-                            uint64_t* spare, uint32_t* vcopy, uint32_t split_len, const uint32_t* total,
+void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, const uint32_t* long_tiles,
+                            const uint32_t* nlong, uint64_t* ent, uint32_t* vals, uint64_t* spare, uint32_t* vcopy, uint32_t split_len, const uint32_t* total,
                             uint32_t* order, uint32_t* queue,
                             uint64_t* long_stat, uint32_t prims) {
     if (tiles <= 0) return;
-    const unsigned grid = (unsigned)((tiles + kTsWaves - 1) / kTsWaves) + 1;  // + the work queue's
-    hipLaunchKernelGGL(k_tile_sort, dim3(grid), dim3(kTsThreads), 0, st, ranges, tiles, ent, vals, spare, vcopy,
+    const unsigned lg = (unsigned)tiles < kTsLongGroups ? (unsigned)tiles : kTsLongGroups;
+    const unsigned grid = (unsigned)((tiles + kTsWaves - 1) / kTsWaves) + 1 + lg;  // + the work queue's, the long runs'
+    hipLaunchKernelGGL(k_tile_sort, dim3(grid), dim3(kTsThreads), 0, st, ranges, tiles, long_tiles, nlong, (int)lg, ent, vals, spare, vcopy,
                        split_len, total, order, queue, long_stat, prims);
 }
 
