@@ -4,9 +4,9 @@
 Workload: the clustered 1M-Gaussian scene (100,000 cells x 10 Gaussians, SH
 degree 3, seed 1) rendered at 1920x1080 along a 60-frame orbit, inputs
 resident in HBM.  A step is one whole frame through the C ABI: cell
-preprocess, Gaussian projection, depth sort of the cells, scan + key
-emission, radix sort of the keys on their tile bits, tile ranges
-and work queue, and the hybrid compositor.  The same frames are
+preprocess, Gaussian projection, tile lists (counted into the tiles and
+sorted tile by tile, or a depth sort of the cells, key emission and a radix
+sort of the keys on their tile bits), work queue, and the hybrid compositor.  The same frames are
 also rendered by the per-Gaussian-sort alpha-blending path of the same
 library (the comparison path).
 
@@ -79,14 +79,14 @@ BYTES_PROJECT_SH3 = 12 + 12 + 16 + 4 + 192 + 48 + 8
 
 # HBM traffic of one Duplex compositor launch on this workload, from two
 # rocprofv3 --pmc passes (FETCH_SIZE, WRITE_SIZE) scaled by a 1 GiB copy
-# kernel's reading (profiles/composite_traffic_1080p_1M_pmc.md): 200.352 MB
-# read + 51.105 MB written.  Valid for the compositor sources it was taken
+# kernel's reading (profiles/composite_traffic_1080p_1M_pmc.md): 245.897 MB
+# read + 51.003 MB written.  Valid for the compositor sources it was taken
 # on; reported as null once one of them changes.
-COMPOSITE_TRAFFIC_BYTES = 200.352e6 + 51.105e6
+COMPOSITE_TRAFFIC_BYTES = 245.897e6 + 51.003e6
 COMPOSITE_TRAFFIC_SOURCES = {
-    "paper_2508_03180_amd/csrc/composite.hip": "9b908b67f959c8916ad4c0dcc83857436caea24a95f6f3b7a36644380df5d4dc",
-    "paper_2508_03180_amd/csrc/common.h": "ba55af4abcd758f5c95eae4b782ec45303dc4fdba45ac22ae5f538575a823139",
-    "paper_2508_03180_amd/csrc/cells.h": "462a33024d920aee0b8df89a3c7d1e57d0c202a65220e8a5e209d45b9729cb2d",
+    "paper_2508_03180_amd/csrc/composite.hip": "25913b2c8ba7aecb786f292614905e888847ec54a4f558a1fd276d2ec1d96657",
+    "paper_2508_03180_amd/csrc/common.h": "08964549a45b346424be039493b2786a08bfe524161787e438427f09cad1f075",
+    "paper_2508_03180_amd/csrc/cells.h": "8b85bbb0b3620e5f17f830979a5f6c936979d398acb07cec2383e2dba3df26a1",
 }
 
 
