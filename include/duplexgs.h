@@ -182,8 +182,10 @@ dgs_status dgs_set_stream(dgs_ctx ctx, void* hip_stream);
 /* Overlap inside a frame (on by default): a Duplex or LC-WSR frame projects
  * its members (Sec. IV-A, the Gaussians each cell emits) on a second stream
  * of the context while the cells are sorted (Sec. IV-B), and joins it
- * before compositing.  The second stream is created by the first frame that
- * uses it (never inside a graph capture: such a frame runs on one stream).
+ * before compositing, when they are many enough to be worth the fork (their
+ * projection moves more than 96 MB, or more than 65,536 are decoded).  The
+ * second stream is created by the first frame that uses it (never inside a
+ * graph capture: such a frame runs on one stream).
  * Callers that overlap whole frames themselves -- several contexts on
  * several streams -- can turn it off (enable = 0) so that each context
  * holds one stream.  Results are identical either way. */

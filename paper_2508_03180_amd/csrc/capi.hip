@@ -619,6 +619,23 @@ static bool per_tile_order(dgs_ctx c, int64_t tiles, bool cells) {
     return c->cap_keys <= kPerTileOrderCapacity * tiles;
 }
 
+// Whether a frame's projection (and decode) is worth the second stream: the
+// fork and the join leave the first one idle for about 6 us each and cost the
+// host four calls.  Measured, us per frame on / off: explicit members, by the
+// bytes their projection moves, 2 MB 73 / 61, 12 MB 159 / 154, 73 MB 161 / 157,
+// 93 MB 226 / 224, 146 MB 213 / 216, 292 MB 317 / 332 (with a wait after each
+// frame off leads up to 146 MB: 107 / 89, 195 / 180, 246 / 239); neural ones
+// 4,000 80 / 69, 50,000 141 / 136, 80,000 241 / 244, 200,000 185 / 187, 1 M
+// 323 / 345.
+constexpr int64_t kOverlapBytes = (int64_t)96 << 20;
+constexpr int64_t kOverlapNeural = (int64_t)1 << 16;
+
+static bool worth_overlap(int64_t M, int sh_degree, bool neural) {
+    if (neural) return M > kOverlapNeural;
+    // mean, scales, quaternion and opacity, SH; the record and the rectangle
+    return M * (44 + 12 * (sh_degree + 1) * (sh_degree + 1) + 56) > kOverlapBytes;
+}
+
 // Scratch of a sort of the keys: the upper half of sort_status (the tile
 // lists' look-back words, in the lower half, must only ever hold such words).
 static SortScratch sort_scratch(dgs_ctx c) {
@@ -682,7 +699,7 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
                            ? bin_chunks(P, k.TX, k.TY, 2 * c->cap_keys, c->sort_status_cap / 2)
                            : 0;
     const bool per_tile = chunks > 0;
-    const bool overlap = cells && !c->timing && c->two_streams && ensure_aux(c);
+    const bool overlap = cells && !c->timing && c->two_streams && worth_overlap(M, s->sh_degree, nn != nullptr) && ensure_aux(c);
     // buffers the backward replays: a saved frame's own, else the context's
     float* cell_v = save ? save->cell_v : c->cell_v;
     GRec* recs = save ? save->recs : c->recs;
