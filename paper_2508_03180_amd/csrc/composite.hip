@@ -573,14 +573,14 @@ __device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, in
                 int m[4];
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    const float thi = any ? th : INFINITY;  // none left: a Gaussian that hits nothing
-                    m[i] = any ? __builtin_ctzll(any) : 0;
+                    const bool has = any != 0;  // none left: record 0 in its place, which hits nothing
+                    m[i] = has ? __builtin_ctzll(any) : 0;
                     any &= any - 1;
                     e[i] = read_rec(lb, m[i]);
                     const Gate g = gate(e[i]);
                     const float dy = g.dy0 + shiftf;
                     pw[i] = fmaf(dy, fmaf(e[i].cc, dy, g.t1), g.t0);
-                    ok[i] = (g.ry0 + (uint32_t)shift <= e[i].wy) & (pw[i] >= thi);
+                    ok[i] = has & (g.ry0 + (uint32_t)shift <= e[i].wy) & (pw[i] >= th);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; i++)
