@@ -149,7 +149,11 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_scatter(const uint64_t* __r
 }
 
 // Sums saturate at 2^32 - 1, far above the largest key capacity: an overflow
-// is reported and no slot beyond the capacity is written or read.
+// is reported and no slot beyond the capacity is written or read.  The slots
+// that the scatter counts on from stop at kNoSlot instead: with the entries of
+// a chunk in one tile, fewer than 2^31, they stay below 2^32.
+constexpr uint32_t kNoSlot = 1u << 31;
+
 __device__ __forceinline__ uint32_t sat_add(uint32_t a, uint32_t b) {
     const uint32_t s = a + b;
     return s < a ? 0xffffffffu : s;
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(kBinScanTiles * kBinScanSplit) void k_bin_scan(
 #pragma unroll
     for (int i = 0; i < kBinScanEach; i++) {
         const int c = grp * kBinScanEach + i;
-        if (c < chunks) col[c * stride] = run;
+        if (c < chunks) col[c * stride] = min(run, kNoSlot);
         run = sat_add(run, x[i]);
     }
 }
