@@ -154,11 +154,6 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_scatter(const uint64_t* __r
 // a chunk in one tile, fewer than 2^31, they stay below 2^32.
 constexpr uint32_t kNoSlot = 1u << 31;
 
-__device__ __forceinline__ uint32_t sat_add(uint32_t a, uint32_t b) {
-    const uint32_t s = a + b;
-    return s < a ? 0xffffffffu : s;
-}
-
 // status word: epoch << 34 | flag << 32 | value; flag 1 = workgroup total,
 // 2 = inclusive prefix.
 __global__ __launch_bounds__(kBinScanTiles * kBinScanSplit) void k_bin_scan(

@@ -107,6 +107,20 @@ __host__ __device__ inline int rect_y0(uint64_t r) { return (int)((r >> 32) & 0x
 __host__ __device__ inline int rect_y1(uint64_t r) { return (int)((r >> 48) & 0xffff); }
 constexpr uint64_t kEmptyRect = ~0ull;
 
+// Sum held at 2^32 - 1.
+__host__ __device__ inline uint32_t sat_add(uint32_t a, uint32_t b) {
+    const uint32_t s = a + b;
+    return s < a ? 0xffffffffu : s;
+}
+
+// Place of a primitive's first key relative to key k0 (below 2^30), from the
+// offset of its block of primitives (held at 2^32 - 1) and its own within the
+// block.  A primitive that begins beyond 2^32 has a place beyond any
+// workgroup's keys, as its true one is.
+__host__ __device__ inline uint32_t key_place(uint32_t block, uint32_t offset, uint32_t k0) {
+    return sat_add(block, offset) - k0;
+}
+
 // Workgroups are dispatched round-robin over the XCDs (block b runs on XCD
 // b % 8).  Give each XCD one contiguous range of logical blocks so that
 // neighbouring tiles, which share cells, share that XCD's L2.

@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void k_emit_keys(int P, DepthOrder order, cons
     for (int i = 0; i < kItems; i++) {
         const uint32_t l = tid + 256 * i, g = first + l;
         if (g < (uint32_t)P) {
-            const uint32_t o = blocks[g / kOffsetBlock] + offsets[g] - k0;  // negative for the first
+            const uint32_t o = key_place(blocks[g / kOffsetBlock], offsets[g], k0);  // negative for the first
             s_off[l] = o;
             if (l > 0 && o < cnt) s_own[o] = (uint16_t)l;
         }
