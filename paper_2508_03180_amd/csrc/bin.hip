@@ -228,6 +228,10 @@ __global__ __launch_bounds__(kBinScanTiles * kBinScanSplit) void k_bin_scan(
                 if (fn == 0) {
                     if (++spins > kBinSpinLimit) {
                         if (lane == 0) atomicOr(err, (1 << kErrTimeout) | (1 << kErrWaitScan));
+                        // unknown: everything from here on lies beyond the capacity (too
+                        // small a prefix would let runs overlap, and list more long ones
+                        // than long_tiles holds)
+                        excl = 0xffffffffu;
                         break;
                     }
                     __builtin_amdgcn_s_sleep(1);
