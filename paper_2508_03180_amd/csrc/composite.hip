@@ -64,8 +64,9 @@ __device__ inline void load_cell_chunk(const CompositeArgs& a, uint32_t pos, uin
     q.r2 = p[2];
 }
 
-// The next chunk of the per-Gaussian walk: up to 64 list entries from pos.
-__device__ inline void load_gauss_chunk(const CompositeArgs& a, uint32_t pos, uint32_t end, int lane, Chunk& q) {
+// The next chunk of the per-Gaussian walk: up to 64 list entries from pos,
+// whose ids are at hand (id: this lane's).
+__device__ inline void load_gauss_chunk(const CompositeArgs& a, uint32_t pos, uint32_t end, int lane, uint32_t id, Chunk& q) {
     const int n = (int)min(64u, end - pos);
     q.nch = n;
     q.first = q.cnt = 0;
@@ -73,7 +74,7 @@ __device__ inline void load_gauss_chunk(const CompositeArgs& a, uint32_t pos, ui
     q.r0 = q.r1 = q.r2 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     q.v = 0.0f;
     if (!q.ok) return;
-    const float4* p = reinterpret_cast<const float4*>(a.recs + a.vals[pos + lane]);
+    const float4* p = reinterpret_cast<const float4*>(a.recs + id);
     q.r0 = p[0];
     q.r1 = p[1];
     q.r2 = p[2];
@@ -503,7 +504,16 @@ __device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, in
     for (int j = 0; j < NS; j++) inbm[j] = __ballot(inb[j]);
     const uint32_t lb = lds_base(lds);
     Chunk q;
-    if (start < end) load_gauss_chunk(a, start, end, lane, q);
+    // ids are loaded two chunks ahead, records one, so that the records' addresses
+    // do not wait for memory: a quarter walks a chunk in less than the two trips
+    // take (105 x 57 pixels, 984,000 Gaussians: frame 3258 -> 3010 us; 1920 x 1080,
+    // 1 M: 461 -> 454)
+    uint32_t id = 0;
+    if (start < end) {
+        const uint32_t first = a.vals[min(start + lane, end - 1)];
+        id = a.vals[min(start + 64 + lane, end - 1)];
+        load_gauss_chunk(a, start, end, lane, first, q);
+    }
     bool alive = true;
     for (uint32_t pos = start; pos < end && (alive || STATS);) {
         const int n = q.nch;
@@ -518,7 +528,10 @@ __device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, in
         // after the first ones were opaque (115 us of compositor, now 10)
         if (NS == 1 && !STATS && !(__ballot(!(T[0] < eps)) & inbm[0])) break;
         const uint32_t next = pos + n;
-        if (next < end) load_gauss_chunk(a, next, end, lane, q);
+        if (next < end) {
+            load_gauss_chunk(a, next, end, lane, id, q);
+            id = a.vals[min(next + 64 + lane, end - 1)];
+        }
         // stops the walk when no pixel of the owned strips still blends, else
         // keeps only the records whose box meets a column that still holds a
         // blending pixel in a strip the box covers (a record outside every such
