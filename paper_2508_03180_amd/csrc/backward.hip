@@ -360,7 +360,8 @@ __device__ inline void duplex_tile_bwd(const BwdArgs& a, int tile, int part, int
     }
 }
 
-template <bool RAGGED>
+// TICKETS: also a wavefront's first item is drawn from the queue.
+template <bool RAGGED, bool TICKETS>
 __global__ __launch_bounds__(256) void k_composite_bwd(BwdArgs a) {
     __shared__ GRec s_rec[kBwdWaves][64];
     a.k = a.fr->k;
@@ -370,28 +371,21 @@ __global__ __launch_bounds__(256) void k_composite_bwd(BwdArgs a) {
     const uint32_t nitems = a.queue[1];
     ItemSource src;
     // as in the forward: the item's number in a scalar register
-    for (uint32_t t = __builtin_amdgcn_readfirstlane(first_item<kBwdWaves, 4>(wave, nitems, src)); t < nitems;
-         t = next_item(a.queue, src, lane)) {
+    uint32_t t = __builtin_amdgcn_readfirstlane(first_item<kBwdWaves, kBwdWaves>(wave, nitems, src));
+    if constexpr (TICKETS) t = first_ticket(a.queue, src, lane);
+    for (; t < nitems; t = next_item(a.queue, src, lane)) {
         const uint32_t item = a.order[t];
         const int tile = (int)(item >> 3), mode = (int)(item & 7u);
-        // a tile that the forward walks in quarters is walked here as it would
-        // be without them, by the items of its even quarters or of the first: a
-        // Gaussian's gradient then has no more terms, whose order is free
-        bool whole = mode == 0;
-        if (mode >= 4) {
-            whole = a.ranges[2 * tile + 1] - a.ranges[2 * tile] < kSplitLenCells;
-            if (whole ? mode != 4 : (mode & 1) != 0) continue;
-        }
         // split tiles' items, which set the kernel's span, issue ahead of
         // whole tiles' on their SIMD
-        if (!whole)
+        if (mode != 0)
             __builtin_amdgcn_s_setprio(3);
         else
             __builtin_amdgcn_s_setprio(0);
-        if (whole)
+        if (mode == 0)
             duplex_tile_bwd<4, RAGGED>(a, tile, 0, lane, lds);
         else
-            duplex_tile_bwd<2, RAGGED>(a, tile, mode >= 4 ? (mode - 4) >> 1 : mode - 2, lane, lds);
+            duplex_tile_bwd<2, RAGGED>(a, tile, mode - 2, lane, lds);
     }
 }
 
@@ -680,10 +674,12 @@ void launch_composite_bwd(hipStream_t st, const BwdArgs& a) {
     if (tiles <= 0) return;
     const int waves = 4 * tiles < 256 * 4 * 4 ? 4 * tiles : 256 * 4 * 4;
     const dim3 g((waves + kBwdWaves - 1) / kBwdWaves), b(256);
-    if (a.offs)
-        hipLaunchKernelGGL(k_composite_bwd<true>, g, b, 0, st, a);
-    else
-        hipLaunchKernelGGL(k_composite_bwd<false>, g, b, 0, st, a);
+    // from here on there can be more items (two a tile) than wavefronts
+    const bool tickets = 2 * tiles > waves;
+    if (a.offs && tickets) hipLaunchKernelGGL((k_composite_bwd<true, true>), g, b, 0, st, a);
+    else if (a.offs) hipLaunchKernelGGL((k_composite_bwd<true, false>), g, b, 0, st, a);
+    else if (tickets) hipLaunchKernelGGL((k_composite_bwd<false, true>), g, b, 0, st, a);
+    else hipLaunchKernelGGL((k_composite_bwd<false, false>), g, b, 0, st, a);
 }
 
 template <bool OW, int DEG>

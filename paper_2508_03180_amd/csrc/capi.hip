@@ -257,7 +257,7 @@ DecodeArgs decode_args(dgs_ctx c, const NeuralSrc& nn, const uint32_t* cell_ntil
 }
 
 void free_frame(dgs_frame_s* f) {
-    void* ptrs[] = {f->recs, f->cell_v, f->vals, f->ranges, f->order, f->pix, f->info};
+    void* ptrs[] = {f->recs, f->cell_v, f->vals, f->ranges, f->order, f->border, f->pix, f->info};
     for (void* p : ptrs)
         if (p) hipFree(p);
     delete f;
@@ -276,7 +276,7 @@ dgs_status acquire_frame(dgs_ctx c, int64_t N, int64_t M, int64_t keys, int64_t 
         c->frames.push_back(f);
     }
     hipError_t e = hipSuccess;
-    if (!f->info && (e = hipMalloc((void**)&f->info, kQueueWords * sizeof(uint32_t))) != hipSuccess) goto oom;
+    if (!f->info && (e = hipMalloc((void**)&f->info, 2 * kQueueWords * sizeof(uint32_t))) != hipSuccess) goto oom;
     if (M > f->cap_recs) {
         if ((e = grow(f->recs, M, c->stream)) != hipSuccess) goto oom;
         f->cap_recs = M;
@@ -292,6 +292,7 @@ dgs_status acquire_frame(dgs_ctx c, int64_t N, int64_t M, int64_t keys, int64_t 
     if (tiles > f->cap_tiles) {
         if ((e = grow(f->ranges, 2 * tiles, c->stream)) != hipSuccess) goto oom;
         if ((e = grow(f->order, 4 * tiles, c->stream)) != hipSuccess) goto oom;
+        if ((e = grow(f->border, 2 * tiles, c->stream)) != hipSuccess) goto oom;
         f->cap_tiles = tiles;
     }
     if (6 * pixels > f->cap_pix) {
@@ -704,8 +705,8 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     float* cell_v = save ? save->cell_v : c->cell_v;
     GRec* recs = save ? save->recs : c->recs;
     uint32_t* ranges = save ? save->ranges : c->ranges;
-    uint32_t* torder = save ? save->order : c->tile_order;
-    uint32_t* queue = save ? save->info : c->queue;
+    const WorkQueue work = save ? WorkQueue{save->order, save->info} : WorkQueue{c->tile_order, c->queue};
+    const WorkQueue bwork = save ? WorkQueue{save->border, save->info + kQueueWords} : WorkQueue{};
 
     StageMarks sm(c);
     {
@@ -769,7 +770,7 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
         sm.mark(6);
         // the same launch also builds the work queue
         launch_tile_depth_sort(q, ranges, tiles, c->vals1, c->misc + 2, c->keys0, svals, c->keys1, save ? save->vals : nullptr,
-                               cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, torder, queue,
+                               cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, work, bwork,
                                cells ? c->load_dev + 1 : nullptr, (uint32_t)P);
     } else {
         launch_prim_keys(q, P, c->p_ntiles, c->p_depth, c->pk0, c->pv0);
@@ -805,11 +806,11 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     a.T = out->final_T;
     a.last = out->last;
     a.counters = o.stats ? c->counters : nullptr;
-    a.order = torder;
-    a.queue = queue;
+    a.order = work.order;
+    a.queue = work.queue;
     a.save = save != nullptr;
     if (!per_tile)
-        launch_tile_order(q, ranges, tiles, cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, torder, queue,
+        launch_tile_order(q, ranges, tiles, cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, work, bwork,
                           cells ? c->load_dev + 1 : nullptr, (uint32_t)P);
     if (overlap) hipStreamWaitEvent(q, c->ev_join, 0);  // the projected members
     sm.mark(8);
@@ -884,12 +885,12 @@ dgs_status dgs_render_backward(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
         float* T = f->pix + 4 * HW;
         int32_t* last = reinterpret_cast<int32_t*>(f->pix + 5 * HW);
         // one launch: zeroed gradient sums, the frame record, and the counters
-        // of the forward's work queue (same ranges, same split; it is in the
-        // frame with its item count) rewound
+        // of the backward's work queue (built with the forward's) rewound
         ClearList cl;
         cl.add((uint32_t*)c->g2d, kG2dRow * (size_t)M);
         cl.add((uint32_t*)c->gv, (size_t)N);
-        cl.add(f->info + kQueueStride, kQueueWords - kQueueStride);
+        uint32_t* queue = f->info + kQueueWords;
+        cl.add(queue + kQueueStride, kQueueWords - kQueueStride);
         const FrameK fk{f->k, f->o, color, D, T, last, nullptr, nullptr, nullptr, nullptr};
         launch_clear(q, cl, &fk, c->frame);
         BwdArgs a;
@@ -911,8 +912,8 @@ dgs_status dgs_render_backward(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
         a.grad_D = grad_weight_sum;
         a.g2d = c->g2d;
         a.gv = c->gv;
-        a.order = f->order;
-        a.queue = f->info;
+        a.order = f->border;
+        a.queue = queue;
         launch_composite_bwd(q, a);
         ProjBwdArgs b;
         b.N = N;

@@ -705,14 +705,17 @@ __global__ __launch_bounds__(256) void k_composite(CompositeArgs a) {
     }
 }
 
-// Builds the work queue (build_work_queue, order.h) in one workgroup.
+// Builds the work queues (build_work_queue, order.h), a workgroup each.
 __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t* __restrict__ ranges, int ntiles,
                                                      uint32_t split_len, const uint32_t* __restrict__ total,
-                                                     uint32_t* __restrict__ order, uint32_t* __restrict__ queue,
-                                                     uint64_t* long_stat, uint32_t prims) {
+                                                     WorkQueue fwd, WorkQueue bwd, uint64_t* long_stat,
+                                                     uint32_t prims) {
     __shared__ uint32_t s_cnt[kOrderClasses];
     __shared__ uint32_t s_part[16];
-    build_work_queue<1024>(ranges, ntiles, split_rule(split_len, *total), order, queue, s_cnt, s_part, (int)threadIdx.x, long_stat, prims);
+    const bool b = blockIdx.x == 1;
+    build_work_queue<1024>(ranges, ntiles, b ? split_rule_bwd(split_len) : split_rule(split_len, *total),
+                           b ? bwd.order : fwd.order, b ? bwd.queue : fwd.queue, s_cnt, s_part, (int)threadIdx.x,
+                           b ? nullptr : long_stat, prims);
 }
 
 static unsigned persistent_grid(int tiles) {
@@ -722,10 +725,10 @@ static unsigned persistent_grid(int tiles) {
 }
 
 void launch_tile_order(hipStream_t st, const uint32_t* ranges, int tiles, uint32_t split_len, const uint32_t* total,
-                       uint32_t* order, uint32_t* queue, uint64_t* long_stat, uint32_t prims) {
+                       const WorkQueue& fwd, const WorkQueue& bwd, uint64_t* long_stat, uint32_t prims) {
     if (tiles <= 0) return;
-    hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, st, ranges, tiles, split_len, total, order, queue,
-                       long_stat, prims);
+    hipLaunchKernelGGL(k_tile_order, dim3(bwd.queue ? 2 : 1), dim3(1024), 0, st, ranges, tiles, split_len, total, fwd,
+                       bwd, long_stat, prims);
 }
 
 template <int MODE, bool SAVE, bool RAGGED>

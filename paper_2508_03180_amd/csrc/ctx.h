@@ -37,12 +37,14 @@ struct dgs_frame_s {
     int64_t cap_vals = 0;
     uint32_t* ranges = nullptr; // [2][tiles] per-tile [start, end)
     uint32_t* order = nullptr;  // [4][tiles] compositor work items
+    uint32_t* border = nullptr; // [2][tiles] those of the backward
     int64_t cap_tiles = 0;
     float* pix = nullptr;       // [6][H*W]: colour (3 planes), D, replay T, replay start (int32)
     int64_t cap_pix = 0;
-    uint32_t* info = nullptr;   // [kQueueWords] work queue (order.h: [1] item count, counters from
-                                // [kQueueStride] on), and in its first line [2] key total, [4..13]
-                                // n_val, n_rendered, n_box, n_cell_hits, n_cell_pixels (u64)
+    uint32_t* info = nullptr;   // [2][kQueueWords] work queues of the forward and of the backward
+                                // (order.h: [1] item count, counters from [kQueueStride] on), and in
+                                // the forward's first line [2] key total, [4..13] n_val, n_rendered,
+                                // n_box, n_cell_hits, n_cell_pixels (u64)
 };
 
 struct dgs_ctx_s {

@@ -109,15 +109,22 @@ constexpr uint32_t kLongRun = 2048;
 int bin_chunks(int64_t P, int TX, int TY, int64_t words, size_t status_words);
 void launch_bin_tiles(hipStream_t st, const BinArgs& a);
 
+// A compositor's work queue (order.h): its items and [kQueueWords] item count
+// and counters.
+struct WorkQueue {
+    uint32_t* order = nullptr;
+    uint32_t* queue = nullptr;
+};
+
 // Per-tile depth order: each tile's run of ent (depth bits << 32 | id) in
 // ascending order; the ids go to vals, and also to vcopy when set.  ent and
 // spare (a buffer of its size) are scratch; long_tiles, nlong as made by
 // launch_bin_tiles.  The same launch builds the
-// compositor's work queue (as launch_tile_order; long_stat, prims too).
+// work queues (as launch_tile_order; long_stat, prims too).
 void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, const uint32_t* long_tiles,
                             const uint32_t* nlong, uint64_t* ent, uint32_t* vals,
                             uint64_t* spare, uint32_t* vcopy, uint32_t split_len, const uint32_t* total,
-                            uint32_t* order, uint32_t* queue,
+                            const WorkQueue& fwd, const WorkQueue& bwd,
                             uint64_t* long_stat = nullptr, uint32_t prims = 0);
 // Keys tile << 32 | depth bits of ordered lists (vals by ranges).
 void launch_list_keys(hipStream_t st, const uint32_t* ranges, int tiles, const uint32_t* vals, const uint32_t* depth,
@@ -169,11 +176,12 @@ struct CompositeArgs {
 // Work queue of the compositor (costliest-first tile / half-tile items);
 // must precede launch_composite_*.  Tiles with at least split_len entries
 // become two half-tile items, the longest of them four quarters; *total: the
-// frame's list entries (order.h).
+// frame's list entries (order.h).  With bwd.queue set, also the queue of
+// launch_composite_bwd, which has no quarters ([2 * tiles] items).
 // long_stat (nullable, pinned host memory): receives prims << 32 | the
 // number of keys in runs of more than 4096 entries.
 void launch_tile_order(hipStream_t st, const uint32_t* ranges, int tiles, uint32_t split_len, const uint32_t* total,
-                       uint32_t* order, uint32_t* queue, uint64_t* long_stat = nullptr, uint32_t prims = 0);
+                       const WorkQueue& fwd, const WorkQueue& bwd, uint64_t* long_stat = nullptr, uint32_t prims = 0);
 // Split lengths, measured: lists of cells (each entry K members) and lists
 // of Gaussians.
 constexpr uint32_t kSplitLenCells = 32;

@@ -48,7 +48,13 @@ namespace dgs {
 // opaque), and four costly ones on a SIMD together bind it for most of the
 // launch; two, with cheap ones beside them, leave the balance to be made by
 // what is taken later.  At 1920 x 1080 (100,000 cells): 4, 2 and 1 of 4
-// heavy: 242, 225 and 241 us; the backward, 620, 662 and 690 us, keeps 4.
+// heavy: 242, 225 and 241 us.
+// The backward's items cost more and differ more: it takes them from the costly
+// end only (with 2 of 4 heavy the step of 1343 us for 1285), and where there can
+// be more of them than wavefronts also the first by ticket (its kernel 599 us,
+// 615 with static first ones, 625 when it took the forward's list, whose quarters
+// it walked as halves in the places of cheaper items; where all get an item at
+// once, tickets cost 5 us: 186 / 191 at 301 x 203, and 780 / 808 at 640 x 360).
 constexpr int kQueues = kXcds;
 constexpr int kQueueStride = 32;  // words
 constexpr int kQueueWords = kQueueStride * (1 + kQueues);  // word 1: item count, line 1 + q: counter q
@@ -65,6 +71,10 @@ constexpr uint32_t kSimds = 1024;
 __device__ __forceinline__ SplitRule split_rule(uint32_t split_len, uint32_t total) {
     return {split_len, max(split_len / 4u, total / kSimds)};
 }
+
+// The backward has a list of its own, without quarters: a Gaussian's gradient
+// has a term from every item that it touches, whose order is free.
+__device__ __forceinline__ SplitRule split_rule_bwd(uint32_t split_len) { return {split_len, 0xffffffffu}; }
 
 __device__ __forceinline__ void tile_items(uint32_t len, SplitRule r, uint32_t& n, uint32_t& cls) {
     n = len >= r.quarter ? 4u : len >= r.half ? 2u : 1u;
@@ -201,6 +211,13 @@ __device__ __forceinline__ uint32_t next_item(uint32_t* queue, ItemSource& s, in
         const uint32_t after = (m >> s.q) | (m << (kQueues - s.q));
         s.q = (s.q + __builtin_ctz(after)) & (kQueues - 1);
     }
+}
+
+// A wavefront's first item where none follows from its number: all are drawn
+// from the counters, the costliest by whichever wavefronts come first.
+__device__ __forceinline__ uint32_t first_ticket(uint32_t* queue, ItemSource& s, int lane) {
+    s.waves = s.heads = 0;
+    return next_item(queue, s, lane);
 }
 
 }  // namespace dgs

@@ -264,26 +264,30 @@ constexpr int kQueueBytes = (kOrderClasses + kTsThreads) * 4;
 constexpr int kTsSharedBytes = kQueueBytes > kTsChunk * 8 ? kQueueBytes : kTsChunk * 8;
 
 // Workgroup 0 builds the compositor's work queue (it needs the tile ranges
-// only), the others sort the runs.
+// only), for a saved frame workgroup 1 its backward's; the others sort the runs.
 __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_tile_sort(
     const uint32_t* __restrict__ ranges, int tiles, const uint32_t* __restrict__ long_tiles,
     const uint32_t* __restrict__ nlong, int long_groups, uint64_t* __restrict__ ent, uint32_t* __restrict__ vals,
-    uint64_t* __restrict__ spare, uint32_t* __restrict__ vcopy, uint32_t split_len, const uint32_t* __restrict__ total, uint32_t* __restrict__ order,
-    uint32_t* __restrict__ queue, uint64_t* long_stat, uint32_t prims) {
+    uint64_t* __restrict__ spare, uint32_t* __restrict__ vcopy, uint32_t split_len, const uint32_t* __restrict__ total,
+    WorkQueue fwd, WorkQueue bwd, uint64_t* long_stat, uint32_t prims) {
     __shared__ __align__(16) unsigned char smem[kTsSharedBytes];
     __shared__ int lt_s[kTsWaves], lt_len[kTsWaves];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    if (blockIdx.x == 0) {
+    const int queues = bwd.queue ? 2 : 1;
+    if ((int)blockIdx.x < queues) {
         uint32_t* s_cnt = reinterpret_cast<uint32_t*>(smem);
-        build_work_queue<kTsThreads>(ranges, tiles, split_rule(split_len, *total), order, queue, s_cnt,
-                                     s_cnt + kOrderClasses, tid, long_stat, prims);
+        const bool b = blockIdx.x == 1;
+        build_work_queue<kTsThreads>(ranges, tiles, b ? split_rule_bwd(split_len) : split_rule(split_len, *total),
+                                     b ? bwd.order : fwd.order, b ? bwd.queue : fwd.queue, s_cnt,
+                                     s_cnt + kOrderClasses, tid, b ? nullptr : long_stat, prims);
         return;
     }
+    const int block = (int)blockIdx.x - queues;
     uint64_t* sd = reinterpret_cast<uint64_t*>(smem);
-    if ((int)blockIdx.x <= long_groups) {
+    if (block < long_groups) {
         const uint32_t n = *nlong;
 #pragma unroll 1
-        for (uint32_t i = blockIdx.x - 1; i < n; i += (uint32_t)long_groups) {
+        for (uint32_t i = (uint32_t)block; i < n; i += (uint32_t)long_groups) {
             const uint32_t t = long_tiles[i], s = ranges[2 * t];
             sort_long_run(sd, (uint32_t)__builtin_amdgcn_readfirstlane(s),
                           __builtin_amdgcn_readfirstlane((int)(ranges[2 * t + 1] - s)), ent, vals, spare, vcopy, tid);
@@ -291,7 +295,7 @@ __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8)))
         }
         return;
     }
-    const int G = (int)gridDim.x - 1 - long_groups, sb = (int)blockIdx.x - 1 - long_groups;
+    const int G = (int)gridDim.x - queues - long_groups, sb = block - long_groups;
     // wavefront w takes a tile of the w-th band of G tiles, at an offset
     // that moves by a fixed stride from band to band
     const int t = w * G + (int)(((int64_t)sb + (int64_t)w * (G * 5 / 8 + 1)) % G);
@@ -328,14 +332,15 @@ __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8)))
 }
 
 void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, const uint32_t* long_tiles,
-                            const uint32_t* nlong, uint64_t* ent, uint32_t* vals, uint64_t* spare, uint32_t* vcopy, uint32_t split_len, const uint32_t* total,
-                            uint32_t* order, uint32_t* queue,
+                            const uint32_t* nlong, uint64_t* ent, uint32_t* vals, uint64_t* spare, uint32_t* vcopy,
+                            uint32_t split_len, const uint32_t* total, const WorkQueue& fwd, const WorkQueue& bwd,
                             uint64_t* long_stat, uint32_t prims) {
     if (tiles <= 0) return;
     const unsigned lg = (unsigned)tiles < kTsLongGroups ? (unsigned)tiles : kTsLongGroups;
-    const unsigned grid = (unsigned)((tiles + kTsWaves - 1) / kTsWaves) + 1 + lg;  // + the work queue's, the long runs'
+    // + the work queues', the long runs'
+    const unsigned grid = (unsigned)((tiles + kTsWaves - 1) / kTsWaves) + (bwd.queue ? 2 : 1) + lg;
     hipLaunchKernelGGL(k_tile_sort, dim3(grid), dim3(kTsThreads), 0, st, ranges, tiles, long_tiles, nlong, (int)lg, ent, vals, spare, vcopy,
-                       split_len, total, order, queue, long_stat, prims);
+                       split_len, total, fwd, bwd, long_stat, prims);
 }
 
 __global__ __launch_bounds__(256) void k_list_keys(const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
