@@ -200,6 +200,10 @@ __global__ __launch_bounds__(1024) void k_block_offsets(uint32_t* __restrict__ s
 // 32 tiles) a wavefront per primitive, which took 1043 us for 13.7 M keys of
 // 600,000 cells, some of 32,400 tiles (the frame 1846 us, now 950).
 constexpr int kEmitKeys = 2048;
+// Workgroups of a grid for the capacity; beyond them each takes several blocks
+// of keys (LOOP), as in the sort.
+constexpr unsigned kMaxEmitGrid = 16384;
+template <bool LOOP>
 __global__ __launch_bounds__(256) void k_emit_keys(int P, DepthOrder order, const uint32_t* __restrict__ offsets,
                                                    const uint32_t* __restrict__ blocks,
                                                    const uint32_t* __restrict__ total, int TX, uint32_t cap,
@@ -209,93 +213,97 @@ __global__ __launch_bounds__(256) void k_emit_keys(int P, DepthOrder order, cons
     __shared__ __align__(16) uint16_t s_own[kEmitKeys];       // the key's primitive, minus first
     __shared__ uint32_t s_wave[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t n = min(*total, cap), k0 = blockIdx.x * (uint32_t)kEmitKeys;
-    if (k0 >= n) return;
-    const uint32_t cnt = min(n - k0, (uint32_t)kEmitKeys);
-    // the number of the workgroup's 256 flags, in every thread
-    const auto count = [&](bool f) {
-        const uint32_t c = (uint32_t)__popcll(__ballot(f));
+    const uint32_t n = min(*total, cap);
+    uint32_t k0 = blockIdx.x * (uint32_t)kEmitKeys;
+    for (; k0 < n; k0 += gridDim.x * (uint32_t)kEmitKeys) {
+        const uint32_t cnt = min(n - k0, (uint32_t)kEmitKeys);
+        // the number of the workgroup's 256 flags, in every thread
+        const auto count = [&](bool f) {
+            const uint32_t c = (uint32_t)__popcll(__ballot(f));
+            if (lane == 0) s_wave[wave] = c;
+            __syncthreads();
+            const uint32_t r = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+            __syncthreads();  // s_wave is written again
+            return r;
+        };
+        // the block of the first key's primitive: the last that begins at or before it
+        uint32_t lo = 0, hi = (uint32_t)((P + kOffsetBlock - 1) / kOffsetBlock);
+        while (hi - lo > 1) {  // blocks[lo] <= k0
+            const uint32_t step = (hi - lo + 255) / 256, b = lo + tid * step;
+            const uint32_t c = count(b < hi && blocks[b] <= k0);  // at least thread 0's
+            lo += (c - 1) * step;
+            hi = min(hi, lo + step);
+        }
+        const uint32_t bo = k0 - blocks[lo], q = lo * kOffsetBlock + tid * 4;
+        uint32_t c = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            c += (uint32_t)__popcll(__ballot(q + i < (uint32_t)P && offsets[min(q + i, (uint32_t)P - 1)] <= bo));
         if (lane == 0) s_wave[wave] = c;
         __syncthreads();
-        const uint32_t r = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
-        __syncthreads();  // s_wave is written again
-        return r;
-    };
-    // the block of the first key's primitive: the last that begins at or before it
-    uint32_t lo = 0, hi = (uint32_t)((P + kOffsetBlock - 1) / kOffsetBlock);
-    while (hi - lo > 1) {  // blocks[lo] <= k0
-        const uint32_t step = (hi - lo + 255) / 256, b = lo + tid * step;
-        const uint32_t c = count(b < hi && blocks[b] <= k0);  // at least thread 0's
-        lo += (c - 1) * step;
-        hi = min(hi, lo + step);
-    }
-    const uint32_t bo = k0 - blocks[lo], q = lo * kOffsetBlock + tid * 4;
-    uint32_t c = 0;
+        const uint32_t first = lo * kOffsetBlock + s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3] - 1;
+        // the primitives from there on: every one before n has a key, so the
+        // workgroup's keys are of at most kEmitKeys of them
 #pragma unroll
-    for (int i = 0; i < 4; i++)
-        c += (uint32_t)__popcll(__ballot(q + i < (uint32_t)P && offsets[min(q + i, (uint32_t)P - 1)] <= bo));
-    if (lane == 0) s_wave[wave] = c;
-    __syncthreads();
-    const uint32_t first = lo * kOffsetBlock + s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3] - 1;
-    // the primitives from there on: every one before n has a key, so the
-    // workgroup's keys are of at most kEmitKeys of them
-#pragma unroll
-    for (int i = 0; i < kItems; i++) s_own[tid + 256 * i] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kItems; i++) {
-        const uint32_t l = tid + 256 * i, g = first + l;
-        if (g < (uint32_t)P) {
-            const uint32_t o = key_place(blocks[g / kOffsetBlock], offsets[g], k0);  // negative for the first
-            s_off[l] = o;
-            if (l > 0 && o < cnt) s_own[o] = (uint16_t)l;
-        }
-    }
-    __syncthreads();
-    // maximum over the keys up to each one: eight consecutive per thread
-    {
-        const uint4 v = reinterpret_cast<const uint4*>(s_own)[tid];
-        uint32_t m[8] = {v.x & 0xffffu, v.x >> 16, v.y & 0xffffu, v.y >> 16,
-                         v.z & 0xffffu, v.z >> 16, v.w & 0xffffu, v.w >> 16};
-#pragma unroll
-        for (int i = 1; i < 8; i++) m[i] = max(m[i], m[i - 1]);
-        uint32_t x = m[7];
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t u = __shfl_up(x, d, 64);
-            if (lane >= d) x = max(x, u);
-        }
-        if (lane == 63) s_wave[wave] = x;
-        uint32_t before = __shfl_up(x, 1, 64);
-        if (lane == 0) before = 0;
+        for (int i = 0; i < kItems; i++) s_own[tid + 256 * i] = 0;
         __syncthreads();
-        for (int w = 0; w < wave; w++) before = max(before, s_wave[w]);
-        uint32_t h[4];
 #pragma unroll
-        for (int i = 0; i < 4; i++) h[i] = max(m[2 * i], before) | max(m[2 * i + 1], before) << 16;
-        reinterpret_cast<uint4*>(s_own)[tid] = make_uint4(h[0], h[1], h[2], h[3]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kItems; i++) {
-        const uint32_t k = tid + 256 * i;
-        if (k >= cnt) break;
-        const uint32_t l = s_own[k], j = k - s_off[l], g = first + l;
-        const uint64_t r = order.rx[g] | (uint64_t)order.ry[g] << 32;
-        const int tx0 = rect_x0(r) / kTile, ty0 = rect_y0(r) / kTile;
-        const uint32_t w = (uint32_t)(rect_x1(r) / kTile - tx0 + 1);
-        // j / w by a reciprocal, at most one off (j < 2^24)
-        uint32_t row = (uint32_t)(((float)j + 0.5f) * __builtin_amdgcn_rcpf((float)w));
-        int col = (int)(j - row * w);
-        if (col < 0) {
-            col += (int)w;
-            row--;
-        } else if (col >= (int)w) {
-            col -= (int)w;
-            row++;
+        for (int i = 0; i < kItems; i++) {
+            const uint32_t l = tid + 256 * i, g = first + l;
+            if (g < (uint32_t)P) {
+                const uint32_t o = key_place(blocks[g / kOffsetBlock], offsets[g], k0);  // negative for the first
+                s_off[l] = o;
+                if (l > 0 && o < cnt) s_own[o] = (uint16_t)l;
+            }
         }
-        keys[k0 + k] = ((uint64_t)((ty0 + row) * (uint32_t)TX + (uint32_t)(tx0 + col)) << 32) | order.depth[g];
-        vals[k0 + k] = order.id[g];
+        __syncthreads();
+        // maximum over the keys up to each one: eight consecutive per thread
+        {
+            const uint4 v = reinterpret_cast<const uint4*>(s_own)[tid];
+            uint32_t m[8] = {v.x & 0xffffu, v.x >> 16, v.y & 0xffffu, v.y >> 16,
+                             v.z & 0xffffu, v.z >> 16, v.w & 0xffffu, v.w >> 16};
+#pragma unroll
+            for (int i = 1; i < 8; i++) m[i] = max(m[i], m[i - 1]);
+            uint32_t x = m[7];
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t u = __shfl_up(x, d, 64);
+                if (lane >= d) x = max(x, u);
+            }
+            if (lane == 63) s_wave[wave] = x;
+            uint32_t before = __shfl_up(x, 1, 64);
+            if (lane == 0) before = 0;
+            __syncthreads();
+            for (int w = 0; w < wave; w++) before = max(before, s_wave[w]);
+            uint32_t h[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) h[i] = max(m[2 * i], before) | max(m[2 * i + 1], before) << 16;
+            reinterpret_cast<uint4*>(s_own)[tid] = make_uint4(h[0], h[1], h[2], h[3]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kItems; i++) {
+            const uint32_t k = tid + 256 * i;
+            if (k >= cnt) break;
+            const uint32_t l = s_own[k], j = k - s_off[l], g = first + l;
+            const uint64_t r = order.rx[g] | (uint64_t)order.ry[g] << 32;
+            const int tx0 = rect_x0(r) / kTile, ty0 = rect_y0(r) / kTile;
+            const uint32_t w = (uint32_t)(rect_x1(r) / kTile - tx0 + 1);
+            // j / w by a reciprocal, at most one off (j < 2^24)
+            uint32_t row = (uint32_t)(((float)j + 0.5f) * __builtin_amdgcn_rcpf((float)w));
+            int col = (int)(j - row * w);
+            if (col < 0) {
+                col += (int)w;
+                row--;
+            } else if (col >= (int)w) {
+                col -= (int)w;
+                row++;
+            }
+            keys[k0 + k] = ((uint64_t)((ty0 + row) * (uint32_t)TX + (uint32_t)(tx0 + col)) << 32) | order.depth[g];
+            vals[k0 + k] = order.id[g];
+        }
+        if (!LOOP) return;
+        __syncthreads();  // the LDS is written again
     }
 }
 
@@ -308,9 +316,13 @@ void launch_emit_keys(hipStream_t st, int P, const DepthOrder& order, const uint
     const unsigned blocks = (unsigned)((P + kOffsetBlock - 1) / kOffsetBlock);
     hipLaunchKernelGGL(k_prim_offsets, dim3(blocks), dim3(256), 0, st, P, order, prect, offsets, sums);
     hipLaunchKernelGGL(k_block_offsets, dim3(1), dim3(1024), 0, st, sums, blocks, cap, total, err);
-    if (cap > 0)
-        hipLaunchKernelGGL(k_emit_keys, dim3((unsigned)(((uint64_t)cap + kEmitKeys - 1) / kEmitKeys)), dim3(256), 0, st,
-                           P, order, offsets, sums, total, TX, cap, keys, vals);
+    const unsigned groups = (unsigned)(((uint64_t)cap + kEmitKeys - 1) / kEmitKeys);
+    if (groups > kMaxEmitGrid)
+        hipLaunchKernelGGL(k_emit_keys<true>, dim3(kMaxEmitGrid), dim3(256), 0, st, P, order, offsets, sums, total, TX,
+                           cap, keys, vals);
+    else if (groups > 0)
+        hipLaunchKernelGGL(k_emit_keys<false>, dim3(groups), dim3(256), 0, st, P, order, offsets, sums, total, TX, cap,
+                           keys, vals);
 }
 
 __global__ __launch_bounds__(256) void k_tile_ranges(const uint64_t* __restrict__ keys,

@@ -40,12 +40,19 @@ static size_t max_parts(int64_t cap) { return (size_t)((cap + kSmallPart - 1) / 
 
 size_t sort_status_words(int64_t cap) { return max_parts(cap) * 256; }
 
-// The workgroup's partition: each XCD (block % 8) has one contiguous range of
-// them, so that the runs which neighbouring partitions write into one line
-// meet in that XCD's L2.  nparts or more: none (the grid is for the capacity).
-__device__ __forceinline__ uint32_t own_part(uint32_t nparts) {
-    const uint32_t per = (nparts + kXcds - 1) / kXcds, i = blockIdx.x / kXcds;
-    return i < per ? blockIdx.x % kXcds * per + i : nparts;
+// The grid of a frame's sort is for the capacity, of which it may use little:
+// beyond this many workgroups they take several partitions each.  A 1920 x 1080
+// frame of 546,000 keys in a buffer of 2^28 took 490 us, 131 of them in two
+// passes of 65,536 workgroups nearly all without keys; now 390, 377 with 4096
+// workgroups, which a frame of 54 M keys pays for (2100 us, with 4096 2212).
+constexpr uint32_t kMaxGrid = 16384;
+
+// Partition i of the workgroups' order: each XCD (block % 8) has one contiguous
+// range of them, so that the runs which neighbouring partitions write into one
+// line meet in that XCD's L2.  nparts or more: none.
+__device__ __forceinline__ uint32_t nth_part(uint32_t i, uint32_t nparts) {
+    const uint32_t per = (nparts + kXcds - 1) / kXcds, k = i / kXcds;
+    return k < per ? i % kXcds * per + k : nparts;
 }
 
 // Digit of a key at a shift that is a multiple of 8: it lies in one word.
@@ -54,7 +61,21 @@ __device__ __forceinline__ uint32_t digit(uint64_t k, int shift) {
 }
 __device__ __forceinline__ uint32_t digit(uint32_t k, int shift) { return (k >> shift) & 255u; }
 
-template <class KeyT, int THREADS, int ITEMS>
+// Runs f(part) for the workgroup's partitions (LOOP: several).
+template <bool LOOP, class F>
+__device__ __forceinline__ void own_parts(uint32_t nparts, F f) {
+    uint32_t b = blockIdx.x;
+    for (;;) {
+        const uint32_t part = nth_part(b, nparts);
+        if (part >= nparts) return;
+        f(part);
+        if (!LOOP) return;
+        __syncthreads();  // the LDS is written again
+        b += gridDim.x;
+    }
+}
+
+template <class KeyT, int THREADS, int ITEMS, bool LOOP>
 __global__ __launch_bounds__(THREADS) void k_sort_count(const KeyT* __restrict__ keys,
                                                         const uint32_t* __restrict__ n_ptr, uint32_t cap, int shift,
                                                         uint32_t* __restrict__ counts) {
@@ -66,26 +87,27 @@ __global__ __launch_bounds__(THREADS) void k_sort_count(const KeyT* __restrict__
     uint32_t n = n_ptr ? *n_ptr : cap;
     if (n > cap) n = cap;
     const uint32_t nparts = (n + kPart - 1) / kPart;
-    const uint32_t part = own_part(nparts), pbase = part * kPart;
-    if (part >= nparts) return;
-    KeyT k[ITEMS];
+    own_parts<LOOP>(nparts, [&](uint32_t part) __attribute__((always_inline)) {
+        const uint32_t pbase = part * kPart;
+        KeyT k[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-        const uint32_t idx = pbase + i * THREADS + tid;
-        k[i] = keys[idx < n ? idx : n - 1];
-    }
-    for (uint32_t d = tid; d < kCopies * 256; d += THREADS) (&s_cnt[0][0])[d] = 0;
-    __syncthreads();
+        for (int i = 0; i < ITEMS; i++) {
+            const uint32_t idx = pbase + i * THREADS + tid;
+            k[i] = keys[idx < n ? idx : n - 1];
+        }
+        for (uint32_t d = tid; d < kCopies * 256; d += THREADS) (&s_cnt[0][0])[d] = 0;
+        __syncthreads();
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++)
-        if (pbase + i * THREADS + tid < n) atomicAdd(&cnt[digit(k[i], shift)], 1u);
-    __syncthreads();
-    if (tid < 256) {
-        uint32_t s = 0;
+        for (int i = 0; i < ITEMS; i++)
+            if (pbase + i * THREADS + tid < n) atomicAdd(&cnt[digit(k[i], shift)], 1u);
+        __syncthreads();
+        if (tid < 256) {
+            uint32_t s = 0;
 #pragma unroll
-        for (int c = 0; c < kCopies; c++) s += s_cnt[c][tid];
-        counts[(size_t)part * 256 + tid] = s;
-    }
+            for (int c = 0; c < kCopies; c++) s += s_cnt[c][tid];
+            counts[(size_t)part * 256 + tid] = s;
+        }
+    });
 }
 
 // Columns of the table [partition][digit] -> exclusive prefixes, in place;
@@ -139,7 +161,7 @@ __device__ inline uint32_t lanes_below(uint64_t mask) {
 // n_ptr (device) holds the item count, or is null for n = cap.  DIRECT: counts
 // holds the partitions' counts (at most kDirectParts rows), else their
 // prefixes, and totals the digits' totals.
-template <class KeyT, int THREADS, int ITEMS, bool DIRECT>
+template <class KeyT, int THREADS, int ITEMS, bool DIRECT, bool LOOP>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 512 ? 8 : 1)))
 void k_sort_scatter(const KeyT* __restrict__ kin, const uint32_t* __restrict__ vin, KeyT* __restrict__ kout,
                     uint32_t* __restrict__ vout, const uint32_t* __restrict__ n_ptr, uint32_t cap, int shift,
@@ -153,131 +175,133 @@ void k_sort_scatter(const KeyT* __restrict__ kin, const uint32_t* __restrict__ v
     __shared__ uint32_t s_gbase[256];     // global start of each digit's run minus its local start
     __shared__ uint32_t s_wsum[2][4];
     uint32_t* s_val = reinterpret_cast<uint32_t*>(s_key);
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint32_t n = n_ptr ? *n_ptr : cap;
     if (n > cap) n = cap;
     const uint32_t nparts = (n + kPart - 1) / kPart;
-    const uint32_t part = own_part(nparts);
-    if (part >= nparts) return;
-    const uint32_t pbase = part * kPart, wbase = pbase + wave * (ITEMS * 64);  // uniform
-    const uint32_t left = n > wbase ? n - wbase : 0u;  // keys from the wavefront's first on
-    // a lane past the end reads the last key again (a wavefront past it key 0)
-    const uint32_t rmax = left ? left - 1 : 0u;
-    const KeyT* kw = kin + (left ? wbase : 0u);
-    const uint32_t* vw = vin + (left ? wbase : 0u);
-    KeyT k[ITEMS];
-    uint32_t v[ITEMS], rank[ITEMS];
+    own_parts<LOOP>(nparts, [&](uint32_t part) __attribute__((always_inline)) {
+        uint32_t tid = threadIdx.x;
+        if (LOOP) asm volatile("" : "+v"(tid));  // nothing made of it is kept from part to part in registers
+        const uint32_t lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const uint32_t pbase = part * kPart, wbase = pbase + wave * (ITEMS * 64);  // uniform
+        const uint32_t left = n > wbase ? n - wbase : 0u;  // keys from the wavefront's first on
+        // a lane past the end reads the last key again (a wavefront past it key 0)
+        const uint32_t rmax = left ? left - 1 : 0u;
+        const KeyT* kw = kin + (left ? wbase : 0u);
+        const uint32_t* vw = vin + (left ? wbase : 0u);
+        KeyT k[ITEMS];
+        uint32_t v[ITEMS], rank[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) k[i] = kw[min(i * 64 + lane, rmax)];
-    uint32_t excl = 0, total = 0;
-    if (DIRECT) {
-        if (tid < 256 && nparts > 1)
+        for (int i = 0; i < ITEMS; i++) k[i] = kw[min(i * 64 + lane, rmax)];
+        uint32_t excl = 0, total = 0;
+        if (DIRECT) {
+            if (tid < 256 && nparts > 1)
 #pragma unroll 8
-            for (uint32_t r = 0; r < nparts; r++) {
-                const uint32_t c = counts[r * 256 + tid];
-                total += c;
-                excl += r < part ? c : 0u;
-            }
-    } else if (tid < 256) {
-        excl = counts[(size_t)part * 256 + tid];
-        total = totals[tid];
-    }
-    for (uint32_t d = tid; d < kWaves * 128; d += THREADS) reinterpret_cast<uint32_t*>(s_cnt)[d] = 0;
-    __syncthreads();
-    // stable ranking inside the wave: item i of every lane precedes item i+1
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-        const bool valid = i * 64 + lane < left;
-        const uint32_t d = digit(k[i], shift);
-        // lanes whose digit differs, bit by bit; lanes without a key differ
-        const uint64_t vb = __ballot(valid);
-        uint32_t dlo = ~(uint32_t)vb, dhi = ~(uint32_t)(vb >> 32);
-#pragma unroll
-        for (int b = 0; b < 8; b++) {
-            const uint32_t m = (uint32_t)((int32_t)(d << (31 - b)) >> 31);  // all ones where the bit is set
-            const uint64_t bb = __ballot(m != 0);
-            dlo |= (uint32_t)bb ^ m;
-            dhi |= (uint32_t)(bb >> 32) ^ m;
+                for (uint32_t r = 0; r < nparts; r++) {
+                    const uint32_t c = counts[r * 256 + tid];
+                    total += c;
+                    excl += r < part ? c : 0u;
+                }
+        } else if (tid < 256) {
+            excl = counts[(size_t)part * 256 + tid];
+            total = totals[tid];
         }
-        const uint64_t peers = ~((uint64_t)dhi << 32 | dlo);
-        uint32_t before = 0;
-        if (valid) before = s_cnt[wave][d];
-        rank[i] = before + lanes_below(peers);
-        asm volatile("" : "+v"(rank[i]));  // now: kept as its three operands, the ranks spill
-        if (valid && lane == (uint32_t)__builtin_ctzll(peers))
-            s_cnt[wave][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
-        __builtin_amdgcn_wave_barrier();
-    }
+        for (uint32_t d = tid; d < kWaves * 128; d += THREADS) reinterpret_cast<uint32_t*>(s_cnt)[d] = 0;
+        __syncthreads();
+        // stable ranking inside the wave: item i of every lane precedes item i+1
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) v[i] = vw[min(i * 64 + lane, rmax)];
-    __syncthreads();
-    // thread d < 256: digit d's per-wave offsets, its start in the
-    // partition and in the output
-    uint32_t tot = 0, x = 0, y = 0;
-    if (tid < 256) {
-#pragma unroll
-        for (int w = 0; w < kWaves; w++) {
-            const uint32_t c = s_cnt[w][tid];
-            s_cnt[w][tid] = (uint16_t)tot;
-            tot += c;
-        }
-        if (DIRECT && nparts == 1) total = tot;  // the only partition: nothing was counted before
-        x = tot;
-        y = total;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t u = __shfl_up(x, o, 64), t = __shfl_up(y, o, 64);
-            if (lane >= (uint32_t)o) {
-                x += u;
-                y += t;
-            }
-        }
-        if (lane == 63) {
-            s_wsum[0][wave] = x;
-            s_wsum[1][wave] = y;
-        }
-    }
-    __syncthreads();
-    if (tid < 256) {
-        uint32_t lstart = x - tot, gstart = y - total;
-        for (uint32_t w = 0; w < wave; w++) {
-            lstart += s_wsum[0][w];
-            gstart += s_wsum[1][w];
-        }
-        s_lstart[tid] = lstart;
-        s_gbase[tid] = gstart + excl - lstart;
-    }
-    __syncthreads();
-    // the partition in digit order through LDS: keys, then values
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++)
-        if (i * 64 + lane < left) {
+        for (int i = 0; i < ITEMS; i++) {
+            const bool valid = i * 64 + lane < left;
             const uint32_t d = digit(k[i], shift);
-            rank[i] += s_lstart[d] + s_cnt[wave][d];
-            s_key[rank[i]] = k[i];
+            // lanes whose digit differs, bit by bit; lanes without a key differ
+            const uint64_t vb = __ballot(valid);
+            uint32_t dlo = ~(uint32_t)vb, dhi = ~(uint32_t)(vb >> 32);
+#pragma unroll
+            for (int b = 0; b < 8; b++) {
+                const uint32_t m = (uint32_t)((int32_t)(d << (31 - b)) >> 31);  // all ones where the bit is set
+                const uint64_t bb = __ballot(m != 0);
+                dlo |= (uint32_t)bb ^ m;
+                dhi |= (uint32_t)(bb >> 32) ^ m;
+            }
+            const uint64_t peers = ~((uint64_t)dhi << 32 | dlo);
+            uint32_t before = 0;
+            if (valid) before = s_cnt[wave][d];
+            rank[i] = before + lanes_below(peers);
+            asm volatile("" : "+v"(rank[i]));  // now: kept as its three operands, the ranks spill
+            if (valid && lane == (uint32_t)__builtin_ctzll(peers))
+                s_cnt[wave][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+            __builtin_amdgcn_wave_barrier();
         }
-    __syncthreads();
-    const uint32_t cnt = n - pbase < kPart ? n - pbase : kPart;
-    uint32_t pos[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-        const uint32_t j = tid + i * THREADS;
-        pos[i] = n;
-        if (j < cnt) {
-            const KeyT kk = s_key[j];
-            pos[i] = s_gbase[digit(kk, shift)] + j;
-            // below n, unless the caller's keys changed under the sort
-            if (pos[i] < n) kout[pos[i]] = kk;
+        for (int i = 0; i < ITEMS; i++) v[i] = vw[min(i * 64 + lane, rmax)];
+        __syncthreads();
+        // thread d < 256: digit d's per-wave offsets, its start in the
+        // partition and in the output
+        uint32_t tot = 0, x = 0, y = 0;
+        if (tid < 256) {
+#pragma unroll
+            for (int w = 0; w < kWaves; w++) {
+                const uint32_t c = s_cnt[w][tid];
+                s_cnt[w][tid] = (uint16_t)tot;
+                tot += c;
+            }
+            if (DIRECT && nparts == 1) total = tot;  // the only partition: nothing was counted before
+            x = tot;
+            y = total;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t u = __shfl_up(x, o, 64), t = __shfl_up(y, o, 64);
+                if (lane >= (uint32_t)o) {
+                    x += u;
+                    y += t;
+                }
+            }
+            if (lane == 63) {
+                s_wsum[0][wave] = x;
+                s_wsum[1][wave] = y;
+            }
         }
-    }
-    __syncthreads();
+        __syncthreads();
+        if (tid < 256) {
+            uint32_t lstart = x - tot, gstart = y - total;
+            for (uint32_t w = 0; w < wave; w++) {
+                lstart += s_wsum[0][w];
+                gstart += s_wsum[1][w];
+            }
+            s_lstart[tid] = lstart;
+            s_gbase[tid] = gstart + excl - lstart;
+        }
+        __syncthreads();
+        // the partition in digit order through LDS: keys, then values
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++)
-        if (i * 64 + lane < left) s_val[rank[i]] = v[i];
-    __syncthreads();
+        for (int i = 0; i < ITEMS; i++)
+            if (i * 64 + lane < left) {
+                const uint32_t d = digit(k[i], shift);
+                rank[i] += s_lstart[d] + s_cnt[wave][d];
+                s_key[rank[i]] = k[i];
+            }
+        __syncthreads();
+        const uint32_t cnt = n - pbase < kPart ? n - pbase : kPart;
+        uint32_t pos[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++)
-        if (pos[i] < n) vout[pos[i]] = s_val[tid + i * THREADS];
+        for (int i = 0; i < ITEMS; i++) {
+            const uint32_t j = tid + i * THREADS;
+            pos[i] = n;
+            if (j < cnt) {
+                const KeyT kk = s_key[j];
+                pos[i] = s_gbase[digit(kk, shift)] + j;
+                // below n, unless the caller's keys changed under the sort
+                if (pos[i] < n) kout[pos[i]] = kk;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < ITEMS; i++)
+            if (i * 64 + lane < left) s_val[rank[i]] = v[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < ITEMS; i++)
+            if (pos[i] < n) vout[pos[i]] = s_val[tid + i * THREADS];
+    });
 }
 
 template <class KeyT, int THREADS, int ITEMS>
@@ -285,23 +309,26 @@ static void sort_passes_launch(hipStream_t st, KeyT* k0, uint32_t* v0, KeyT* k1,
                                const uint32_t* n_ptr, uint32_t cap, int first_bit, int passes, const SortScratch& s) {
     constexpr uint32_t kPart = THREADS * ITEMS;
     const uint32_t parts = (uint32_t)(((uint64_t)cap + kPart - 1) / kPart);
-    const dim3 grid((parts + kXcds - 1) / kXcds * kXcds), block(THREADS);
+    const uint32_t groups = (parts + kXcds - 1) / kXcds * kXcds;
+    const bool loop = n_ptr && groups > kMaxGrid;
+    const dim3 grid(loop ? kMaxGrid : groups), block(THREADS);
     KeyT *ki = k0, *ko = k1;
     uint32_t *vi = v0, *vo = v1;
     for (int p = 0; p < passes; p++) {
         const int shift = first_bit + 8 * p;
-        if (parts > 1)
-            hipLaunchKernelGGL((k_sort_count<KeyT, THREADS, ITEMS>), grid, block, 0, st, ki, n_ptr, cap, shift,
-                               s.counts);
-        if (parts <= kDirectParts) {
-            hipLaunchKernelGGL((k_sort_scatter<KeyT, THREADS, ITEMS, true>), grid, block, 0, st, ki, vi, ko, vo, n_ptr,
-                               cap, shift, s.counts, s.totals);
-        } else {
-            hipLaunchKernelGGL(k_sort_scan, dim3(256 / kScanDigits), dim3(1024), 0, st, s.counts, n_ptr, cap, kPart,
-                               s.totals);
-            hipLaunchKernelGGL((k_sort_scatter<KeyT, THREADS, ITEMS, false>), grid, block, 0, st, ki, vi, ko, vo,
-                               n_ptr, cap, shift, s.counts, s.totals);
-        }
+        const auto launch = [&](auto* count, auto* scatter, bool direct) {
+            if (parts > 1) hipLaunchKernelGGL(count, grid, block, 0, st, ki, n_ptr, cap, shift, s.counts);
+            if (!direct)
+                hipLaunchKernelGGL(k_sort_scan, dim3(256 / kScanDigits), dim3(1024), 0, st, s.counts, n_ptr, cap, kPart,
+                                   s.totals);
+            hipLaunchKernelGGL(scatter, grid, block, 0, st, ki, vi, ko, vo, n_ptr, cap, shift, s.counts, s.totals);
+        };
+        if (parts <= kDirectParts)
+            launch(k_sort_count<KeyT, THREADS, ITEMS, false>, k_sort_scatter<KeyT, THREADS, ITEMS, true, false>, true);
+        else if (!loop)
+            launch(k_sort_count<KeyT, THREADS, ITEMS, false>, k_sort_scatter<KeyT, THREADS, ITEMS, false, false>, false);
+        else if constexpr (THREADS == 512)  // sorts with small partitions have few of them
+            launch(k_sort_count<KeyT, THREADS, ITEMS, true>, k_sort_scatter<KeyT, THREADS, ITEMS, false, true>, false);
         KeyT* tk = ki; ki = ko; ko = tk;
         uint32_t* tv = vi; vi = vo; vo = tv;
     }
