@@ -608,15 +608,25 @@ constexpr uint64_t kPerTileOrderLongShare = 64;     // at most 1 / this of the k
 constexpr uint64_t kPerTileOrderMaxKeys = 8u << 20;
 constexpr int64_t kPerTileOrderCapacity = 256;      // keys per tile, before any cell frame
 
-static bool per_tile_order(dgs_ctx c, int64_t tiles, bool cells) {
+// The load of the context's last cell frame.
+struct LastLoad {
+    uint64_t tiles, keys, long_keys;  // tiles 0: no such frame yet
+    // more of the keys in long runs than AUTO gives to the per-tile order
+    bool many_long() const { return kPerTileOrderLongShare * long_keys > keys; }
+};
+
+static LastLoad last_load(dgs_ctx c) {
+    const uint64_t load = __atomic_load_n(c->load_host, __ATOMIC_RELAXED);
+    const uint64_t lng = __atomic_load_n(c->load_host + 1, __ATOMIC_RELAXED);
+    return {load >> 32, load & 0xffffffffull, lng & 0xffffffffull};
+}
+
+static bool per_tile_order(dgs_ctx c, const LastLoad& l, int64_t tiles, bool cells) {
     if (c->list_order == DGS_LIST_ORDER_PER_TILE) return true;
     if (c->list_order == DGS_LIST_ORDER_GLOBAL) return false;
     if (!cells) return false;
-    const uint64_t load = __atomic_load_n(c->load_host, __ATOMIC_RELAXED);
-    const uint64_t lng = __atomic_load_n(c->load_host + 1, __ATOMIC_RELAXED);
-    const uint64_t lt = load >> 32, lk = load & 0xffffffffull, ll = lng & 0xffffffffull;
-    if (lt)
-        return lk <= (uint64_t)kPerTileOrderMaxMean * lt && kPerTileOrderLongShare * ll <= lk && lk <= kPerTileOrderMaxKeys;
+    if (l.tiles)
+        return l.keys <= (uint64_t)kPerTileOrderMaxMean * l.tiles && !l.many_long() && l.keys <= kPerTileOrderMaxKeys;
     return c->cap_keys <= kPerTileOrderCapacity * tiles;
 }
 
@@ -696,7 +706,8 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     // before the key emission, or, when the tile lists are short, a sort of
     // each tile's run after the tile sort (the same order); with the second
     // stream, the work queue is then built there beside the per-tile sort
-    const int chunks = per_tile_order(c, tiles, cells)
+    const LastLoad load = last_load(c);
+    const int chunks = per_tile_order(c, load, tiles, cells)
                            ? bin_chunks(P, k.TX, k.TY, 2 * c->cap_keys, c->sort_status_cap / 2)
                            : 0;
     const bool per_tile = chunks > 0;
@@ -768,8 +779,11 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
                                     c->misc + 2, c->dev_err, cells ? c->load_dev : nullptr});
         sm.mark(5);
         sm.mark(6);
-        // the same launch also builds the work queue
-        launch_tile_depth_sort(q, ranges, tiles, c->vals1, c->misc + 2, c->keys0, svals, c->keys1, save ? save->vals : nullptr,
+        // the same launch also builds the work queue.  With the order chosen by
+        // the caller, a frame (or a captured one) before any load is known may
+        // hold long runs
+        const bool many_long = load.many_long() || (!load.tiles && c->list_order == DGS_LIST_ORDER_PER_TILE);
+        launch_tile_depth_sort(q, ranges, tiles, c->vals1, c->misc + 2, many_long, c->keys0, svals, c->keys1, save ? save->vals : nullptr,
                                cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, work, bwork,
                                cells ? c->load_dev + 1 : nullptr, (uint32_t)P);
     } else {

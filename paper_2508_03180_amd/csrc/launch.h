@@ -119,10 +119,11 @@ struct WorkQueue {
 // Per-tile depth order: each tile's run of ent (depth bits << 32 | id) in
 // ascending order; the ids go to vals, and also to vcopy when set.  ent and
 // spare (a buffer of its size) are scratch; long_tiles, nlong as made by
-// launch_bin_tiles.  The same launch builds the
+// launch_bin_tiles.  many_long: many of the keys are expected in listed runs
+// (only the time depends on it).  The same launch builds the
 // work queues (as launch_tile_order; long_stat, prims too).
 void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, const uint32_t* long_tiles,
-                            const uint32_t* nlong, uint64_t* ent, uint32_t* vals,
+                            const uint32_t* nlong, bool many_long, uint64_t* ent, uint32_t* vals,
                             uint64_t* spare, uint32_t* vcopy, uint32_t split_len, const uint32_t* total,
                             const WorkQueue& fwd, const WorkQueue& bwd,
                             uint64_t* long_stat = nullptr, uint32_t prims = 0);

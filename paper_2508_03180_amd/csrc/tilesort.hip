@@ -28,13 +28,21 @@ namespace dgs {
 constexpr int kTsWaves = 4;
 constexpr int kTsThreads = 64 * kTsWaves;
 constexpr int kTsShort = 256;            // longest run one wavefront sorts
-constexpr int kTsChunk = 4 * kTsThreads;  // longest run the workgroup sorts in registers
+// Longest run that a workgroup of W wavefronts sorts in registers.
+constexpr int ts_chunk(int waves) { return waves == kTsWaves ? 4 * kTsThreads : 2 * 64 * waves; }
+constexpr int kTsChunk = ts_chunk(kTsWaves);
 // Workgroups that sort the listed longer runs, one run at a time: among the
 // others' four tiles, two such runs in one workgroup were the kernel's span
 // (1920 x 1080, 333,333 cells of 3 with a few runs of 3,600: frame 568 -> 503
 // us).  With runs from 1,024 on listed, and 256 workgroups, views with a
 // thousand of them waited here (large scene 685 -> 860 us, now 669).
 constexpr unsigned kTsLongGroups = 1024;
+// Frames with many keys in long runs (the per-tile order chosen by the caller) sort
+// the listed ones in a launch of their own, by workgroups of 16 wavefronts, in
+// about half the span a run has here: 2,000,000 single Gaussians as cells at 1920 x
+// 1080, 10.9 M keys, frame 2543 -> 1622 us; 6,000,000 cells at 320 x 180, 2.3 M
+// keys, 8918 -> 3603.  Where long runs are few the launch costs more than it gives.
+constexpr int kLongWaves = 16;
 
 __device__ __forceinline__ void put_sorted(uint32_t* vr, uint32_t* vcopy, int i, uint64_t v) {
     vr[i] = (uint32_t)v;
@@ -200,10 +208,13 @@ __device__ __forceinline__ void group_sort_run(uint64_t* sd, const uint64_t* __r
     }
 }
 
+// By a whole workgroup of W wavefronts, up to ts_chunk(W) entries.
+template <int W>
 __device__ __forceinline__ void group_sort_any(uint64_t* sd, const uint64_t* kr, uint32_t* vr, uint32_t* vc, uint64_t* out,
                                                int L, int tid) {
-    if (L <= 2 * kTsThreads) group_sort_run<2>(sd, kr, vr, vc, out, L, tid);
-    else group_sort_run<4>(sd, kr, vr, vc, out, L, tid);
+    constexpr int M = ts_chunk(W) / (64 * W);
+    if (L <= ts_chunk(W) / 2) group_sort_run<M / 2, W>(sd, kr, vr, vc, out, L, tid);
+    else group_sort_run<M, W>(sd, kr, vr, vc, out, L, tid);
 }
 
 // Number of entries of the ascending array y[0, n) below v.
@@ -217,20 +228,23 @@ __device__ __forceinline__ int count_below(const uint64_t* y, int n, uint64_t v)
     return lo;
 }
 
-// One run of more than kTsShort entries, by the whole workgroup (sd: its LDS).
+// One run of more than kTsShort entries, by the whole workgroup of W wavefronts
+// (sd: its LDS, ts_chunk(W) entries).
+template <int W>
 __device__ __forceinline__ void sort_long_run(uint64_t* sd, uint32_t s, int L,
                                               uint64_t* __restrict__ ent, uint32_t* __restrict__ vals,
                                               uint64_t* __restrict__ spare, uint32_t* __restrict__ vcopy, int tid) {
+    constexpr int kChunk = ts_chunk(W), kThreads = 64 * W;
     uint64_t* kr = ent + s;
     uint32_t* vr = vals + s;
     uint32_t* vc = vcopy ? vcopy + s : nullptr;
-    // A run of up to kTsChunk entries is one chunk sorted straight back into
+    // A run of up to kChunk entries is one chunk sorted straight back into
     // place; a longer one is sorted in chunks into the spare buffer, then
     // merged pairwise.  (One call site: the network is inlined once.)
-    const bool chunked = L > kTsChunk;
+    const bool chunked = L > kChunk;
     uint64_t* a = spare + s;
-    for (int c0 = 0; c0 < L; c0 += kTsChunk) {
-        group_sort_any(sd, kr + c0, vr + c0, vc, chunked ? a + c0 : nullptr, min(kTsChunk, L - c0), tid);
+    for (int c0 = 0; c0 < L; c0 += kChunk) {
+        group_sort_any<W>(sd, kr + c0, vr + c0, vc, chunked ? a + c0 : nullptr, min(kChunk, L - c0), tid);
         __syncthreads();  // sd is reused by the next chunk
     }
     if (!chunked) return;
@@ -238,8 +252,8 @@ __device__ __forceinline__ void sort_long_run(uint64_t* sd, uint32_t s, int L,
     __syncthreads();
     uint64_t* src = a;
     uint64_t* dst = kr;  // the run's own entries (every one has been read)
-    for (int w = kTsChunk; w < L; w <<= 1) {
-        for (int i = tid; i < L; i += kTsThreads) {
+    for (int w = kChunk; w < L; w <<= 1) {
+        for (int i = tid; i < L; i += kThreads) {
             const int x0 = (i / (2 * w)) * (2 * w), y0 = x0 + w;
             const uint64_t v = src[i];
             if (i < y0) {  // in the first run of the pair
@@ -255,7 +269,31 @@ __device__ __forceinline__ void sort_long_run(uint64_t* sd, uint32_t s, int L,
         src = dst;
         dst = t;
     }
-    for (int i = tid; i < L; i += kTsThreads) put_sorted(vr, vc, i, src[i]);
+    for (int i = tid; i < L; i += kThreads) put_sorted(vr, vc, i, src[i]);
+}
+
+// The listed runs, one at a time by a workgroup of W wavefronts, number `first`
+// of `groups`.
+template <int W>
+__device__ __forceinline__ void sort_listed_runs(uint64_t* sd, const uint32_t* __restrict__ ranges,
+                                                 const uint32_t* __restrict__ long_tiles, uint32_t n, uint32_t first,
+                                                 uint32_t groups, uint64_t* __restrict__ ent, uint32_t* __restrict__ vals,
+                                                 uint64_t* __restrict__ spare, uint32_t* __restrict__ vcopy, int tid) {
+#pragma unroll 1
+    for (uint32_t i = first; i < n; i += groups) {
+        const uint32_t t = long_tiles[i], s = ranges[2 * t];
+        sort_long_run<W>(sd, (uint32_t)__builtin_amdgcn_readfirstlane(s),
+                         __builtin_amdgcn_readfirstlane((int)(ranges[2 * t + 1] - s)), ent, vals, spare, vcopy, tid);
+        __syncthreads();  // sd is reused by the next run
+    }
+}
+
+__global__ __launch_bounds__(64 * kLongWaves) __attribute__((amdgpu_waves_per_eu(8))) void k_long_sort(
+    const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ long_tiles, const uint32_t* __restrict__ nlong,
+    uint64_t* __restrict__ ent, uint32_t* __restrict__ vals, uint64_t* __restrict__ spare, uint32_t* __restrict__ vcopy) {
+    __shared__ uint64_t sd[ts_chunk(kLongWaves)];
+    sort_listed_runs<kLongWaves>(sd, ranges, long_tiles, *nlong, blockIdx.x, gridDim.x, ent, vals, spare, vcopy,
+                                 (int)threadIdx.x);
 }
 
 // A workgroup's LDS: the work queue's counts and partial sums (order.h), or
@@ -285,14 +323,8 @@ __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8)))
     const int block = (int)blockIdx.x - queues;
     uint64_t* sd = reinterpret_cast<uint64_t*>(smem);
     if (block < long_groups) {
-        const uint32_t n = *nlong;
-#pragma unroll 1
-        for (uint32_t i = (uint32_t)block; i < n; i += (uint32_t)long_groups) {
-            const uint32_t t = long_tiles[i], s = ranges[2 * t];
-            sort_long_run(sd, (uint32_t)__builtin_amdgcn_readfirstlane(s),
-                          __builtin_amdgcn_readfirstlane((int)(ranges[2 * t + 1] - s)), ent, vals, spare, vcopy, tid);
-            __syncthreads();  // sd is reused by the next run
-        }
+        sort_listed_runs<kTsWaves>(sd, ranges, long_tiles, *nlong, (uint32_t)block, (uint32_t)long_groups, ent, vals, spare,
+                                   vcopy, tid);
         return;
     }
     const int G = (int)gridDim.x - queues - long_groups, sb = block - long_groups;
@@ -326,17 +358,22 @@ __global__ __launch_bounds__(kTsThreads) __attribute__((amdgpu_waves_per_eu(8)))
     for (int i = 0; i < kTsWaves; i++) {
         const int len = __builtin_amdgcn_readfirstlane(lt_len[i]);
         if (len <= kTsShort || len > (int)kLongRun) continue;
-        sort_long_run(sd, (uint32_t)__builtin_amdgcn_readfirstlane(lt_s[i]), len, ent, vals, spare, vcopy, tid);
+        sort_long_run<kTsWaves>(sd, (uint32_t)__builtin_amdgcn_readfirstlane(lt_s[i]), len, ent, vals, spare, vcopy, tid);
         __syncthreads();  // sd is reused by the next run
     }
 }
 
 void launch_tile_depth_sort(hipStream_t st, const uint32_t* ranges, int tiles, const uint32_t* long_tiles,
-                            const uint32_t* nlong, uint64_t* ent, uint32_t* vals, uint64_t* spare, uint32_t* vcopy,
-                            uint32_t split_len, const uint32_t* total, const WorkQueue& fwd, const WorkQueue& bwd,
-                            uint64_t* long_stat, uint32_t prims) {
+                            const uint32_t* nlong, bool many_long, uint64_t* ent, uint32_t* vals, uint64_t* spare,
+                            uint32_t* vcopy, uint32_t split_len, const uint32_t* total, const WorkQueue& fwd,
+                            const WorkQueue& bwd, uint64_t* long_stat, uint32_t prims) {
     if (tiles <= 0) return;
-    const unsigned lg = (unsigned)tiles < kTsLongGroups ? (unsigned)tiles : kTsLongGroups;
+    unsigned lg = (unsigned)tiles < kTsLongGroups ? (unsigned)tiles : kTsLongGroups;
+    if (many_long) {
+        hipLaunchKernelGGL(k_long_sort, dim3(lg), dim3(64 * kLongWaves), 0, st, ranges, long_tiles, nlong, ent, vals, spare,
+                           vcopy);
+        lg = 0;
+    }
     // + the work queues', the long runs'
     const unsigned grid = (unsigned)((tiles + kTsWaves - 1) / kTsWaves) + (bwd.queue ? 2 : 1) + lg;
     hipLaunchKernelGGL(k_tile_sort, dim3(grid), dim3(kTsThreads), 0, st, ranges, tiles, long_tiles, nlong, (int)lg, ent, vals, spare, vcopy,
