@@ -200,7 +200,8 @@ dgs_status dgs_set_overlap(dgs_ctx ctx, int32_t enable);
  *   DGS_LIST_ORDER_PER_TILE: the entries are counted into their tiles' runs
  *     and each run is then sorted by (depth, id) on its own (fast when the
  *     lists are short; a grid of tiles too large for the counters -- beyond
- *     about 131,000 tiles -- takes the global way);
+ *     about 131,000 tiles -- or a key buffer too small to hold them for the
+ *     number of primitives takes the global way);
  *   DGS_LIST_ORDER_AUTO (default): per tile for per-cell lists (Duplex,
  *     LC-WSR) when the context's last such frame had at most 1024 keys per
  *     screen tile on average, at most 1/64 of its keys in tile runs of

@@ -48,13 +48,24 @@ constexpr int kBinSpinLimit = 1 << 22;
 
 static int band_rows(int TY) { return (TY + kBinBands - 1) / kBinBands; }
 
+// With c chunks the counting takes about 2.1 ns x P / c longer than with many,
+// the global way 32 us + 0.05 ns x P: it is the faster one beyond
+// P (kFewChunks - c) = kFewChunks kFewChunkPrims c, and never from kFewChunks on.
+// Mostly culled cells at 3840 x 2160 in a tight key buffer, per tile / global
+// us: 100,000 in 8, 4 and 1 chunks 291 / 313, 318 / 308 and 481 / 307; 300,000 in
+// 32, 16 and 1 293 / 312, 311 / 310 and 916 / 310; 1 M in 32 and 16 358 / 376 and
+// 427 / 376; 3 M in 64 and 32 456 / 537 and 549 / 531.
+constexpr int64_t kFewChunks = 42, kFewChunkPrims = 15000;
+
 // Chunks of primitives: one per kBinPerChunk of them up to kBinMaxChunks, and
-// no more than `words` counters hold; 0: this grid takes the radix sort.
+// no more than `words` counters hold; 0: this grid, or these primitives with
+// so few counters, take the radix sort.
 int bin_chunks(int64_t P, int TX, int TY, int64_t words, size_t status_words) {
     const int64_t tiles = (int64_t)TX * TY, local = (int64_t)TX * band_rows(TY);
     if (P <= 0 || local > kBinMaxLocal || (size_t)((tiles + kBinScanTiles - 1) / kBinScanTiles) > status_words) return 0;
-    const int64_t c = std::min<int64_t>((P + kBinPerChunk - 1) / kBinPerChunk, kBinMaxChunks);
-    return (int)std::min(c, words / (kBinBands * local));
+    const int64_t most = std::min<int64_t>((P + kBinPerChunk - 1) / kBinPerChunk, kBinMaxChunks);
+    const int64_t c = std::min(most, words / (kBinBands * local));
+    return P * (kFewChunks - c) > kFewChunks * kFewChunkPrims * c ? 0 : (int)c;
 }
 
 // Calls f(slot, payload) for every tile of the band that each lane's

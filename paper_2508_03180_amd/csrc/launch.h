@@ -105,7 +105,8 @@ struct BinArgs {
 constexpr uint32_t kLongRun = 2048;
 // Chunks of primitives the counting works in, for P primitives on a grid of
 // TX x TY tiles with `words` 32-bit counters and `status_words` look-back
-// words at hand; 0 when the grid is too large for the counting.
+// words at hand; 0 when the grid is too large for the counting, or the
+// counters too few for the primitives.
 int bin_chunks(int64_t P, int TX, int TY, int64_t words, size_t status_words);
 void launch_bin_tiles(hipStream_t st, const BinArgs& a);
 
