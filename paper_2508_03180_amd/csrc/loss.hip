@@ -22,7 +22,8 @@
 //               blur is the same blur);
 //   loss_sum    the strip sums in a fixed order -> L (binary64, stored as
 //               binary32): the result does not depend on scheduling.  One more
-//               workgroup of the backward pass; a launch of its own without one.
+//               workgroup of the backward pass; a launch of its own (k_loss_sum)
+//               without one.
 // The rows are unrolled by 11, the period of the register rings (unrolled
 // whole, 42 rows were more code than the instruction cache holds).  The
 // forward is bound by its VALU work (237 instructions a row, of them 110
@@ -104,7 +105,15 @@ struct Strip {
         : c(t / (a.nx * a.ny)), c0(t % a.nx * kStrip), r0(t / a.nx % a.ny * a.rows) {}
 };
 
-// The strip sums, by one wavefront in a fixed order, then L.
+// L from one wavefront's sums of the strips' (lane i: strips i, i + 64, ... in
+// that order).
+__device__ __forceinline__ void store_loss(const LossArgs& a, double s, double l, int lane) {
+    s = wave_sum(s);
+    l = wave_sum(l);
+    if (lane == 0) *a.loss = (float)((1.0 - a.lam) * l / a.n + a.lam * (1.0 - s / a.n));
+}
+
+// The strip sums by one wavefront, then L: beside the strips of the backward.
 __device__ void loss_sum(const LossArgs& a, int strips, int lane) {
     double s = 0.0, l = 0.0;
     const double2* part = reinterpret_cast<const double2*>(a.part);
@@ -114,9 +123,7 @@ __device__ void loss_sum(const LossArgs& a, int strips, int lane) {
         s += p.x;
         l += p.y;
     }
-    s = wave_sum(s);
-    l = wave_sum(l);
-    if (lane == 0) *a.loss = (float)((1.0 - a.lam) * l / a.n + a.lam * (1.0 - s / a.n));
+    store_loss(a, s, l, lane);
 }
 
 template <bool GRAD>
@@ -285,20 +292,49 @@ __global__ __launch_bounds__(64) void k_ssim_bwd(LossArgs a, Window w) {
     }
 }
 
-__global__ __launch_bounds__(64) void k_loss_sum(LossArgs a, int strips) { loss_sum(a, strips, (int)threadIdx.x); }
+// The same sums, in the same order, where nothing runs beside them: 16 wavefronts
+// bring the strips' sums to LDS, 4096 at a time.  (One wavefront with
+// eight loads in flight took 3 us more for 3 x 1920 x 1080.)
+constexpr int kSumThreads = 1024, kSumItems = 4;
+__global__ __launch_bounds__(kSumThreads) void k_loss_sum(LossArgs a, int strips) {
+    __shared__ double2 buf[kSumThreads * kSumItems];
+    const int tid = threadIdx.x;
+    const double2* part = reinterpret_cast<const double2*>(a.part);
+    double s = 0.0, l = 0.0;
+    for (int t0 = 0; t0 < strips; t0 += kSumThreads * kSumItems) {
+        const int n = min(strips - t0, kSumThreads * kSumItems);
+        double2 p[kSumItems];
+#pragma unroll
+        for (int i = 0; i < kSumItems; i++) p[i] = part[t0 + min(tid + i * kSumThreads, n - 1)];
+#pragma unroll
+        for (int i = 0; i < kSumItems; i++) buf[tid + i * kSumThreads] = p[i];
+        __syncthreads();
+        if (tid < 64)
+#pragma unroll 4
+            for (int t = tid; t < n; t += 64) {
+                s += buf[t].x;
+                l += buf[t].y;
+            }
+        __syncthreads();  // buf is written again
+    }
+    if (tid < 64) store_loss(a, s, l, tid);
+}
 
 // Output rows of a strip, 11 k + 1 (with the 10 rows of its window a whole
 // number of ring periods): the least (strips per SIMD + 2) x (rows + 10).  A
 // row takes a wavefront about as long alone as two more strips on its SIMD
 // add: 3 x 1600 x 1200 with its gradient takes 80, 87, 89 and 119 us in 23,
-// 34, 45 and 67 rows, 4, 3, 2 and 2 strips per SIMD.
+// 34, 45 and 67 rows, 4, 3, 2 and 2 strips per SIMD.  Of equal ones the most
+// rows, which read least: 3 x 1920 x 1080 in 12 and 34 rows (cost 220 both) 98 and
+// 86 us with the gradient, 55 and 44 without; 3 x 2560 x 1440 in 23 and 45 140 and
+// 133.
 int strip_rows(int64_t columns, int H) {
     int best = 12;
     double least = INFINITY;
     for (int rows = 12; rows <= 67; rows += kTaps) {
         const int64_t strips = columns * ((H + rows - 1) / rows), per = (strips + kSimds - 1) / kSimds;
         const double cost = (double)(per + 2) * (rows + 2 * kRad);
-        if (cost < least) {
+        if (cost <= least) {
             least = cost;
             best = rows;
         }
@@ -386,7 +422,7 @@ dgs_status dgs_loss_l1_ssim(dgs_ctx c, const float* image, const float* target, 
         hipLaunchKernelGGL(k_ssim_bwd, dim3((unsigned)strips + 1), block, 0, c->stream, a, w);
     } else {
         hipLaunchKernelGGL(k_ssim_fwd<false>, grid, block, 0, c->stream, a, w);
-        hipLaunchKernelGGL(k_loss_sum, dim3(1), block, 0, c->stream, a, (int)strips);
+        hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(kSumThreads), 0, c->stream, a, (int)strips);
     }
     e = hipGetLastError();
     if (e != hipSuccess) {
