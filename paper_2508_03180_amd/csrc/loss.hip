@@ -126,6 +126,12 @@ __device__ void loss_sum(const LossArgs& a, int strips, int lane) {
     store_loss(a, s, l, lane);
 }
 
+// a / b from i = 1 / b: the product corrected by its remainder.
+__device__ __forceinline__ float quotient(float a, float b, float i) {
+    const float q = a * i;
+    return fmaf(fmaf(-q, b, a), i, q);
+}
+
 template <bool GRAD>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_ssim_fwd(LossArgs a, Window w) {
     __shared__ float bx[kRowBuf], by[kRowBuf];
@@ -203,13 +209,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 // S = a1 a2 / (b1 b2): d/d mu_x through a1 (2 mu_y), a2 (-2 mu_y),
                 // b1 (2 mu_x), b2 (-2 mu_x); d/d E[x^2] through b2; d/d E[xy] through a2
                 // (with a2 from S cancelled against the division by a2, so that
-                // only b1, b2 >= c1, c2 are divided by)
+                // only b1, b2 >= c1, c2 are divided by).  Where x is near y the terms
+                // cancel, and what is left of the larger 1 / b2 must be exact: a
+                // quotient of equal numbers is 1, S the product of the two, and
+                // no product is fused with the sum of it and its negative.
+#pragma clang fp contract(off)
                 const float i1 = 1.0f / b1, i2 = 1.0f / b2;
-                const float ds = a.dls * sv, q = 2.0f * a.dls * (i1 * i2);
+                const float q1 = quotient(a1, b1, i1), q2 = quotient(a2, b2, i2), s = q1 * q2;
                 const size_t p = st.c * plane + (size_t)gy * a.W + gx;
-                a.coef[p] = q * my * (a2 - a1) + 2.0f * mx * ds * (i2 - i1);
-                a.coef[n + p] = -ds * i2;
-                a.coef[2 * n + p] = q * a1;
+                a.coef[p] = 2.0f * a.dls * (i1 * (my * q2 - mx * s) - i2 * (my * q1 - mx * s));
+                a.coef[n + p] = -(a.dls * s) * i2;
+                a.coef[2 * n + p] = 2.0f * (a.dls * q1 * i2);
             }
         }
     }
