@@ -608,25 +608,21 @@ constexpr uint64_t kPerTileOrderLongShare = 64;     // at most 1 / this of the k
 constexpr uint64_t kPerTileOrderMaxKeys = 8u << 20;
 constexpr int64_t kPerTileOrderCapacity = 256;      // keys per tile, before any cell frame
 
-// The load of the context's last cell frame.
-struct LastLoad {
-    uint64_t tiles, keys, long_keys;  // tiles 0: no such frame yet
-    // more of the keys in long runs than AUTO gives to the per-tile order
-    bool many_long() const { return kPerTileOrderLongShare * long_keys > keys; }
-};
-
-static LastLoad last_load(dgs_ctx c) {
+FrameLoad dgs_internal_load(dgs_ctx c) {
     const uint64_t load = __atomic_load_n(c->load_host, __ATOMIC_RELAXED);
     const uint64_t lng = __atomic_load_n(c->load_host + 1, __ATOMIC_RELAXED);
     return {load >> 32, load & 0xffffffffull, lng & 0xffffffffull};
 }
 
-static bool per_tile_order(dgs_ctx c, const LastLoad& l, int64_t tiles, bool cells) {
+// More of the keys in long runs than AUTO gives to the per-tile order.
+static bool many_long_runs(const FrameLoad& l) { return kPerTileOrderLongShare * l.long_keys > l.keys; }
+
+bool dgs_internal_per_tile(dgs_ctx c, const FrameLoad& l, int64_t tiles, bool cells) {
     if (c->list_order == DGS_LIST_ORDER_PER_TILE) return true;
     if (c->list_order == DGS_LIST_ORDER_GLOBAL) return false;
     if (!cells) return false;
     if (l.tiles)
-        return l.keys <= (uint64_t)kPerTileOrderMaxMean * l.tiles && !l.many_long() && l.keys <= kPerTileOrderMaxKeys;
+        return l.keys <= (uint64_t)kPerTileOrderMaxMean * l.tiles && !many_long_runs(l) && l.keys <= kPerTileOrderMaxKeys;
     return c->cap_keys <= kPerTileOrderCapacity * tiles;
 }
 
@@ -681,7 +677,8 @@ static bool ensure_aux(dgs_ctx c) {
 // written to the context's device FrameK by the first kernel; without it the
 // caller has put them there (a captured graph replayed for a new camera).
 dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* cam, const dgs_render_opts* opts,
-                               const dgs_image* out, bool write_frame, const NeuralSrc* nn, dgs_frame_s* save) {
+                               const dgs_image* out, bool write_frame, const NeuralSrc* nn, dgs_frame_s* save,
+                               const FrameLoad* expect) {
     if (!c) return DGS_ERR_INVALID_ARG;
     CamK k;
     OptK o;
@@ -706,8 +703,8 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     // before the key emission, or, when the tile lists are short, a sort of
     // each tile's run after the tile sort (the same order); with the second
     // stream, the work queue is then built there beside the per-tile sort
-    const LastLoad load = last_load(c);
-    const int chunks = per_tile_order(c, load, tiles, cells)
+    const FrameLoad load = expect ? *expect : dgs_internal_load(c);
+    const int chunks = dgs_internal_per_tile(c, load, tiles, cells)
                            ? bin_chunks(P, k.TX, k.TY, 2 * c->cap_keys, c->sort_status_cap / 2)
                            : 0;
     const bool per_tile = chunks > 0;
@@ -782,7 +779,7 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
         // the same launch also builds the work queue.  With the order chosen by
         // the caller, a frame (or a captured one) before any load is known may
         // hold long runs
-        const bool many_long = load.many_long() || (!load.tiles && c->list_order == DGS_LIST_ORDER_PER_TILE);
+        const bool many_long = many_long_runs(load) || (!load.tiles && c->list_order == DGS_LIST_ORDER_PER_TILE);
         launch_tile_depth_sort(q, ranges, tiles, c->vals1, c->misc + 2, many_long, c->keys0, svals, c->keys1, save ? save->vals : nullptr,
                                cells ? kSplitLenCells : kSplitLenGauss, c->misc + 0, work, bwork,
                                cells ? c->load_dev + 1 : nullptr, (uint32_t)P);

@@ -137,6 +137,14 @@ int64_t dgs_internal_default_keys(int64_t prims);
 // Frees the context's workspace (capacities drop to zero); synchronises.
 void dgs_internal_release(dgs_ctx c);
 
+// The load of a cell frame, as the device reports it (load_host).
+struct FrameLoad {
+    uint64_t tiles = 0, keys = 0, long_keys = 0;  // tiles 0: no such frame yet
+};
+FrameLoad dgs_internal_load(dgs_ctx c);  // of the context's last one
+// Whether a frame takes the per-tile list order, by a load that it may expect.
+bool dgs_internal_per_tile(dgs_ctx c, const FrameLoad& l, int64_t tiles, bool cells);
+
 // The frame pipeline behind dgs_render.  With write_frame the camera,
 // options and output pointers are written to ctx->frame by the first kernel;
 // without it the caller has put them there (a captured frame replayed for a
@@ -148,10 +156,11 @@ struct NeuralSrc {
     const dgs_neural_scene* scene;
     const dgs_decoder* decoder;
 };
-// With save set (Duplex only), the frame's replay state goes into *save.
+// With save set (Duplex only), the frame's replay state goes into *save.  load:
+// the load the frame may expect (null: the context's last one).
 dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* cam, const dgs_render_opts* opts,
                                const dgs_image* out, bool write_frame, const NeuralSrc* nn = nullptr,
-                               dgs_frame_s* save = nullptr);
+                               dgs_frame_s* save = nullptr, const FrameLoad* load = nullptr);
 
 // Validates camera, options and output and builds the frame record; *mode
 // receives the render mode.  c may be a host-only context (errors land in c->err).

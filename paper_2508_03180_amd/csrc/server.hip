@@ -8,7 +8,9 @@
 // workspace back when the head of the queue needs the room.  With graphs on,
 // each (scene, image size, mode, statistics flag) is captured once per slot
 // into a HIP graph; later requests copy their camera, options and output
-// pointers into the slot's device frame record and replay the graph.  A
+// pointers into the slot's device frame record and replay the graph.  (Once
+// for each list order that its frames take: a graph keeps the order it was
+// captured with, so the choice is made again before every frame.)  A
 // frame that overflows its key capacity is re-queued at the front after the
 // slot grows to the count the device reported.
 #include <math.h>
@@ -91,11 +93,24 @@ class DeviceExecutor final : public Executor {
             uint64_t generation;
             hipGraphExec_t exec;
         };
-        std::map<ShapeKey, Graph> graphs;
+        std::map<std::pair<ShapeKey, bool>, Graph> graphs;  // by shape and list order (true: per tile)
+        std::map<ShapeKey, FrameLoad> loads;                // of each shape's last cell frame here
+        ShapeKey shape{};                                   // the running frame's
     };
     int device_;
     bool graphs_;
     std::vector<Slot> slots_;
+
+    // The load that a frame may expect: its shape's last one in this slot, else
+    // whatever the slot drew last.
+    static FrameLoad expected_load(const Slot& s, const ShapeKey& k) {
+        auto it = s.loads.find(k);
+        return it != s.loads.end() ? it->second : dgs_internal_load(s.ctx);
+    }
+    static bool per_tile(const Slot& s, const ShapeKey& k, const FrameLoad& l) {
+        const int64_t tiles = (int64_t)((k.width + kTile - 1) / kTile) * ((k.height + kTile - 1) / kTile);
+        return dgs_internal_per_tile(s.ctx, l, tiles, k.mode != DGS_MODE_ALPHA);
+    }
 
     void drop_graphs(Slot& s) {
         for (auto& g : s.graphs) hipGraphExecDestroy(g.second.exec);
@@ -146,8 +161,9 @@ public:
     int num_slots() const override { return (int)slots_.size(); }
     WorkspaceCaps caps(int slot) const override { return dgs_internal_caps(slots_[slot].ctx); }
     bool has_graph(int slot, const ShapeKey& k) const override {
-        auto it = slots_[slot].graphs.find(k);
-        return it != slots_[slot].graphs.end() && it->second.generation == slots_[slot].ctx->generation;
+        const Slot& s = slots_[slot];
+        auto it = s.graphs.find({k, per_tile(s, k, expected_load(s, k))});
+        return it != s.graphs.end() && it->second.generation == s.ctx->generation;
     }
 
     dgs_status launch(int slot, const dgs_scene& sc, Request& r, const WorkspaceCaps& want, int* graph,
@@ -160,8 +176,11 @@ public:
             err = dgs_last_error(s.ctx);
             return st;
         }
+        s.shape = r.shape;
+        const FrameLoad load = expected_load(s, r.shape);
         if (graphs_) {
-            auto it = s.graphs.find(r.shape);
+            const std::pair<ShapeKey, bool> key{r.shape, per_tile(s, r.shape, load)};
+            auto it = s.graphs.find(key);
             if (it != s.graphs.end() && it->second.generation != s.ctx->generation) {
                 hipGraphExecDestroy(it->second.exec);
                 s.graphs.erase(it);
@@ -173,7 +192,7 @@ public:
                     err = "graph capture could not start";
                     return DGS_ERR_DEVICE;
                 }
-                st = dgs_internal_render(s.ctx, &sc, &r.cam, &r.opts, &r.out, false);
+                st = dgs_internal_render(s.ctx, &sc, &r.cam, &r.opts, &r.out, false, nullptr, nullptr, &load);
                 hipError_t e = hipStreamEndCapture(s.stream, &g);
                 if (st != DGS_OK || e != hipSuccess) {
                     if (g) hipGraphDestroy(g);
@@ -187,7 +206,7 @@ public:
                     err = "graph instantiation failed";
                     return DGS_ERR_DEVICE;
                 }
-                it = s.graphs.emplace(r.shape, Slot::Graph{s.ctx->generation, ex}).first;
+                it = s.graphs.emplace(key, Slot::Graph{s.ctx->generation, ex}).first;
                 *graph = 2;
             } else {
                 *graph = 1;
@@ -200,7 +219,7 @@ public:
                 return DGS_ERR_DEVICE;
             }
         } else {
-            st = dgs_internal_render(s.ctx, &sc, &r.cam, &r.opts, &r.out, true);
+            st = dgs_internal_render(s.ctx, &sc, &r.cam, &r.opts, &r.out, true, nullptr, nullptr, &load);
             if (st != DGS_OK) {
                 err = dgs_last_error(s.ctx);
                 return st;
@@ -232,6 +251,7 @@ public:
             err = "frame failed on the device";
             return DGS_ERR_DEVICE;
         }
+        if (s.shape.mode != DGS_MODE_ALPHA) s.loads[s.shape] = dgs_internal_load(s.ctx);
         if (bits) {
             hipMemsetAsync(s.ctx->dev_err, 0, sizeof(int), s.stream);
             hipStreamSynchronize(s.stream);
