@@ -37,7 +37,8 @@ namespace dgs {
 
 constexpr int kDecodeWaves = 4, kDecodeThreads = 64 * kDecodeWaves;
 constexpr int kDecodeSlots = 20;          // outputs per cell of the LDS buffer, at most
-constexpr size_t kDecodeLds = 64 * 1024;  // LDS of a workgroup, at most
+constexpr size_t kVoteLds = 256;                     // of __syncthreads_or
+constexpr size_t kDecodeLds = 64 * 1024 - kVoteLds;  // dynamic LDS: 64 KB in all, at most
 
 // Orders a wavefront's own LDS accesses: its lanes exchange values through it.
 __device__ __forceinline__ void wave_order() {
