@@ -31,8 +31,7 @@ hipError_t grow(T*& p, int64_t want, hipStream_t st) {
     return hipMalloc((void**)&p, sizeof(T) * (size_t)(want > 0 ? want : 1));
 }
 
-// Look-back status buffers start zeroed (epoch 0 is never used).  The
-// zeroing is a fill kernel on the context's stream, ordered before the
+// Look-back words start zeroed (epoch 0 is never used).  The zeroing is a fill kernel on the context's stream, ordered before the
 // frames that use the buffer: a null-stream memset is not ordered with a
 // non-blocking stream and could erase status words in the middle of a sort.
 hipError_t grow_zeroed(uint64_t*& p, int64_t want, hipStream_t st) {
@@ -60,11 +59,8 @@ dgs_status ensure(dgs_ctx c, int64_t prims, int64_t gauss, int64_t keys, int64_t
         if ((e = grow(c->pk1, nc.prims, c->stream)) != hipSuccess) goto oom;
         if ((e = grow(c->pv0, nc.prims, c->stream)) != hipSuccess) goto oom;
         if ((e = grow(c->pv1, nc.prims, c->stream)) != hipSuccess) goto oom;
-        size_t sw = scan_status_words(nc.prims);
-        if ((e = grow_zeroed(c->scan_status, (int64_t)sw, c->stream)) != hipSuccess) goto oom;
-        c->scan_status_cap = sw;
-        if ((e = grow_zeroed(c->psort_status, (int64_t)sort_status_words(nc.prims), c->stream)) != hipSuccess)
-            goto oom;
+        if ((e = grow(c->scan_status, (int64_t)scan_status_words(nc.prims), c->stream)) != hipSuccess) goto oom;
+        if ((e = grow(c->psort_status, (int64_t)sort_status_words(nc.prims), c->stream)) != hipSuccess) goto oom;
         c->cap_prims = nc.prims;
     }
     if (nc.gauss != cur.gauss) {
@@ -355,7 +351,7 @@ void dgs_internal_release(dgs_ctx c) {
         *p = nullptr;
     }
     c->cap_prims = c->cap_gauss = c->cap_keys = c->cap_tiles = 0;
-    c->scan_status_cap = c->sort_status_cap = 0;
+    c->sort_status_cap = 0;
     c->last_mode = -1;
     c->cur_ranges = nullptr;
     c->generation++;
@@ -413,7 +409,7 @@ dgs_status dgs_create(int device, void* hip_stream, dgs_ctx* out) {
     dgs_ctx c = new dgs_ctx_s();
     c->device = device;
     c->stream = (hipStream_t)hip_stream;
-    if (hipMalloc((void**)&c->hist, 8 * 256 * sizeof(uint32_t)) != hipSuccess ||
+    if (hipMalloc((void**)&c->hist, 256 * sizeof(uint32_t)) != hipSuccess ||
         hipMalloc((void**)&c->misc, 16 * sizeof(uint32_t)) != hipSuccess ||
         hipMalloc((void**)&c->dev_err, sizeof(int)) != hipSuccess ||
         hipMalloc((void**)&c->counters, 5 * sizeof(unsigned long long)) != hipSuccess ||

@@ -73,7 +73,7 @@ struct dgs_ctx_s {
     uint32_t *p_depth = nullptr, *p_ntiles = nullptr, *p_offsets = nullptr;
     uint64_t* p_rect = nullptr;
     uint32_t *pk0 = nullptr, *pk1 = nullptr, *pv0 = nullptr, *pv1 = nullptr;  // depth sort of the primitives
-    uint64_t* psort_status = nullptr;  // digit counts of the depth sort
+    uint64_t* psort_status = nullptr;  // digit counts of the depth sort (32-bit: they take half)
     float* cell_v = nullptr;
     dgs::GRec* recs = nullptr;
     uint64_t* grect = nullptr;
@@ -82,7 +82,6 @@ struct dgs_ctx_s {
     uint32_t* ranges = nullptr;
     uint32_t* tile_order = nullptr;
     uint64_t* scan_status = nullptr;  // key offsets of blocks of primitives
-    size_t scan_status_cap = 0;
     uint64_t* sort_status = nullptr;  // lower half: the tile lists' look-back words; upper: digit counts of the key sort
     size_t sort_status_cap = 0;
     dgs::FrameK* frame = nullptr;  // device copy of the current frame's camera and options
