@@ -67,7 +67,7 @@ public:
     virtual int num_slots() const = 0;
     virtual WorkspaceCaps caps(int slot) const = 0;
     // True when the slot holds a valid captured frame for this shape.
-    virtual bool has_graph(int slot, const ShapeKey& k) const = 0;
+    virtual bool has_graph(int slot, const ShapeKey& k, const dgs_scene& s) const = 0;
     // Starts the frame (asynchronously); *graph = 1 replayed, 2 captured, 0 none.
     virtual dgs_status launch(int slot, const dgs_scene& s, Request& r, const WorkspaceCaps& want, int* graph,
                               std::string& err) = 0;
@@ -94,22 +94,24 @@ class DeviceExecutor final : public Executor {
             hipGraphExec_t exec;
         };
         std::map<std::pair<ShapeKey, bool>, Graph> graphs;  // by shape and list order (true: per tile)
-        std::map<ShapeKey, FrameLoad> loads;                // of each shape's last cell frame here
         ShapeKey shape{};                                   // the running frame's
     };
     int device_;
     bool graphs_;
     std::vector<Slot> slots_;
+    std::map<ShapeKey, FrameLoad> loads_;  // of each shape's last cell frame, in any slot
 
-    // The load that a frame may expect: its shape's last one in this slot, else
-    // whatever the slot drew last.
-    static FrameLoad expected_load(const Slot& s, const ShapeKey& k) {
-        auto it = s.loads.find(k);
-        return it != s.loads.end() ? it->second : dgs_internal_load(s.ctx);
+    static int64_t tile_count(const ShapeKey& k) {
+        return (int64_t)((k.width + kTile - 1) / kTile) * ((k.height + kTile - 1) / kTile);
+    }
+    // The load that a frame may expect: its shape's last one; before there is
+    // one, a key per cell (of `cells`) and no long runs.
+    FrameLoad expected_load(const ShapeKey& k, int cells) const {
+        auto it = loads_.find(k);
+        return it != loads_.end() ? it->second : FrameLoad{(uint64_t)tile_count(k), (uint64_t)cells, 0};
     }
     static bool per_tile(const Slot& s, const ShapeKey& k, const FrameLoad& l) {
-        const int64_t tiles = (int64_t)((k.width + kTile - 1) / kTile) * ((k.height + kTile - 1) / kTile);
-        return dgs_internal_per_tile(s.ctx, l, tiles, k.mode != DGS_MODE_ALPHA);
+        return dgs_internal_per_tile(s.ctx, l, tile_count(k), k.mode != DGS_MODE_ALPHA);
     }
 
     void drop_graphs(Slot& s) {
@@ -160,9 +162,9 @@ public:
 
     int num_slots() const override { return (int)slots_.size(); }
     WorkspaceCaps caps(int slot) const override { return dgs_internal_caps(slots_[slot].ctx); }
-    bool has_graph(int slot, const ShapeKey& k) const override {
+    bool has_graph(int slot, const ShapeKey& k, const dgs_scene& sc) const override {
         const Slot& s = slots_[slot];
-        auto it = s.graphs.find({k, per_tile(s, k, expected_load(s, k))});
+        auto it = s.graphs.find({k, per_tile(s, k, expected_load(k, sc.num_cells))});
         return it != s.graphs.end() && it->second.generation == s.ctx->generation;
     }
 
@@ -177,7 +179,7 @@ public:
             return st;
         }
         s.shape = r.shape;
-        const FrameLoad load = expected_load(s, r.shape);
+        const FrameLoad load = expected_load(r.shape, sc.num_cells);
         if (graphs_) {
             const std::pair<ShapeKey, bool> key{r.shape, per_tile(s, r.shape, load)};
             auto it = s.graphs.find(key);
@@ -251,7 +253,7 @@ public:
             err = "frame failed on the device";
             return DGS_ERR_DEVICE;
         }
-        if (s.shape.mode != DGS_MODE_ALPHA) s.loads[s.shape] = dgs_internal_load(s.ctx);
+        if (s.shape.mode != DGS_MODE_ALPHA) loads_[s.shape] = dgs_internal_load(s.ctx);
         if (bits) {
             hipMemsetAsync(s.ctx->dev_err, 0, sizeof(int), s.stream);
             hipStreamSynchronize(s.stream);
@@ -298,7 +300,9 @@ public:
     SimExecutor(const dgs_sim_device& sim, int n, bool graphs) : sim_(sim), graphs_(graphs), slots_(n) {}
     int num_slots() const override { return (int)slots_.size(); }
     WorkspaceCaps caps(int slot) const override { return slots_[slot].caps; }
-    bool has_graph(int slot, const ShapeKey& k) const override { return slots_[slot].graphs.count(k) != 0; }
+    bool has_graph(int slot, const ShapeKey& k, const dgs_scene&) const override {
+        return slots_[slot].graphs.count(k) != 0;
+    }
 
     dgs_status launch(int slot, const dgs_scene&, Request& r, const WorkspaceCaps& want, int* graph,
                       std::string&) override {
@@ -397,7 +401,7 @@ struct dgs_server_s {
                 const WorkspaceCaps c = ex->caps(s);
                 const int64_t delta = dgs_internal_bytes(dgs_internal_plan(c, w)) - dgs_internal_bytes(c);
                 // prefer no growth, then a slot that can replay this shape
-                const bool replay = delta == 0 && ex->has_graph(s, r.shape);
+                const bool replay = delta == 0 && ex->has_graph(s, r.shape, scenes[(size_t)r.scene]);
                 if (best < 0 || delta < best_delta || (delta == best_delta && replay && !best_graph)) {
                     best = s;
                     best_delta = delta;
