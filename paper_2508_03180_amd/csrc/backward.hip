@@ -374,7 +374,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const uint32_t nitems = a.queue[1];
     ItemSource src;
     // as in the forward: the item's number in a scalar register
-    uint32_t t = __builtin_amdgcn_readfirstlane(first_item<kBwdWaves, kBwdWaves>(wave, nitems, src));
+    uint32_t t = __builtin_amdgcn_readfirstlane(first_item_packed<kBwdWaves>(wave, nitems, src));
     if constexpr (TICKETS) t = first_ticket(a.queue, src, lane);
     for (; t < nitems; t = next_item(a.queue, src, lane)) {
         const uint32_t item = a.order[t];
@@ -677,8 +677,10 @@ void launch_composite_bwd(hipStream_t st, const BwdArgs& a) {
     if (tiles <= 0) return;
     const int waves = 4 * tiles < 256 * 4 * 4 ? 4 * tiles : 256 * 4 * 4;
     const dim3 g((waves + kBwdWaves - 1) / kBwdWaves), b(256);
-    // from here on there can be more items (two a tile) than wavefronts
-    const bool tickets = 2 * tiles > waves;
+    // by the most items there can be, two a tile: at 960 x 540 (4080) 384 us by
+    // ticket and 417 without, at 800 x 450 (2850) 720 and 704, at 640 x 360 (1840)
+    // 477 and 461
+    const bool tickets = 2 * tiles > 3072;
     if (a.offs && tickets) hipLaunchKernelGGL((k_composite_bwd<true, true>), g, b, 0, st, a);
     else if (a.offs) hipLaunchKernelGGL((k_composite_bwd<true, false>), g, b, 0, st, a);
     else if (tickets) hipLaunchKernelGGL((k_composite_bwd<false, true>), g, b, 0, st, a);

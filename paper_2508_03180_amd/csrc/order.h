@@ -53,8 +53,8 @@ namespace dgs {
 // end only (with 2 of 4 heavy the step of 1343 us for 1285), and where there can
 // be more of them than wavefronts also the first by ticket (its kernel 599 us,
 // 615 with static first ones, 625 when it took the forward's list, whose quarters
-// it walked as halves in the places of cheaper items; where all get an item at
-// once, tickets cost 5 us: 186 / 191 at 301 x 203, and 780 / 808 at 640 x 360).
+// it walked as halves in the places of cheaper items; with few items tickets
+// cost 5 us: 186 / 191 at 301 x 203, and 780 / 808 at 640 x 360).
 constexpr int kQueues = kXcds;
 constexpr int kQueueStride = 32;  // words
 constexpr int kQueueWords = kQueueStride * (1 + kQueues);  // word 1: item count, line 1 + q: counter q
@@ -185,6 +185,21 @@ __device__ __forceinline__ uint32_t first_item(int wave, uint32_t n, ItemSource&
     const uint32_t i = (uint32_t)slot * gridDim.x + blockIdx.x;
     if (n <= src.waves || src.heavy) return i;
     return n - 1 - (i - src.heads);
+}
+
+// First item where every wavefront is heavy and items may be fewer than
+// wavefronts: they fill as few workgroups as they can, but one on every CU
+// before a second.  Taken from the first wavefronts of all workgroups instead, the
+// 1840 halves of a 640 x 360 frame shared SIMDs while others had none (20,000
+// ragged cells: backward 605 us, 461 packed; by ticket 477).
+constexpr uint32_t kCus = 256;
+template <int W>
+__device__ __forceinline__ uint32_t first_item_packed(int wave, uint32_t n, ItemSource& src) {
+    const uint32_t i = first_item<W, W>(wave, n, src);
+    if (n > src.waves) return i;
+    const uint32_t blocks = max((n + W - 1) / W, min(gridDim.x, kCus));
+    const uint32_t slot = (uint32_t)(wave + (int)(blockIdx.x >> 8)) & (W - 1);
+    return blockIdx.x < blocks ? slot * blocks + blockIdx.x : n;
 }
 
 // The wavefront's next item (n: none left).  A counter holds the items taken

@@ -62,6 +62,7 @@ def test_gradients_do_not_depend_on_the_other_items(order, n):
     assert float(alone["means"].abs().max()) > 0
     wide = beside(s, 4000, n)
     for other in (grads(order, wide, dict(cam, width=1024), n),  # 64 tiles
+                  grads(order, wide, dict(cam, width=1024), n, height=304),  # 1216: more than a workgroup per CU
                   grads(order, wide, dict(cam, width=1024), n, height=1024)):  # 4096 tiles: tickets
         for k in alone:
             assert torch.equal(alone[k], other[k]), k
