@@ -37,13 +37,12 @@ __device__ __forceinline__ int row_shift(int row, uint32_t len, uint32_t split_l
     return len >= split_len ? row & 4 : row & 12;
 }
 
-// Block columns (bit x: column x) holding an active pixel in a strip, from
-// the ballot of the strip's active lanes.
+// Block columns (bit x: column x) holding an active pixel in a strip of 16 x 4,
+// from the ballot of the strip's active lanes.
 template <int NS>
 __device__ inline uint32_t active_columns(uint64_t m) {
     uint32_t c = (uint32_t)(m | (m >> 32));
     c |= c >> 16;
-    if constexpr (NS == 1) c |= c >> 8;
     return c & ((1u << Block<NS>::kCols) - 1u);
 }
 

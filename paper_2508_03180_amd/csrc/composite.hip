@@ -80,27 +80,56 @@ __device__ inline void load_gauss_chunk(const CompositeArgs& a, uint32_t pos, ui
     q.r2 = p[2];
 }
 
+// What a record's box covers of the block: its columns (bit x for column bx + x),
+// for a quarter its pixels (the bit of each one's lane).  Nothing when it misses
+// the block.
+template <int NS>
+struct BoxCover {
+    uint32_t cols = 0;
+    // may the record hit one of the pixels `am` (lanes of a strip that it touches)?
+    __device__ __forceinline__ bool meets(uint64_t am) const { return (cols & active_columns<NS>(am)) != 0u; }
+};
+// A quarter's 64 pixels are one strip: by columns alone, records below a skyline
+// met the sky's pixels above them, which blend to the list's end (64 x 227 pixels
+// of a street view, 74,000 cells of 11: frame 2373 -> 1657 us).
+template <>
+struct BoxCover<1> {
+    uint32_t lo = 0, hi = 0;
+    __device__ __forceinline__ bool meets(uint64_t am) const {
+        return ((lo & (uint32_t)am) | (hi & (uint32_t)(am >> 32))) != 0u;
+    }
+};
+
 // Ballots of the owned strips each lane's record touches: B[j] for strip j of
 // the block.  The block's origin is wavefront-uniform, so the ballots stay in
 // scalar registers.
-// Also returns, per lane, its record's strip bits (sm) and the block columns
-// its box covers (cols, bit x for column bx + x; 0 when it misses the block).
+// Also returns, per lane, what its record's box covers.
 template <int NS>
-__device__ inline void strip_ballots(const Chunk& q, int bx, int by, uint64_t* B, uint32_t& sm, uint32_t& cols) {
+__device__ inline void strip_ballots(const Chunk& q, int bx, int by, uint64_t* B, BoxCover<NS>& box) {
     constexpr int W = Block<NS>::kCols, R = Block<NS>::kRows;
-    sm = 0;
-    cols = 0;
+    uint32_t sm = 0;  // strip bits
+    box = BoxCover<NS>();
     if (q.ok) {
         const int x0 = __float_as_int(q.r2.y), y0 = __float_as_int(q.r2.z);
         const uint32_t wxy = __float_as_uint(q.r2.w);
         const int x1 = x0 + (int)(wxy & 0xffffu), y1 = y0 + (int)(wxy >> 16);
         if (x0 <= bx + W - 1 && x1 >= bx) {
             const int lo = max(x0, bx) - bx, hi = min(x1, bx + W - 1) - bx;
-            cols = ((2u << (hi - lo)) - 1u) << lo;
+            const uint32_t cols = ((2u << (hi - lo)) - 1u) << lo;
 #pragma unroll
             for (int j = 0; j < NS; j++) {
                 const int r0 = by + R * j;
                 if (y0 <= r0 + R - 1 && y1 >= r0) sm |= 1u << j;
+            }
+            if constexpr (NS == 1) {
+                if (sm) {
+                    const int first = max(y0, by) - by, last = min(y1, by + R - 1) - by;
+                    const uint64_t rows = (~0ull >> (56 - 8 * last)) & (~0ull << (8 * first));
+                    box.lo = cols * 0x01010101u & (uint32_t)rows;
+                    box.hi = cols * 0x01010101u & (uint32_t)(rows >> 32);
+                }
+            } else {
+                box.cols = cols;
             }
         }
     }
@@ -273,8 +302,8 @@ __device__ inline void duplex_tile(const CompositeArgs& a, const FrameView& f, i
         }
         store_chunk(lds, lane, q);
         uint64_t B[NS];
-        uint32_t rsm, rcols;  // this lane's record: strips and tile columns its box touches
-        strip_ballots<NS>(q, bl.x, bl.y, B, rsm, rcols);
+        BoxCover<NS> box;  // of this lane's record
+        strip_ballots<NS>(q, bl.x, bl.y, B, box);
         const float cv = q.v;
         const uint32_t next = pos + nch;
         if (next < end) load_cell_chunk<RAGGED>(a, next, end, lane, q);
@@ -328,8 +357,7 @@ __device__ inline void duplex_tile(const CompositeArgs& a, const FrameView& f, i
                             continue;
                         }
                         // B[j]: the records touching strip j
-                        const uint32_t ac = active_columns<NS>(am[j]);
-                        mj[j] = (uint32_t)((__ballot((rcols & ac) != 0u) & B[j]) >> base) & cm;
+                        mj[j] = (uint32_t)((__ballot(box.meets(am[j])) & B[j]) >> base) & cm;
                         live |= mj[j];
                     }
                     any = live;
@@ -519,8 +547,8 @@ __device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, in
         const int n = q.nch;
         store_chunk(lds, lane, q);
         uint64_t B[NS], any = 0;
-        uint32_t rsm, rcols;
-        strip_ballots<NS>(q, bl.x, bl.y, B, rsm, rcols);
+        BoxCover<NS> box;  // of this lane's record
+        strip_ballots<NS>(q, bl.x, bl.y, B, box);
 #pragma unroll
         for (int j = 0; j < NS; j++) any |= B[j];
         // a quarter's termination once per chunk, however few of its records touch
@@ -545,8 +573,7 @@ __device__ inline void alpha_tile(const CompositeArgs& a, const FrameView& f, in
                 // touching strip j
                 const uint64_t am = __ballot(!(T[j] < eps)) & inbm[j];
                 amall |= am;
-                const uint32_t ac = active_columns<NS>(am);
-                live |= __ballot((rcols & ac) != 0u) & B[j];
+                live |= __ballot(box.meets(am)) & B[j];
             }
             if (!amall) alive = false;
             any = amall ? any & live : 0;
