@@ -349,12 +349,12 @@ dgs_status dgs_read_decoded(dgs_ctx ctx, float* means, float* scales, float* rot
  * context stream at the boundaries of its stages (and runs all of a frame on
  * that stream, so the stages do not overlap):
  *   0 cell preprocess (or nothing in alpha mode), 1 Gaussian projection,
- *   2 depth sort of the primitives (empty with the per-tile list order),
- *   3 scan + key emission, 4 radix sort of the keys on their tile bits,
- *   5 tile ranges, 6 per-tile depth order (empty with the global list
- *   order; it also builds the compositor's work queue), 7 compositor work
- *   queue (empty with the per-tile list order), 8 the compositor kernel
- *   alone. */
+ *   2 depth sort of the primitives, 3 offsets + key emission,
+ *   4 radix sort of the keys on their tile bits, 5 tile ranges,
+ *   6 per-tile depth order (it also builds the compositor's work queue),
+ *   7 compositor work queue, 8 the compositor kernel alone.
+ * With the per-tile list order, stage 4 is the counting of the keys into
+ * their tiles and 2, 3, 5 and 7 are empty; with the global one, 6 is. */
 #define DGS_NUM_STAGES 9
 dgs_status dgs_set_timing(dgs_ctx ctx, int32_t enable);
 
@@ -371,15 +371,15 @@ dgs_status dgs_sort_pairs(dgs_ctx ctx, uint64_t* keys, uint32_t* values, int64_t
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * sort as dgs_sort_pairs, with the same results, whose scratch memory (the
- * ping-pong key/value buffers and digit counts, ~13.3 MB) is one static device array per GPU, held from library load until
- * the process ends.  It calls no hipMalloc, hipFree or allocating routine;
- * it enqueues on the context's stream (kernels and device-to-device copies,
- * no memset).  n above DGS_SORT_NOALLOC_MAX_KEYS returns DGS_ERR_INVALID_ARG
+ * ping-pong key/value buffers and digit counts, ~13.3 MB) is one static device
+ * array per GPU, held from library load until the process ends.  It calls no
+ * hipMalloc, hipFree or allocating routine; it enqueues on the context's
+ * stream (kernels and device-to-device copies, no memset).  n above DGS_SORT_NOALLOC_MAX_KEYS returns DGS_ERR_INVALID_ARG
  * and enqueues nothing.  All calls on one GPU share that GPU's array, from
  * every context and thread: calls whose work overlaps on one GPU (different
  * streams, or threads) race and give undefined results; serialise them.
- * Device-side errors (a look-back wait that timed out) are reported by
- * dgs_sync on the context. */
+ * No workgroup of the sort waits for another, so it raises no device-side
+ * error of its own. */
 #define DGS_SORT_NOALLOC_MAX_KEYS (1 << 20)
 dgs_status dgs_sort_pairs_noalloc(dgs_ctx ctx, uint64_t* keys, uint32_t* values, int64_t n, int32_t key_bits);
 

@@ -31,9 +31,10 @@ hipError_t grow(T*& p, int64_t want, hipStream_t st) {
     return hipMalloc((void**)&p, sizeof(T) * (size_t)(want > 0 ? want : 1));
 }
 
-// Look-back words start zeroed (epoch 0 is never used).  The zeroing is a fill kernel on the context's stream, ordered before the
-// frames that use the buffer: a null-stream memset is not ordered with a
-// non-blocking stream and could erase status words in the middle of a sort.
+// Look-back words start zeroed (epoch 0 is never used).  The zeroing is a
+// fill kernel on the context's stream, ordered before the frames that use the
+// buffer: a null-stream memset is not ordered with a non-blocking stream and
+// could erase status words in the middle of a scan.
 hipError_t grow_zeroed(uint64_t*& p, int64_t want, hipStream_t st) {
     hipError_t e = grow(p, want, st);
     if (e == hipSuccess) {
@@ -696,9 +697,9 @@ dgs_status dgs_internal_render(dgs_ctx c, const dgs_scene* s, const dgs_camera* 
     const uint32_t cap = (uint32_t)c->cap_keys;
     hipStream_t q = c->stream;
     // the lists' depth order: a depth sort of the primitives (ties by id)
-    // before the key emission, or, when the tile lists are short, a sort of
-    // each tile's run after the tile sort (the same order); with the second
-    // stream, the work queue is then built there beside the per-tile sort
+    // before the key emission, or, when the tile lists are short, entries
+    // counted into their tiles and a sort of each tile's run (the same order),
+    // whose launch also builds the work queue
     const FrameLoad load = expect ? *expect : dgs_internal_load(c);
     const int chunks = dgs_internal_per_tile(c, load, tiles, cells)
                            ? bin_chunks(P, k.TX, k.TY, 2 * c->cap_keys, c->sort_status_cap / 2)

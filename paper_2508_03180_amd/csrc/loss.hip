@@ -26,9 +26,9 @@
 //               without one.
 // The rows are unrolled by 11, the period of the register rings (unrolled
 // whole, 42 rows were more code than the instruction cache holds).  The
-// forward is bound by its VALU work (237 instructions a row, of them 110
-// multiply-adds and 33 products; keeping the products in the row buffer
-// instead took 61 us for 54), the backward by memory (five planes read, one
+// forward is bound by its VALU work (235 instructions a row, of them 110
+// multiply-adds and 33 products for the sums; keeping the products in the row
+// buffer instead took 61 us for 54), the backward by memory (five planes read, one
 // written): 3 x 1600 x 1200 54 and 42 us, 71 and 49 before; 3 x 843 x 178,
 // whose 32-row strips left most SIMDs idle, 16 and 13 us, 35 and 26 before.
 #include <math.h>

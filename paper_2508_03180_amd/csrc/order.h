@@ -21,11 +21,11 @@ namespace dgs {
 // of keys in runs of more than kLongRunKeys entries, for the host's choice
 // of list order.
 //
-// A wavefront alone issues one instruction every four cycles: a half-tile
-// item takes ~340 cycles per member it meets (80 instructions, 45 of them
-// vector ones) however idle the chip is, a quarter (8 x 8 pixels) ~160 and
-// meets fewer members, but spends a fifth more vector instructions and twice
-// the LDS reads on a tile.  So tiles whose list is longer than the frame's
+// A wavefront alone issues one instruction every four cycles, however idle
+// the chip is: a half-tile item spends 58 on each member it meets (40 of them
+// vector ones), a quarter (8 x 8 pixels; four members at a time) 40 (28), and
+// meets fewer members, but over a tile that is 40% more vector instructions and
+// twice the LDS reads.  So tiles whose list is longer than the frame's
 // entries per SIMD (kSimds), which would outlast the rest of the launch, are
 // cut in quarters; of the others those of at least split_len entries in
 // halves.  Quarters from an eighth, a quarter, half and all of that length
@@ -78,8 +78,10 @@ __device__ __forceinline__ SplitRule split_rule_bwd(uint32_t split_len) { return
 
 __device__ __forceinline__ void tile_items(uint32_t len, SplitRule r, uint32_t& n, uint32_t& cls) {
     n = len >= r.quarter ? 4u : len >= r.half ? 2u : 1u;
-    // vector instructions per member of a whole-tile (4 strips), a half (2
-    // strips) and a quarter walk, counted in the compiled member loop
+    // Relative costs per member of a whole-tile (4 strips), a half (2 strips)
+    // and a quarter walk: vector instructions of its member loop as first
+    // counted.  The loops have 70, 40 and 28 now, but with those as costs a
+    // ragged 1280 x 720 frame is 1.1% slower and 1920 x 1080 the same.
     const uint32_t w = n == 4u ? 29u : n == 2u ? 45u : 77u;
     const uint32_t c = (uint32_t)min((uint64_t)len * w >> 5, (uint64_t)kOrderClasses - 1u);
     cls = c;

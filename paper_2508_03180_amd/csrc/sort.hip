@@ -23,7 +23,9 @@ namespace dgs {
 // are resident at once.  Sorts of fewer than 2^19 keys, which would leave half
 // of the CUs idle, take partitions of 1024 in workgroups of 256 threads
 // (47-bit sorts of 250,000 and 500,000 keys: 93 and 107 us, 110 and 121 with
-// the large partitions).
+// the large partitions).  The size is chosen on the host, by the key count of a
+// caller's sort and of a frame's depth sort, by the capacity of its key sort (at
+// least 2^20 unless reserved smaller).
 constexpr int kSmallPart = 1024;
 constexpr int64_t kSmallSort = (int64_t)1 << 19;
 // A table of at most this many rows is summed by the scatter itself: 47-bit

@@ -11,13 +11,13 @@
 // bitonic network whose exchanges between entries less than 64 apart are
 // cross-lane moves (DPP and row swaps, no LDS) and the others moves between
 // a lane's own slots.  The workgroup then sorts its longer runs one at a
-// time with the same network spread over its wavefronts, up to 8 slots per
-// lane (2048 entries), only the exchanges between wavefronts going through
-// LDS (at most three of its 66 steps).  Runs longer than that are sorted in
-// chunks of 2048 into a spare buffer and merged pairwise between that buffer
-// and the run's own entries, each element's place being its index in its
-// half plus the number of smaller elements in the other half (binary
-// search).  The sorted ids go to vals, and to vcopy when set.  Every helper
+// time with the same network spread over its wavefronts, up to 4 slots per
+// lane (1024 entries), only the exchanges between wavefronts going through
+// LDS (at most three of its 55 steps).  Runs longer than that are sorted in
+// chunks of 1024 (of 2048 by the 16 wavefronts of k_long_sort) into a spare
+// buffer and merged pairwise between that buffer and the run's own entries,
+// each element's place being its index in its half plus the number of smaller
+// elements in the other half (binary search).  The sorted ids go to vals, and to vcopy when set.  Every helper
 // is inlined: the kernel makes no calls.
 #include "common.h"
 #include "launch.h"
