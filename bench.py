@@ -79,14 +79,14 @@ BYTES_PROJECT_SH3 = 12 + 12 + 16 + 4 + 192 + 48 + 8
 
 # HBM traffic of one Duplex compositor launch on this workload, from two
 # rocprofv3 --pmc passes (FETCH_SIZE, WRITE_SIZE) scaled by a 1 GiB copy
-# kernel's reading (profiles/composite_traffic_1080p_1M_pmc.md): 245.897 MB
-# read + 51.003 MB written.  Valid for the compositor sources it was taken
+# kernel's reading (profiles/composite_traffic_1080p_1M_pmc.md): 245.228 MB
+# read + 51.019 MB written.  Valid for the compositor sources it was taken
 # on; reported as null once one of them changes.
-COMPOSITE_TRAFFIC_BYTES = 245.897e6 + 51.003e6
+COMPOSITE_TRAFFIC_BYTES = 245.228e6 + 51.019e6
 COMPOSITE_TRAFFIC_SOURCES = {
-    "paper_2508_03180_amd/csrc/composite.hip": "25913b2c8ba7aecb786f292614905e888847ec54a4f558a1fd276d2ec1d96657",
-    "paper_2508_03180_amd/csrc/common.h": "08964549a45b346424be039493b2786a08bfe524161787e438427f09cad1f075",
-    "paper_2508_03180_amd/csrc/cells.h": "8b85bbb0b3620e5f17f830979a5f6c936979d398acb07cec2383e2dba3df26a1",
+    "paper_2508_03180_amd/csrc/composite.hip": "2b3625b16bc26b6f298f7a9e344925b0c17ca869007908ca02b4e5201867ad76",
+    "paper_2508_03180_amd/csrc/common.h": "ec9881551297965df5c7c56833f700bd9b26008116f56cf2fbe5bb4ecfdc4e3e",
+    "paper_2508_03180_amd/csrc/cells.h": "eb6dc3a6e90f3c3cd8a3cb1defdb0f6723b5673e873e784cb6faaefeec4af826",
 }
 
 
